@@ -2449,13 +2449,8 @@ __device__ __forceinline__ void wave_sort_out(const int32_t* kt, const double* v
 // Numeric, sub-wave lane groups.  T slots of (int32 key, FP64 value); a row
 // with r = row_nnz_i <= T/2 entries.  After accumulation the occupied slots
 // are compacted (group ballot) and each entry's output position is its
-// rank among the row's keys (keys are distinct): for a whole-wave row whose
-// columns span less than 32 T, from a bitmap of the span, else counted with
-// 16-byte LDS reads (or, past 160 entries, by a sort across the wave).
-// Other whole-wave rows of at least 64 entries are ordered through 64
-// buckets of equal column width when no bucket holds more than kBucketMax
-// keys.  Per-group LDS rows are padded so groups start on different banks.
-constexpr int kBucketMax = 24;
+// rank among the row's keys (keys are distinct), counted with 16-byte LDS
+// reads.  Per-group LDS rows are padded so groups start on different banks.
 template <int G, int T, typename VT, bool BATCH = false>
 __global__ void __launch_bounds__(256)
 k_num_group(Work wk,
@@ -2467,6 +2462,7 @@ k_num_group(Work wk,
     const int32_t* perm;
     work_rows(wk, &nrows_bin, &perm);
     constexpr int NG = GroupCfg<G>::NG;
+    static_assert(G < 64, "whole-wave rows have a kernel of their own");
     static_assert(T % G == 0, "the table clears in T / G whole steps of the group");
     // (rows of 16-byte multiples: the rank count reads four keys at a time;
     // the occupied slots are compacted to the front of the table in place)
@@ -2492,15 +2488,9 @@ k_num_group(Work wk,
     const long long a0 = arp[row], a1 = arp[row + 1];
     const long long rp = crp[row];
     const int expect = (int)(crp[row + 1] - rp);
-    // a whole-wave row of one chunk with as many products as outputs has no
-    // two products in one column: they go straight to the table's first
-    // slots, without the hash and the compaction
-    bool direct = false;
-    if (a1 <= a0) {
 #pragma unroll
-        for (int i = 0; i < T / G; ++i) { kt[gl + i * G] = kEmpty; vt[gl + i * G] = 0.0; }
-        lds_fence();
-    }
+    for (int i = 0; i < T / G; ++i) { kt[gl + i * G] = kEmpty; vt[gl + i * G] = 0.0; }
+    lds_fence();
     for (long long c0 = a0; c0 < a1; c0 += G) {
         const long long p = c0 + gl;
         long long len = 0, bst = 0;
@@ -2516,56 +2506,37 @@ k_num_group(Work wk,
         s_off[g][gl] = incl;
         s_bst[g][gl] = bst - (incl - len);
         s_a[g][gl] = a;
-        if (c0 == a0) {                              // group-uniform
-            direct = G == 64 && !cnt_out && a1 - a0 <= G && total == expect && total <= T / 2;
-            if (!direct) {
-#pragma unroll
-                for (int i = 0; i < T / G; ++i) { kt[gl + i * G] = kEmpty; vt[gl + i * G] = 0.0; }
-            }
-        }
         lds_fence();
         const int nact = (int)((a1 - c0) < G ? (a1 - c0) : G);
         int t = -1;                                  // owner of q: one search, then it only moves forward
-        if (direct) {
-            for (long long q = gl; q < total; q += G) {
-                if (t < 0) t = owner_search(s_off[g], nact, q);
-                else while (s_off[g][t] <= q) ++t;
-                const long long bi = s_bst[g][t] + q;
-                kt[q] = bcol[bi];
-                vt[q] = 0.0 + s_a[g][t] * to_f64(bval[bi]);      // (a sum from zero, as in the table: -0 becomes +0)
-            }
-        } else {
-            for (long long q = gl; q < total; q += G) {
-                if (t < 0) t = owner_search(s_off[g], nact, q);
-                else while (s_off[g][t] <= q) ++t;
-                const long long bi = s_bst[g][t] + q;
-                const int32_t j = bcol[bi];
-                const double prod = s_a[g][t] * to_f64(bval[bi]);
-                const int h = hash_slot_of<T>(kt, j, &re);
-                if (h >= 0) atomicAdd(&vt[h], prod);
-            }
+        for (long long q = gl; q < total; q += G) {
+            if (t < 0) t = owner_search(s_off[g], nact, q);
+            else while (s_off[g][t] <= q) ++t;
+            const long long bi = s_bst[g][t] + q;
+            const int32_t j = bcol[bi];
+            const double prod = s_a[g][t] * to_f64(bval[bi]);
+            const int h = hash_slot_of<T>(kt, j, &re);
+            if (h >= 0) atomicAdd(&vt[h], prod);
         }
         lds_fence();
     }
     // compact the occupied slots to the front, in place: a slot moves to a
     // position no later than its own, and the group reads its G slots before
     // any of them is written
-    int n = direct ? expect : 0;
-    if (!direct) {
+    int n = 0;
 #pragma unroll
-        for (int s0 = 0; s0 < T; s0 += G) {
-            const int s = s0 + gl;
-            const int32_t k = kt[s];
-            const double v = vt[s];
-            const bool occ = k != kEmpty;
-            const uint64_t mask = group_ballot<G>(occ, lane);
-            if (occ) {
-                const int pos = n + __builtin_popcountll(mask & ((1ull << gl) - 1));
-                kt[pos] = k;
-                vt[pos] = v;
-            }
-            n += __builtin_popcountll(mask);
+    for (int s0 = 0; s0 < T; s0 += G) {
+        const int s = s0 + gl;
+        const int32_t k = kt[s];
+        const double v = vt[s];
+        const bool occ = k != kEmpty;
+        const uint64_t mask = group_ballot<G>(occ, lane);
+        if (occ) {
+            const int pos = n + __builtin_popcountll(mask & ((1ull << gl) - 1));
+            kt[pos] = k;
+            vt[pos] = v;
         }
+        n += __builtin_popcountll(mask);
     }
     const bool failed = group_ballot<G>(re != 0, lane) != 0;
     if (cnt_out) {                               // capacity mode
@@ -2576,109 +2547,6 @@ k_num_group(Work wk,
         if (gl == 0) atomicOr(&info->err, failed ? kErrProbe : kErrCount);
         lds_fence();
         continue;
-    }
-    if constexpr (G == 64) {
-        // rows whose columns span less than 32 T: column order from a
-        // bitmap of the span (the free upper half of the value table, T / 2
-        // words) and a rank per word (the free upper half of the key
-        // table), O(n / 64 + T / 128) steps a lane instead of a sort
-        int kmn = 0x7fffffff, kmx = -1;
-        for (int e = lane; e < n; e += 64) {
-            kmn = min(kmn, kt[e]);
-            kmx = max(kmx, kt[e]);
-        }
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) {
-            kmn = min(kmn, __shfl_xor(kmn, d));
-            kmx = max(kmx, __shfl_xor(kmx, d));
-        }
-        if (n > 0 && (long long)kmx - kmn < 32LL * T) {       // wave-uniform
-            unsigned long long* bm = reinterpret_cast<unsigned long long*>(vt + T / 2);
-            int* wr = kt + T / 2;
-            const int nwd = ((kmx - kmn) >> 6) + 1;            // <= T / 2
-            for (int i = lane; i < nwd; i += 64) bm[i] = 0ull;
-            lds_fence();
-            for (int e = lane; e < n; e += 64) {
-                const int d = kt[e] - kmn;
-                atomicOr(&bm[d >> 6], 1ull << (d & 63));
-            }
-            lds_fence();
-            // lane l ranks the E consecutive words from l E
-            const int E = (nwd + 63) >> 6;
-            const int i0 = lane * E, i1 = min(i0 + E, nwd);
-            int loc = 0;
-            for (int i = i0; i < i1; ++i) loc += __builtin_popcountll(bm[i]);
-            int run = (int)group_incl_scan<64>(loc, lane) - loc;
-            for (int i = i0; i < i1; ++i) {
-                wr[i] = run;
-                run += __builtin_popcountll(bm[i]);
-            }
-            lds_fence();
-            for (int e = lane; e < n; e += 64) {
-                const int32_t k = kt[e];
-                const int d = k - kmn;
-                const int rank = wr[d >> 6] + __builtin_popcountll(bm[d >> 6] & ((1ull << (d & 63)) - 1ull));
-                ccol[rp + rank] = k;
-                cval[rp + rank] = (VT)vt[e];
-            }
-            lds_fence();
-            continue;
-        }
-        // (the counters and slots below need T >= 256)
-        if (T >= 256 && n >= 64) {                            // wave-uniform
-            // wider rows: the keys counted into 64 buckets of equal column
-            // width, placed bucket by bucket, and each ranked by comparison
-            // within its bucket; taken while no bucket holds more than
-            // kBucketMax keys (else the sort or the rank count below)
-            int* cnt = reinterpret_cast<int*>(vt + T / 2);    // the free upper half
-            int* cur = cnt + 64;
-            int* sidx = cur + 64;                             // n <= T / 2 entries
-            int32_t* skey = kt + T / 2;                       // n <= T / 2 entries
-            const float scale = 64.0f / (float)((long long)kmx - kmn + 1);
-            auto bucket = [&](int32_t k) { return min(63, (int)((float)(k - kmn) * scale)); };
-            cnt[lane] = 0;
-            lds_fence();
-            for (int e = lane; e < n; e += 64) atomicAdd(&cnt[bucket(kt[e])], 1);
-            lds_fence();
-            const int c = cnt[lane];
-            int cmax = c;
-#pragma unroll
-            for (int d = 32; d > 0; d >>= 1) cmax = max(cmax, __shfl_xor(cmax, d));
-            if (cmax <= kBucketMax) {                         // wave-uniform
-                cur[lane] = (int)group_incl_scan<64>(c, lane) - c;
-                lds_fence();
-                for (int e = lane; e < n; e += 64) {
-                    const int32_t k = kt[e];
-                    const int slot = atomicAdd(&cur[bucket(k)], 1);
-                    skey[slot] = k;
-                    sidx[slot] = e;
-                }
-                lds_fence();
-                // cur[b] is now the end of bucket b
-                for (int sl = lane; sl < n; sl += 64) {
-                    const int32_t k = skey[sl];
-                    const int b = bucket(k);
-                    const int b1 = cur[b], b0 = b1 - cnt[b];
-                    int rank = b0;
-                    for (int j = b0; j < b1; ++j) rank += skey[j] < k;
-                    ccol[rp + rank] = k;
-                    cval[rp + rank] = (VT)vt[sidx[sl]];
-                }
-                lds_fence();
-                continue;
-            }
-        }
-    }
-    if constexpr (G == 64 && T / 2 > 128) {
-        // long rows: a bitonic sort across the wave (the rank count below
-        // costs n / 4 LDS reads and n compares per output, n / 64 outputs a
-        // lane; the sort of T / 2 elements costs less from about 160 on)
-        if (n > 160) {                                  // wave-uniform (a row per wave)
-            lds_fence();
-            wave_sort_out<T / 128>(kt, vt, n, ccol + rp, cval + rp, lane);
-            lds_fence();
-            continue;
-        }
     }
     const int n4 = (n + 3) & ~3;
     if (gl < n4 - n) kt[n + gl] = 0x7fffffff;         // pads sort after every key
@@ -3749,3 +3617,5 @@ k_validate(long long nrows, long long ncols, long long nnz, const int64_t* __res
 }
 
 }  // namespace msp
+
+#include "wave_rows.hpp"

@@ -68,7 +68,7 @@ static void add_small_bins(BinPlan& p, const msp_tuning& t, int limit, bool nume
         } else if (T <= 64) {
             const int R = (T == 32 ? (t.group_scale == 0 ? 12 : 8 >> (t.group_scale - 1)) : 8 >> t.group_scale);
             add_bin(p, umax[i], BinSpec{Kind::Batch, R, T});
-        } else if (T <= 512) {
+        } else if (T <= 1024) {
             int G = std::min(64, g0[i] << t.group_scale);
             G = std::min(G, T / 2);
             add_bin(p, umax[i], BinSpec{Kind::Group, G, T});
@@ -141,9 +141,10 @@ static int win_lds(const msp_handle* h) {
 }
 
 #define MSP_GROUP_SHAPES(X) \
-    X(8, 32) X(16, 32) X(8, 64) X(16, 64) X(32, 64) X(16, 128) X(32, 128) X(64, 128) \
-    X(32, 256) X(64, 256) X(64, 512)
-#define MSP_SYM_GROUP_SHAPES(X) MSP_GROUP_SHAPES(X) X(64, 1024) X(64, 2048)
+    X(8, 32) X(16, 32) X(8, 64) X(16, 64) X(32, 64) X(16, 128) X(32, 128) \
+    X(32, 256)
+#define MSP_NUM_ROW_SHAPES(X) X(128) X(256) X(512) X(1024)
+#define MSP_SYM_GROUP_SHAPES(X) MSP_GROUP_SHAPES(X) X(64, 128) X(64, 256) X(64, 512) X(64, 1024) X(64, 2048)
 #define MSP_SYM_BATCH_SHAPES(X) X(32, 16) X(64, 16) X(128, 8) X(256, 4) X(512, 2)
 #define MSP_NUM_BATCH_SHAPES(X) X(32, 12) X(32, 8) X(32, 4) X(64, 8) X(64, 4) X(64, 2)
 #define MSP_SYM_BLOCK_SHAPES(X) \
@@ -162,6 +163,9 @@ static bool spec_supported(const BinSpec& sp, bool numeric) {
         case Kind::Group:
 #define X(G, T) if (sp.lanes == G && sp.slots == T) return true;
             if (numeric) { MSP_GROUP_SHAPES(X) } else { MSP_SYM_GROUP_SHAPES(X) }
+#undef X
+#define X(T) if (numeric && sp.lanes == 64 && sp.slots == T) return true;
+            MSP_NUM_ROW_SHAPES(X)
 #undef X
             return false;
         case Kind::Block:
@@ -249,7 +253,7 @@ msp_status configure_kernels(msp_handle* h) {
 // Grid of a persistent lane-group kernel: as many workgroups as can be
 // resident (occupancy from the kernel's registers and LDS), a multiple of 8
 // for the XCD-aware order, and no more than the rows need.
-static int group_grid(msp_handle* h, const void* fn, int rows, int rows_per_block) {
+static int group_grid(msp_handle* h, const void* fn, int rows, int rows_per_block, int threads = 256) {
     // shared by every handle, and handles may be used from several threads
     static std::mutex occ_mutex;
     static std::unordered_map<const void*, int> occ_cache;
@@ -260,7 +264,7 @@ static int group_grid(msp_handle* h, const void* fn, int rows, int rows_per_bloc
         if (it != occ_cache.end()) occ = it->second;
     }
     if (occ == 0) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, 256, 0) != hipSuccess || occ < 1) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, threads, 0) != hipSuccess || occ < 1) {
             (void)hipGetLastError();
             occ = 1;
         }
@@ -440,6 +444,16 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
         return launch_check("k_num_group");                                                                \
     }
         MSP_GROUP_SHAPES(X)
+#undef X
+        // one wave per row
+#define X(T)                                                                                               \
+    if (s.lanes == 64 && s.slots == T) {                                                                   \
+        const int grid = group_grid(h, (const void*)k_num_row<T, VT, BATCH>, rows, 1, 64);                \
+        k_num_row<T, VT, BATCH><<<grid, 64, 0, st>>>(wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp,   \
+                                                     ccol, cval, cnt_out, info, mp);                      \
+        return launch_check("k_num_row");                                                                  \
+    }
+        MSP_NUM_ROW_SHAPES(X)
 #undef X
     } else if (s.kind == Kind::Block) {
         const int grid = std::min(rows, 4 * h->num_cu);

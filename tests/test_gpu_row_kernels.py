@@ -1,0 +1,118 @@
+"""Edges of the whole-wave row kernels against the oracle: product counts at
+the register and sort limits, column spans at the bitmap's, buckets at their
+fullest, empty B rows, more A entries than lanes.  Structure identical,
+values within the repository's bounds (1e-12 FP64, 1e-5 FP32 times the sum of
+|a||b|: a row of at most 1024 FP64 additions is off by less than 1024 2^-53)."""
+import numpy as np
+import pytest
+
+from paper_2112_10037_amd import binding, gen
+
+from gpu_util import check_full
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def h():
+    hh = binding.Handle(0)
+    yield hh
+    hh.close()
+
+
+def _csr(rows, ncols, rng, dtype):
+    rp = np.zeros(len(rows) + 1, np.int64)
+    rp[1:] = np.cumsum([len(r) for r in rows])
+    col = np.concatenate([np.sort(np.asarray(r)) for r in rows]).astype(np.int32) if rp[-1] else np.zeros(0, np.int32)
+    return gen.CSR(len(rows), ncols, rp, col, (2 * rng.random(int(rp[-1])) - 1).astype(dtype))
+
+
+def _lengths(total, na):
+    """na B-row lengths that add up to total, some of them 0 when na allows."""
+    out = np.full(na, total // na)
+    out[: total % na] += 1
+    return out
+
+
+# name: (total products, A entries, distinct columns to draw from, first and last column)
+CASES = {
+    "narrow_full": (768, 64, 500, 0, 39_999),
+    "narrow_over": (769, 64, 500, 0, 39_999),
+    "narrow_one_entry": (65, 1, 65, 7, 8_000),
+    "narrow_step": (256, 32, 240, 3, 300),
+    "narrow_step_over": (257, 32, 240, 3, 300),
+    "span_last_narrow": (200, 20, 180, 5, 5 + 43_007),
+    "span_first_wide": (200, 20, 180, 5, 5 + 43_008),
+    "wide_sort_full": (512, 40, 250, 0, 999_999),
+    "wide_sort_over": (513, 40, 250, 0, 999_999),
+    "wide_sort_full_512": (768, 48, 500, 0, 999_999),
+    "wide_sort_over_512": (769, 48, 500, 0, 999_999),
+    "wide_one_step": (64, 8, 64, 0, 2_000_000),
+    "wide_lanes_plus_one": (65, 13, 65, 0, 2_000_000),
+    "symbolic_256": (256, 30, 4000, 0, 900_000),
+    "symbolic_257": (257, 30, 4000, 0, 900_000),
+    "symbolic_512": (512, 30, 40_000, 0, 900_000),
+    "symbolic_513": (513, 30, 40_000, 0, 900_000),
+    "symbolic_1024": (1024, 50, 900, 0, 900_000),
+    "entries_64": (200, 64, 150, 0, 900_000),
+    "entries_65": (200, 65, 150, 0, 900_000),
+    "entries_65_narrow": (200, 65, 150, 0, 900),
+}
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_row_kernel_edges(h, name, dtype):
+    total, na, pool, lo, hi = CASES[name]
+    rng = np.random.default_rng(total * 131 + na)
+    n = hi + 1
+    arows, brows = [], []
+    for _ in range(24):
+        cols = np.unique(np.concatenate([[lo, hi], rng.integers(lo, hi + 1, size=4 * pool)]))
+        cols = np.sort(np.concatenate([[lo, hi], rng.permutation(cols[1:-1])[: pool - 2]]))
+        first = len(brows)
+        # empty B rows first, in the middle and last, where the entries leave room
+        empty = [0, na // 2, na - 1] if 8 <= na < 64 else []
+        lens = np.zeros(na, np.int64)
+        lens[[i for i in range(na) if i not in empty]] = _lengths(total, na - len(empty))
+        ends = int(np.argmax(lens >= 2))             # the B row that holds the span's ends
+        for i, length in enumerate(lens):
+            if i == ends:
+                pick = np.concatenate([[0, len(cols) - 1], 1 + rng.permutation(len(cols) - 2)[: length - 2]])
+            else:
+                pick = rng.permutation(len(cols))[:length]
+            brows.append(cols[pick])
+        arows.append(np.arange(first, first + na))
+    A = _csr(arows, len(brows), rng, dtype)
+    B = _csr(brows, n, rng, dtype)
+    check_full(h, A, B)
+    check_full(h, A, B, tuning=(1, 0, 4096, 128, 8))
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("same", [24, 25])
+def test_row_kernel_fullest_bucket(h, same, dtype):
+    """`same` products share one column, the others spread over two million."""
+    rng = np.random.default_rng(same)
+    arows, brows = [], []
+    for _ in range(12):
+        first = len(brows)
+        other = 10 + rng.permutation(2_000_000)[: 9 * same]
+        for i in range(same):
+            brows.append(np.concatenate([[3], other[9 * i: 9 * i + 9]]))
+        arows.append(np.arange(first, first + same))
+    A = _csr(arows, len(brows), rng, dtype)
+    B = _csr(brows, 2_000_010, rng, dtype)
+    check_full(h, A, B)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_row_kernel_many_rows_per_wave(h, dtype):
+    """More rows than waves, long, short and empty ones in turn, so that every
+    wave loads rows of one path while it works on another's."""
+    rng = np.random.default_rng(5)
+    k = rng.choice([0, 1, 9, 16, 30, 70], size=24_000, p=[0.1, 0.1, 0.2, 0.3, 0.2, 0.1])
+    A = gen.erdos_renyi(24_000, 5_000, k, seed=6, dtype=dtype)
+    kb = rng.integers(0, 14, size=5_000)
+    check_full(h, A, gen.erdos_renyi(5_000, 300_000, kb, seed=7, dtype=dtype))
+    check_full(h, A, gen.erdos_renyi(5_000, 3_000, kb, seed=8, dtype=dtype))
