@@ -144,7 +144,7 @@ static int win_lds(const msp_handle* h) {
     X(8, 32) X(16, 32) X(8, 64) X(16, 64) X(32, 64) X(16, 128) X(32, 128) \
     X(32, 256)
 #define MSP_NUM_ROW_SHAPES(X) X(128) X(256) X(512) X(1024)
-#define MSP_SYM_GROUP_SHAPES(X) MSP_GROUP_SHAPES(X) X(64, 128) X(64, 256) X(64, 512) X(64, 1024) X(64, 2048)
+#define MSP_SYM_ROW_SHAPES(X) MSP_NUM_ROW_SHAPES(X) X(2048)
 #define MSP_SYM_BATCH_SHAPES(X) X(32, 16) X(64, 16) X(128, 8) X(256, 4) X(512, 2)
 #define MSP_NUM_BATCH_SHAPES(X) X(32, 12) X(32, 8) X(32, 4) X(64, 8) X(64, 4) X(64, 2)
 #define MSP_SYM_BLOCK_SHAPES(X) \
@@ -162,10 +162,10 @@ static bool spec_supported(const BinSpec& sp, bool numeric) {
             return false;
         case Kind::Group:
 #define X(G, T) if (sp.lanes == G && sp.slots == T) return true;
-            if (numeric) { MSP_GROUP_SHAPES(X) } else { MSP_SYM_GROUP_SHAPES(X) }
+            MSP_GROUP_SHAPES(X)
 #undef X
-#define X(T) if (numeric && sp.lanes == 64 && sp.slots == T) return true;
-            MSP_NUM_ROW_SHAPES(X)
+#define X(T) if (sp.lanes == 64 && sp.slots == T) return true;
+            if (numeric) { MSP_NUM_ROW_SHAPES(X) } else { MSP_SYM_ROW_SHAPES(X) }
 #undef X
             return false;
         case Kind::Block:
@@ -322,7 +322,16 @@ static msp_status launch_symbolic_t(msp_handle* h, const BinSpec& s, Work wk, in
                                                        info, mp);                                     \
         return launch_check("k_sym_group");                                                           \
     }
-        MSP_SYM_GROUP_SHAPES(X)
+        MSP_GROUP_SHAPES(X)
+#undef X
+        // one wave per row
+#define X(T)                                                                                          \
+    if (s.lanes == 64 && s.slots == T) {                                                              \
+        const int grid = group_grid(h, (const void*)k_sym_row<T, BATCH>, rows, 1, 64);               \
+        k_sym_row<T, BATCH><<<grid, 64, 0, st>>>(wk, op.arp, op.acol, op.brp, op.bcol, rnnz, info, mp); \
+        return launch_check("k_sym_row");                                                             \
+    }
+        MSP_SYM_ROW_SHAPES(X)
 #undef X
     } else if (s.kind == Kind::Block) {
         const int grid = std::min(rows, 4 * h->num_cu);

@@ -695,4 +695,219 @@ k_num_row(Work wk,
     if (err) atomicOr(&info->err, err);
 }
 
+// Symbolic, one wave per row of at most T / 2 products (or columns of B).
+//
+// Rows of at most 64 A entries and T / 2 products: the products' columns in
+// registers; within 32 kRowWords columns their bits are counted in a bitmap
+// of the span, else every product joins the list of its column's hash slot
+// (one LDS exchange) and counts unless an earlier member has its column.
+// Other rows: an LDS hash of T keys.
+//
+// Bound by LDS and instruction issue, as k_num_row.  The lists need one
+// returning LDS operation a product and then only reads, where a hash of
+// compare-and-swaps repeats the slow operation on every collision of the
+// wave's unluckiest lane: the 257- to 512-product rows of a uniform matrix of
+// 262,144 rows take 134 us (compare-and-swap four keys a lane at once 573, the
+// kernel before, read first, 326), the 513- to 1024-product ones 78 (148
+// before), the 129- to 256-product ones 62 (103 before).  Bitmap rows: 260,000
+// banded rows 208 -> 142 us, 300,763 27-point rows 626 -> 331 us.
+template <int T, bool BATCH = false>
+__global__ void __launch_bounds__(64, 4)
+k_sym_row(Work wk,
+          const int64_t* __restrict__ arp, const int32_t* __restrict__ acol,
+          const int64_t* __restrict__ brp, const int32_t* __restrict__ bcol,
+          int32_t* __restrict__ row_nnz, DevInfo* info, RowMap mp) {
+    constexpr int R = T / 128, GS = R < kRowStep ? R : kRowStep;
+    int nrows_bin;
+    const int32_t* perm;
+    work_rows(wk, &nrows_bin, &perm);
+    __shared__ long long s_off[65];                 // general path: offsets; else the walk's marks
+    __shared__ long long s_bst[65];
+    // the bitmap; or the lists' heads and members (column, earlier member); or the hash
+    constexpr int H = T <= 1024 ? T / 2 : T / 4;
+    __shared__ __align__(16) int32_t keys[H + T > kRowWords ? H + T : kRowWords];
+    static_assert(R <= 65, "the marks take the offsets' place");
+    const int lane = threadIdx.x;
+    int err = 0;
+    const long long per = (nrows_bin + gridDim.x - 1) / gridDim.x;
+    const long long first = (long long)xcd_block() * per;
+    const long long last = first + per < nrows_bin ? first + per : nrows_bin;
+    if (first >= last) return;
+
+    // the next row is loaded ahead, as in k_num_row
+    struct Head {
+        int row;
+        long long a0, a1, bo;
+    };
+    int listed = 0;
+    auto head_of = [&](long long slot) {
+        Head h;
+        h.row = (int)slot;
+        if (perm) {
+            const int i = (int)(slot - first) & 63;
+            if (i == 0) listed = perm[slot + lane < last ? slot + lane : last - 1];
+            h.row = __builtin_amdgcn_readlane(listed, i);
+        }
+        h.a0 = arp[h.row];
+        h.a1 = arp[h.row + 1];
+        h.bo = row_boff<BATCH>(mp, h.row);
+        return h;
+    };
+    auto load_entry = [&](const Head& h, int* k) {
+        if (h.a1 <= h.a0) return;                   // wave-uniform
+        *k = acol[h.a0 + lane < h.a1 ? h.a0 + lane : h.a1 - 1];
+    };
+    auto load_bounds = [&](const Head& h, int k, long long* b0, long long* b1) {
+        if (h.a1 <= h.a0) return;
+        *b0 = brp[k + h.bo];
+        *b1 = brp[k + h.bo + 1];
+    };
+    Head cur = head_of(first);
+    int k = 0, kn = 0;
+    long long b0 = 0, b1 = 0, b0n = 0, b1n = 0;
+    load_entry(cur, &k);
+    load_bounds(cur, k, &b0, &b1);
+    for (long long slot = first; slot < last; ++slot) {
+        const Head nxt = head_of(slot + 1 < last ? slot + 1 : slot);
+        RowWalk<R> walk;
+        walk.total = 64 * R + 1;
+        if (cur.a1 - cur.a0 <= 64)
+            walk.open(lane, b0, cur.a0 + lane < cur.a1 ? b1 - b0 : 0, reinterpret_cast<unsigned long long*>(s_off),
+                      s_bst, nullptr, 0.0);
+        const int total = walk.total;
+        load_entry(nxt, &kn);
+        int cnt = 0;
+        if (total <= 64 * R) {                      // wave-uniform
+            // lanes past the last product repeat the row's first one
+            int c[R];
+            const long long at0 = s_bst[0];
+#pragma unroll
+            for (int g = 0; g < R; g += GS)
+                if (64 * g < total) {
+                    long long at[GS];
+#pragma unroll
+                    for (int s = g; s < g + GS; ++s) at[s - g] = s_bst[walk.entry(s)] + (64 * s + lane);
+#pragma unroll
+                    for (int s = g; s < g + GS; ++s) c[s] = bcol[64 * s + lane < total ? at[s - g] : at0];
+                }
+            int mn = 0x7fffffff, mx = -1;
+#pragma unroll
+            for (int g = 0; g < R; g += GS)
+                if (64 * g < total) {
+#pragma unroll
+                    for (int s = g; s < g + GS; ++s) {
+                        mn = min(mn, c[s]);
+                        mx = max(mx, c[s]);
+                    }
+                }
+            load_bounds(nxt, kn, &b0n, &b1n);
+            mn = wave_least(mn);
+            mx = wave_most(mx);
+            const int span = total > 0 ? mx - mn : 0;
+            if (span < 32 * kRowWords) {
+                uint32_t* const bm = reinterpret_cast<uint32_t*>(keys);
+                const int nwd = total > 0 ? (span >> 5) + 1 : 0;
+                for (int i = lane * 4; i < nwd; i += 256) *reinterpret_cast<uint4*>(bm + i) = make_uint4(0, 0, 0, 0);
+                lds_fence();
+#pragma unroll
+                for (int g = 0; g < R; g += GS)
+                    if (64 * g < total) {
+#pragma unroll
+                        for (int s = g; s < g + GS; ++s) {
+                            const int d = c[s] - mn;
+                            atomicOr(&bm[d >> 5], 1u << (d & 31));
+                        }
+                    }
+                lds_fence();
+                for (int i = lane * 4; i < nwd; i += 256) {
+                    const uint4 x = *reinterpret_cast<const uint4*>(bm + i);
+                    cnt += __builtin_popcount(x.x) + __builtin_popcount(x.y) + __builtin_popcount(x.z) +
+                           __builtin_popcount(x.w);
+                }
+            } else {
+                int32_t* const head = keys;
+                int2* const list = reinterpret_cast<int2*>(keys + H);
+                for (int i = lane; i < H / 4; i += 64)
+                    reinterpret_cast<int4*>(head)[i] = make_int4(-1, -1, -1, -1);
+                lds_fence();
+                int prev[R];
+#pragma unroll
+                for (int g = 0; g < R; g += GS)
+                    if (64 * g < total) {
+#pragma unroll
+                        for (int s = g; s < g + GS; ++s) {
+                            const int q = 64 * s + lane;
+                            prev[s] = -1;
+                            if (q < total) prev[s] = atomicExch(&head[hash_slot<H>(c[s])], q);
+                        }
+#pragma unroll
+                        for (int s = g; s < g + GS; ++s) {
+                            list[64 * s + lane] = make_int2(c[s], prev[s]);
+                            cnt += 64 * s + lane < total;
+                        }
+                    }
+                lds_fence();
+#pragma unroll
+                for (int g = 0; g < R; g += GS)
+                    if (64 * g < total) {
+                        // the members before this one, GS products a lane at once
+                        while (true) {
+                            bool more = false;
+#pragma unroll
+                            for (int s = g; s < g + GS; ++s) more |= prev[s] >= 0;
+                            if (!__ballot(more)) break;
+                            int2 x[GS];
+#pragma unroll
+                            for (int s = g; s < g + GS; ++s) x[s - g] = list[max(prev[s], 0)];
+#pragma unroll
+                            for (int s = g; s < g + GS; ++s) {
+                                const bool same = prev[s] >= 0 && x[s - g].x == c[s];
+                                cnt -= same;
+                                prev[s] = prev[s] < 0 || same ? -1 : x[s - g].y;
+                            }
+                        }
+                    }
+                lds_fence();
+            }
+        } else {
+            load_bounds(nxt, kn, &b0n, &b1n);
+            for (int i = lane; i < T / 4; i += 64)
+                reinterpret_cast<int4*>(keys)[i] = make_int4(kEmpty, kEmpty, kEmpty, kEmpty);
+            lds_fence();
+            int full = 0;
+            for (long long c0 = cur.a0; c0 < cur.a1; c0 += 64) {
+                const long long p = c0 + lane;
+                long long len = 0, bst = 0;
+                if (p < cur.a1) {
+                    const long long kk = acol[p] + cur.bo;
+                    bst = brp[kk];
+                    len = brp[kk + 1] - bst;
+                }
+                const long long incl = group_incl_scan<64>(len, lane);
+                const long long all = __shfl(incl, 63);
+                s_off[lane] = incl;
+                s_bst[lane] = bst - (incl - len);
+                lds_fence();
+                const int nact = (int)((cur.a1 - c0) < 64 ? (cur.a1 - c0) : 64);
+                int t = -1;                          // owner of q: one search, then it only moves forward
+                for (long long q = lane; q < all; q += 64) {
+                    if (t < 0) t = owner_search(s_off, nact, q);
+                    else while (s_off[t] <= q) ++t;
+                    cnt += hash_insert_key<T>(keys, bcol[s_bst[t] + q], &full);
+                }
+                lds_fence();
+            }
+            if (full) err |= kErrProbe;
+        }
+        cnt = __builtin_amdgcn_readlane(wave_scan(cnt), 63);
+        if (lane == 0) row_nnz[cur.row] = cnt;
+        lds_fence();
+        cur = nxt;
+        k = kn;
+        b0 = b0n;
+        b1 = b1n;
+    }
+    if (err) atomicOr(&info->err, err);
+}
+
 }  // namespace msp
