@@ -108,7 +108,7 @@ typedef struct {
     int32_t block_rows;     /* rows with bound above this (a power of two,
                                32..1024) use one workgroup per row; below it,
                                merges, lane groups or one wave per row (the
-                               wave tables stop at 2048 symbolic keys and 512
+                               wave tables stop at 2048 symbolic keys and 1024
                                numeric slots, beyond which workgroups take
                                over)                                            */
     int32_t merge_k;        /* rows with bound <= 32 and at most merge_k A

@@ -8,7 +8,7 @@
 // (Sec. IV-B3).  On CDNA4 the same sums are formed with per-row accumulators
 // sized by a bound on the row's output:
 //   * a symbolic pass counts row_nnz_i = |union of the column sets| with an
-//     LDS hash of keys (sub-wave lane groups or whole workgroups per row) or
+//     LDS hash, lists or a bitmap (whole waves or workgroups per row) or
 //     an n-bit bitmap for the largest rows;
 //   * a numeric pass adds a_ik * b_kj into an LDS hash of (key, FP64 value)
 //     sized by the exact row_nnz_i, then writes the row in column order (a
@@ -729,72 +729,6 @@ struct GroupCfg {
     static constexpr int BS = 256;
     static constexpr int NG = BS / G;
 };
-
-// Symbolic, sub-wave lane groups: G lanes per row, T key slots per row.
-// rows = perm (bin list) or identity when perm == nullptr.  Every per-group
-// LDS row is padded by one word so that the groups of a wave start on
-// different banks.
-template <int G, int T, bool BATCH = false>
-__global__ void __launch_bounds__(256)
-k_sym_group(Work wk, int m,
-            const int64_t* __restrict__ arp, const int32_t* __restrict__ acol,
-            const int64_t* __restrict__ brp, const int32_t* __restrict__ bcol,
-            int32_t* __restrict__ row_nnz, DevInfo* info, RowMap mp) {
-    constexpr int NG = GroupCfg<G>::NG;
-    static_assert(G < 64, "whole-wave rows have a kernel of their own");
-    static_assert(T % G == 0, "the table clears in T / G whole steps of the group");
-    int nrows_bin;
-    const int32_t* perm;
-    work_rows(wk, &nrows_bin, &perm);
-    __shared__ int32_t keys[NG][T + 1];
-    __shared__ long long s_off[NG][G + 1];
-    __shared__ long long s_bst[NG][G + 1];
-    const int gl = threadIdx.x & (G - 1);
-    const int g = threadIdx.x / G;
-    (void)m;
-    int err = 0;
-    int32_t* kt = keys[g];
-    // persistent: workgroup lb owns the contiguous slot range [lo, hi)
-    const long long per = (nrows_bin + gridDim.x - 1) / gridDim.x;
-    const long long lo = (long long)xcd_block() * per;
-    const long long hi = lo + per < nrows_bin ? lo + per : nrows_bin;
-    for (long long slot = lo + g; slot < hi; slot += NG) {      // group-uniform
-    const int row = perm ? perm[slot] : (int)slot;
-    const long long bo = row_boff<BATCH>(mp, row);
-    const long long a0 = arp[row], a1 = arp[row + 1];
-#pragma unroll
-    for (int i = 0; i < T / G; ++i) kt[gl + i * G] = kEmpty;
-    lds_fence();
-    int cnt = 0;
-    for (long long c0 = a0; c0 < a1; c0 += G) {
-        const long long p = c0 + gl;
-        long long len = 0, bst = 0;
-        if (p < a1) {
-            const long long k = acol[p] + bo;
-            bst = brp[k];
-            len = brp[k + 1] - bst;
-        }
-        const long long incl = group_incl_scan<G>(len, gl);
-        const long long total = __shfl(incl, G - 1, G);
-        s_off[g][gl] = incl;
-        s_bst[g][gl] = bst - (incl - len);
-        lds_fence();
-        const int nact = (int)((a1 - c0) < G ? (a1 - c0) : G);
-        int t = -1;                                  // owner of q: one search, then it only moves forward
-        for (long long q = gl; q < total; q += G) {
-            if (t < 0) t = owner_search(s_off[g], nact, q);
-            else while (s_off[g][t] <= q) ++t;
-            const int32_t j = bcol[s_bst[g][t] + q];
-            cnt += hash_insert_key<T>(kt, j, &err);
-        }
-        lds_fence();
-    }
-    cnt = group_sum<G>(cnt);
-    if (gl == 0) row_nnz[row] = cnt;
-    lds_fence();
-    }
-    if (err) atomicOr(&info->err, kErrProbe);
-}
 
 // Symbolic, one workgroup of BS threads per row, T key slots (LDS).
 template <int BS, int T, bool BATCH = false>

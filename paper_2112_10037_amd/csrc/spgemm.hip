@@ -28,12 +28,12 @@ static int next_pow2(int x) {
 // ---------------------------------------------------------------------------
 // bin plans
 // ---------------------------------------------------------------------------
-// Bounds up to block_rows go to the merge kernel (<= 32), wave-local row
-// batches and lane groups (16, 32, 64, 128 with 8, 16, 32, 64 lanes, scaled
-// by group_scale), and whole waves per row with LDS tables of up to 2048
-// keys (symbolic) or 512 (key, value) slots (numeric); workgroup kernels
-// cover the middle; the last bin is the global path.  Hash tables get
-// nextpow2(bound) << hash_scale slots, so they are at most half full.
+// Bounds up to block_rows go to the merge kernel (<= 32; without it wave-local
+// row batches and lane groups, the lanes scaled by group_scale) and to whole
+// waves per row with LDS tables of up to 2048 keys (symbolic) or 1024 (key,
+// value) slots (numeric); workgroup kernels cover the middle; the last bin is
+// the global path.  Hash tables get nextpow2(bound) << hash_scale slots, so
+// they are at most half full.
 
 static void add_bin(BinPlan& p, int umax, BinSpec s) {
     const int b = p.table.nb;          // bins are appended after bin 0
@@ -42,14 +42,17 @@ static void add_bin(BinPlan& p, int umax, BinSpec s) {
     p.table.nb = b + 1;
 }
 
-// Small bins (bound <= 128).  Symbolic: wave-local row batches (k_sym_wave) of
-// at most R rows with T key slots.  Numeric: wave batches while T <= 64, lane groups of
-// G lanes per row (k_num_group) for larger tables.
+// Small bins.  From 33 outputs a row takes a whole wave: one step of 64 lanes
+// holds a row of 64 products.  (In batches of eight rows a wave, 4096 rows of
+// 64 products took 16.3 us in the symbolic pass and 13.7 us in the numeric one
+// as lane groups of 32; a wave each 4.6 and 10.3 us.)  Shorter rows, when the
+// merge is off: wave-local row batches (k_sym_wave, k_num_wave) of at most R
+// rows with T key slots, lane groups (k_num_group) for larger tables.
 static int sym_batch_rows(int T) { return T <= 64 ? 16 : 1024 / T; }
 
 static void add_small_bins(BinPlan& p, const msp_tuning& t, int limit, bool numeric) {
     static const int umax[7] = {16, 32, 64, 128, 256, 512, 1024};
-    static const int g0[7] = {8, 16, 32, 64, 64, 64, 64};
+    static const int g0[7] = {8, 16, 64, 64, 64, 64, 64};
     int covered = 0;
     // the merge takes row_nnz steps of K comparisons each: worth it for the
     // shortest rows only
@@ -62,7 +65,7 @@ static void add_small_bins(BinPlan& p, const msp_tuning& t, int limit, bool nume
         if (umax[i] <= covered) continue;
         const int T = next_pow2(umax[i]) << t.hash_scale;
         if (!numeric) {
-            if (T <= 256) add_bin(p, umax[i], BinSpec{Kind::Batch, sym_batch_rows(T), T});
+            if (umax[i] < 64) add_bin(p, umax[i], BinSpec{Kind::Batch, sym_batch_rows(T), T});
             else if (T <= 2048) add_bin(p, umax[i], BinSpec{Kind::Group, 64, T});
             else break;
         } else if (T <= 64) {
@@ -140,12 +143,10 @@ static int win_lds(const msp_handle* h) {
     return dyn >= kWinFixed + kWinOut * kWin + kWinSlack ? dyn : 0;
 }
 
-#define MSP_GROUP_SHAPES(X) \
-    X(8, 32) X(16, 32) X(8, 64) X(16, 64) X(32, 64) X(16, 128) X(32, 128) \
-    X(32, 256)
+#define MSP_NUM_GROUP_SHAPES(X) X(16, 128) X(32, 128)
 #define MSP_NUM_ROW_SHAPES(X) X(128) X(256) X(512) X(1024)
 #define MSP_SYM_ROW_SHAPES(X) MSP_NUM_ROW_SHAPES(X) X(2048)
-#define MSP_SYM_BATCH_SHAPES(X) X(32, 16) X(64, 16) X(128, 8) X(256, 4) X(512, 2)
+#define MSP_SYM_BATCH_SHAPES(X) X(32, 16) X(64, 16) X(128, 8)
 #define MSP_NUM_BATCH_SHAPES(X) X(32, 12) X(32, 8) X(32, 4) X(64, 8) X(64, 4) X(64, 2)
 #define MSP_SYM_BLOCK_SHAPES(X) \
     X(256, 1024) X(256, 2048) X(512, 4096) X(512, 8192) X(1024, 16384) X(1024, 32768)
@@ -161,8 +162,8 @@ static bool spec_supported(const BinSpec& sp, bool numeric) {
 #undef X
             return false;
         case Kind::Group:
-#define X(G, T) if (sp.lanes == G && sp.slots == T) return true;
-            MSP_GROUP_SHAPES(X)
+#define X(G, T) if (numeric && sp.lanes == G && sp.slots == T) return true;
+            MSP_NUM_GROUP_SHAPES(X)
 #undef X
 #define X(T) if (sp.lanes == 64 && sp.slots == T) return true;
             if (numeric) { MSP_NUM_ROW_SHAPES(X) } else { MSP_SYM_ROW_SHAPES(X) }
@@ -315,15 +316,6 @@ static msp_status launch_symbolic_t(msp_handle* h, const BinSpec& s, Work wk, in
         MSP_SYM_BATCH_SHAPES(X)
 #undef X
     } else if (s.kind == Kind::Group) {
-#define X(G, T)                                                                                       \
-    if (s.lanes == G && s.slots == T) {                                                               \
-        const int grid = group_grid(h, (const void*)k_sym_group<G, T, BATCH>, rows, 256 / G);        \
-        k_sym_group<G, T, BATCH><<<grid, 256, 0, st>>>(wk, (int)op.m, op.arp, op.acol, op.brp, op.bcol, rnnz, \
-                                                       info, mp);                                     \
-        return launch_check("k_sym_group");                                                           \
-    }
-        MSP_GROUP_SHAPES(X)
-#undef X
         // one wave per row
 #define X(T)                                                                                          \
     if (s.lanes == 64 && s.slots == T) {                                                              \
@@ -452,7 +444,7 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
                                                            ccol, cval, cnt_out, info, mp);                \
         return launch_check("k_num_group");                                                                \
     }
-        MSP_GROUP_SHAPES(X)
+        MSP_NUM_GROUP_SHAPES(X)
 #undef X
         // one wave per row
 #define X(T)                                                                                               \
