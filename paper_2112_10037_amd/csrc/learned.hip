@@ -138,171 +138,227 @@ k_capacity(int m, const float* __restrict__ feats, const int32_t* __restrict__ h
 }
 
 // ---------------------------------------------------------------------------
-// training: forward + per-sample backward, gradient reduction, Adam
+// training: forward, backward and gradient of a batch tile on the matrix
+// cores, then the tiles' sums and Adam
 // ---------------------------------------------------------------------------
-// Per sample s of the batch: activations and the backward deltas of the
-// mean-squared error, stored for the reduction kernel.
-__global__ void __launch_bounds__(256)
-k_mlp_fwd_bwd(int batch, long long n, const int32_t* __restrict__ idx, const float* __restrict__ feats,
-              const float* __restrict__ targets, const float* __restrict__ params,
-              float* __restrict__ X, float* __restrict__ H1, float* __restrict__ H2,
-              float* __restrict__ DZ1, float* __restrict__ DZ2, float* __restrict__ D, int* __restrict__ bad) {
-    __shared__ __align__(16) float w[kNParam + 3];
-    for (int i = threadIdx.x; i < kNParam; i += 256) w[i] = params[i];
-    __syncthreads();
-    const int s = blockIdx.x * 256 + threadIdx.x;
-    if (s >= batch) return;
-    long long r = idx[s];
-    if (r < 0 || r >= n) {          // flagged; the sample reads row 0 instead
-        atomicOr(bad, 1);
-        r = 0;
-    }
-    float x[kNF];
-#pragma unroll
-    for (int f = 0; f < kNF; ++f) { x[f] = feats[r * kNF + f]; X[(long long)s * kNF + f] = x[f]; }
-    // forward; activity masks of both hidden layers
-    uint64_t act1 = 0, act2 = 0;
-    float y = w[kOffB3];
-    {
-        float h1[kH1];
-#pragma unroll
-        for (int i = 0; i < kH1; ++i) {
-            float z = w[kOffB1 + i];
-#pragma unroll
-            for (int f = 0; f < kNF; ++f) z += w[kOffW1 + i * kNF + f] * x[f];
-            h1[i] = z > 0.f ? z : 0.f;
-            act1 |= (uint64_t)(z > 0.f) << i;
-            H1[(long long)s * kH1 + i] = h1[i];
-        }
-#pragma unroll 1
-        for (int j = 0; j < kH2; ++j) {
-            const float4* row = reinterpret_cast<const float4*>(w + kOffW2 + j * kH1);
-            float z = w[kOffB2 + j];
-#pragma unroll
-            for (int i4 = 0; i4 < kH1 / 4; ++i4) {
-                const float4 q = row[i4];
-                z += q.x * h1[4 * i4] + q.y * h1[4 * i4 + 1] + q.z * h1[4 * i4 + 2] + q.w * h1[4 * i4 + 3];
-            }
-            const float h2 = z > 0.f ? z : 0.f;
-            act2 |= (uint64_t)(z > 0.f) << j;
-            H2[(long long)s * kH2 + j] = h2;
-            y += w[kOffW3 + j] * h2;
-        }
-    }
-    const float d = y - targets[r];
-    D[s] = d;
-    const float dy = 2.f * d / (float)batch;
-    // backward: dz2_j = dy W3_j [z2_j > 0]; dz1_i = [z1_i > 0] sum_j W2[j][i] dz2_j
-    float dz1[kH1];
-#pragma unroll
-    for (int i = 0; i < kH1; ++i) dz1[i] = 0.f;
-#pragma unroll 1
-    for (int j = 0; j < kH2; ++j) {
-        const float dz2 = (act2 >> j) & 1 ? dy * w[kOffW3 + j] : 0.f;
-        DZ2[(long long)s * kH2 + j] = dz2;
-        const float4* row = reinterpret_cast<const float4*>(w + kOffW2 + j * kH1);
-#pragma unroll
-        for (int i4 = 0; i4 < kH1 / 4; ++i4) {
-            const float4 q = row[i4];
-            dz1[4 * i4] += q.x * dz2;
-            dz1[4 * i4 + 1] += q.y * dz2;
-            dz1[4 * i4 + 2] += q.z * dz2;
-            dz1[4 * i4 + 3] += q.w * dz2;
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < kH1; ++i) DZ1[(long long)s * kH1 + i] = (act1 >> i) & 1 ? dz1[i] : 0.f;
+// A workgroup of four waves takes tiles of 16 samples.  Wave w owns the hidden
+// units 16 w .. 16 w + 15 of both layers: its part of every product is a 16 x
+// 16 FP64 matrix-core tile (v_mfma_f64_16x16x4: lane l holds A[l % 16][l / 16]
+// and B[l / 16][l % 16]; register r of the result is row 4 r + l / 16, column
+// l % 16).  A product's terms may come in any order, so lane group g takes the
+// terms 16 g + k in step k: its weights are then consecutive in memory and
+// stay in registers over the tiles.  Activations and deltas pass between the
+// waves through LDS in FP64; the gradient's sums over the workgroup's samples
+// stay in the result registers and leave as one partial sum per workgroup, so
+// the gradient is deterministic.
+//
+// Bound by latency: a step of 4096 samples is 115 MFLOP, 1.6 us at the FP64
+// matrix rate, and takes 11.9 us here (256 workgroups of one tile: 11.6, but
+// 5.9 instead of 4.5 us for the sum of twice the partial sums).  Before (a
+// thread per sample, 16 workgroups, activations and deltas through memory, one
+// thread per parameter and tile): 51 + 25 + 37 us for forward and backward,
+// tile sums and their sum.  FP64 keeps every sum at least as close as the FP32
+// forward pass with FP64 gradient sums was.
+constexpr int kTile = 16;                      // samples per tile
+constexpr int kTileWG = 128;                   // most workgroups of a step
+constexpr int kPartRow = 4864;                 // doubles per workgroup's partial sums (whole 512-byte lines)
+constexpr int kTilePad = 66;                   // doubles per LDS row of 64 (rows start on different banks)
+static_assert(kPartRow >= kNParam, "a partial row holds every parameter");
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// Gradient, first level: workgroup t sums the batch tile [t TS, t TS + TS)
-// for every parameter, in FP64, in sample order, into partial[t][p]; the
-// tile's activations and deltas are staged in LDS first.  (The tiles
-// replace one long serial loop per parameter; the sums stay in a fixed
-// order, so the gradient is deterministic.)
-constexpr int kGradTS = 32;                    // samples per tile
 __global__ void __launch_bounds__(256)
-k_mlp_grad_tile(int batch, const float* __restrict__ X, const float* __restrict__ H1, const float* __restrict__ H2,
-                const float* __restrict__ DZ1, const float* __restrict__ DZ2, const float* __restrict__ D,
-                double* __restrict__ partial, double* __restrict__ partial_loss) {
-    __shared__ float sx[kGradTS][kNF], sh1[kGradTS][kH1], sh2[kGradTS][kH2], sd1[kGradTS][kH1 + 1],
-        sd2[kGradTS][kH2 + 1], sd[kGradTS];
-    const int t = blockIdx.x, tid = threadIdx.x;
-    const int s0 = t * kGradTS;
-    const int ns = batch - s0 < kGradTS ? batch - s0 : kGradTS;
-    for (int e = tid; e < kGradTS * kH1; e += 256) {
-        const int a = e / kH1, b = e % kH1;
-        const bool in = a < ns;
-        const long long g = (long long)(s0 + a);
-        sh1[a][b] = in ? H1[g * kH1 + b] : 0.f;
-        sh2[a][b] = in ? H2[g * kH2 + b] : 0.f;
-        sd1[a][b] = in ? DZ1[g * kH1 + b] : 0.f;
-        sd2[a][b] = in ? DZ2[g * kH2 + b] : 0.f;
-        if (b < kNF) sx[a][b] = in ? X[g * kNF + b] : 0.f;
-        if (b == 0) sd[a] = in ? D[g] : 0.f;
-    }
-    __syncthreads();
+k_mlp_tiles(int batch, long long n, const int32_t* __restrict__ idx, const float* __restrict__ feats,
+            const float* __restrict__ targets, const float* __restrict__ params, double* __restrict__ partial,
+            double* __restrict__ partial_loss, int* __restrict__ bad) {
+    __shared__ __align__(16) double h1[kTile][kTilePad], dz2[kTile][kTilePad], dz1[kTile][kTilePad];
+    __shared__ double ypart[4][kTile];
+    __shared__ float sx[kTile][kNF], st[kTile];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int u = 16 * w + c;                   // this lane's hidden unit
+    // a tile's samples: lane group g takes the features 2 g and 2 g + 1 of sample c
+    float x[2], target;
+    auto samples = [&](int s0) {
+        x[0] = x[1] = target = 0.f;
+        if (s0 + c >= batch) return;
+        long long r = idx[s0 + c];
+        if (r < 0 || r >= n) {                  // flagged; the sample reads row 0 instead
+            atomicOr(bad, 1);
+            r = 0;
+        }
+        x[0] = feats[r * kNF + 2 * g];
+        x[1] = feats[r * kNF + 2 * g + 1];
+        target = targets[r];
+    };
+    samples(blockIdx.x * kTile);
+    // the wave's weights: rows of W1 and W2 for the forward pass, columns of W2 for the backward one
+    double w1[2], w2f[16], w2b[16];
+    for (int k = 0; k < 2; ++k) w1[k] = params[kOffW1 + u * kNF + 2 * g + k];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) w2f[k] = params[kOffW2 + u * kH1 + 16 * g + k];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) w2b[k] = params[kOffW2 + (16 * g + k) * kH1 + u];
+    const double b1 = params[kOffB1 + u], b2 = params[kOffB2 + u], w3 = params[kOffW3 + u], b3 = params[kOffB3];
     const double scale = 2.0 / (double)batch;
-    for (int p = tid; p < kNParam; p += 256) {
-        double acc = 0.0;
-        if (p < kOffB1) {
-            const int i = p / kNF, f = p % kNF;
-            for (int a = 0; a < ns; ++a) acc += (double)sd1[a][i] * sx[a][f];
-        } else if (p < kOffW2) {
-            const int i = p - kOffB1;
-            for (int a = 0; a < ns; ++a) acc += sd1[a][i];
-        } else if (p < kOffB2) {
-            const int q = p - kOffW2, j = q / kH1, i = q % kH1;
-            for (int a = 0; a < ns; ++a) acc += (double)sd2[a][j] * sh1[a][i];
-        } else if (p < kOffW3) {
-            const int j = p - kOffB2;
-            for (int a = 0; a < ns; ++a) acc += sd2[a][j];
-        } else if (p < kOffB3) {
-            const int j = p - kOffW3;
-            for (int a = 0; a < ns; ++a) acc += scale * sd[a] * sh2[a][j];
-        } else {
-            double l = 0.0;
-            for (int a = 0; a < ns; ++a) {
-                acc += scale * sd[a];
-                l += (double)sd[a] * sd[a];
-            }
-            partial_loss[t] = l;
+    f64x4 gw2[4] = {}, gw1 = {};
+    double gb1 = 0.0, gb2 = 0.0, gw3 = 0.0, gb3 = 0.0, loss = 0.0;
+    for (int s0 = blockIdx.x * kTile; s0 < batch; s0 += gridDim.x * kTile) {
+        // layer 1, then the next tile's samples
+        if (w == 0) {
+            sx[c][2 * g] = x[0];
+            sx[c][2 * g + 1] = x[1];
+            if (g == 0) st[c] = target;
         }
-        partial[(long long)t * kNParam + p] = acc;
+        f64x4 z = {b1, b1, b1, b1};
+        z = mfma_f64(x[0], w1[0], z);
+        z = mfma_f64(x[1], w1[1], z);
+        samples(s0 + gridDim.x * kTile);
+        bool on1[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            on1[r] = z[r] > 0.0;
+            h1[4 * r + g][u] = on1[r] ? z[r] : 0.0;
+        }
+        __syncthreads();
+        // layer 2 and the output
+        z = f64x4{b2, b2, b2, b2};
+#pragma unroll
+        for (int k = 0; k < 16; ++k) z = mfma_f64(h1[c][16 * g + k], w2f[k], z);
+        double h2[4], y[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            h2[r] = z[r] > 0.0 ? z[r] : 0.0;
+            y[r] = h2[r] * w3;
+        }
+        {
+            // over the 16 units: lanes that differ in bits 3 and 2 share out the
+            // four samples (lane c ends with sample register c / 4), then the rest
+            const bool up = c & 8;
+            double p = up ? y[2] : y[0], q = up ? y[3] : y[1];
+            p += __shfl_xor(up ? y[0] : y[2], 8);
+            q += __shfl_xor(up ? y[1] : y[3], 8);
+            const bool odd = c & 4;
+            const double o = __shfl_xor(odd ? p : q, 4);
+            double v = (odd ? q : p) + o;
+            v += __shfl_xor(v, 2);
+            v += __shfl_xor(v, 1);
+            if ((c & 3) == 0) ypart[w][4 * (c >> 2) + g] = v;
+        }
+        __syncthreads();
+        // the samples' errors and the second layer's deltas
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int s = 4 * r + g;
+            double d = 0.0;
+            if (s0 + s < batch) d = b3 + ypart[0][s] + ypart[1][s] + ypart[2][s] + ypart[3][s] - (double)st[s];
+            const double dy = scale * d;
+            const double dz = z[r] > 0.0 ? dy * w3 : 0.0;
+            dz2[s][u] = dz;
+            gb2 += dz;
+            gw3 += dy * h2[r];
+            gb3 += dy;
+            loss += d * d;
+        }
+        __syncthreads();
+        // the first layer's deltas, and W2's gradient: rows of this wave, all columns
+        z = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < 16; ++k) z = mfma_f64(dz2[c][16 * g + k], w2b[k], z);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const double dz = on1[r] ? z[r] : 0.0;
+            dz1[4 * r + g][u] = dz;
+            gb1 += dz;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double a = dz2[4 * g + k][u];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) gw2[t] = mfma_f64(a, h1[4 * g + k][16 * t + c], gw2[t]);
+        }
+        __syncthreads();
+        // W1's gradient (columns past the features are not kept)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) gw1 = mfma_f64(dz1[4 * g + k][u], c < kNF ? (double)sx[4 * g + k][c] : 0.0, gw1);
+        __syncthreads();
+    }
+    double* const out = partial + (long long)blockIdx.x * kPartRow;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = 16 * w + 4 * r + g;
+        if (c < kNF) out[kOffW1 + row * kNF + c] = gw1[r];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) out[kOffW2 + row * kH1 + 16 * t + c] = gw2[t][r];
+    }
+#pragma unroll
+    for (int d = 16; d < 64; d <<= 1) {         // over the lane groups
+        gb1 += __shfl_xor(gb1, d);
+        gb2 += __shfl_xor(gb2, d);
+        gw3 += __shfl_xor(gw3, d);
+        gb3 += __shfl_xor(gb3, d);
+        loss += __shfl_xor(loss, d);
+    }
+    if (g == 0) {
+        out[kOffB1 + u] = gb1;
+        out[kOffB2 + u] = gb2;
+        out[kOffW3 + u] = gw3;
+        if (u == 0) {
+            out[kOffB3] = gb3;
+            partial_loss[blockIdx.x] = loss;
+        }
     }
 }
 
-// Gradient, second level: the tiles' partial sums in tile order.
-__global__ void __launch_bounds__(256)
-k_mlp_grad_sum(int tiles, int batch, const double* __restrict__ partial, const double* __restrict__ partial_loss,
-               float* __restrict__ grad, float* __restrict__ loss) {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p < kNParam) {
-        double acc = 0.0;
-        for (int t = 0; t < tiles; ++t) acc += partial[(long long)t * kNParam + p];
-        grad[p] = (float)acc;
+// The workgroups' partial sums in a fixed order, and with ADAM the update
+// (Kingma and Ba, 2015, bias-corrected moments; step is 1-based).  A
+// workgroup takes 32 parameters, eight threads each; the last one the loss.
+constexpr int kSumP = 32, kSumT = 8;
+template <bool ADAM>
+__global__ void __launch_bounds__(kSumP * kSumT)
+k_mlp_sum(int parts, int batch, const double* __restrict__ partial, const double* __restrict__ partial_loss,
+          float* __restrict__ grad, float* __restrict__ loss, float* __restrict__ params, float* __restrict__ m,
+          float* __restrict__ v, int step, float lr, float beta1, float beta2, float eps) {
+    __shared__ double acc[kSumT][kSumP];
+    const int pl = threadIdx.x % kSumP, t = threadIdx.x / kSumP;
+    const bool is_loss = blockIdx.x == gridDim.x - 1;
+    const int p = blockIdx.x * kSumP + pl;
+    double s = 0.0;
+    if (is_loss) {
+        for (int i = threadIdx.x; i < parts; i += kSumP * kSumT) s += partial_loss[i];
+    } else if (p < kNParam) {
+#pragma unroll 4
+        for (int i = t; i < parts; i += kSumT) s += partial[(long long)i * kPartRow + p];
     }
-    if (p == 0 && loss) {
-        double l = 0.0;
-        for (int t = 0; t < tiles; ++t) l += partial_loss[t];
-        *loss = (float)(l / batch);
+    acc[t][pl] = s;
+    __syncthreads();
+    if (t != 0) return;
+    s = 0.0;
+#pragma unroll
+    for (int i = 0; i < kSumT; ++i) s += acc[i][pl];
+    if (is_loss) {
+#pragma unroll
+        for (int d = kSumP / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, kSumP);
+        if (pl == 0 && loss) *loss = (float)(s / batch);
+        return;
     }
-}
-
-// Adam (Kingma and Ba, 2015) with bias-corrected moments; step is 1-based.
-__global__ void __launch_bounds__(256)
-k_adam(float* __restrict__ params, const float* __restrict__ grad, float* __restrict__ m, float* __restrict__ v,
-       int step, float lr, float beta1, float beta2, float eps) {
-    const int p = blockIdx.x * 256 + threadIdx.x;
     if (p >= kNParam) return;
-    const float g = grad[p];
-    const float mm = beta1 * m[p] + (1.f - beta1) * g;
-    const float vv = beta2 * v[p] + (1.f - beta2) * g * g;
-    m[p] = mm;
-    v[p] = vv;
-    const float mhat = mm / (1.f - powf(beta1, (float)step));
-    const float vhat = vv / (1.f - powf(beta2, (float)step));
-    params[p] -= lr * mhat / (sqrtf(vhat) + eps);
+    const float g = (float)s;
+    grad[p] = g;
+    if constexpr (ADAM) {
+        const float mm = beta1 * m[p] + (1.f - beta1) * g;
+        const float vv = beta2 * v[p] + (1.f - beta2) * g * g;
+        m[p] = mm;
+        v[p] = vv;
+        const float mhat = mm / (1.f - powf(beta1, (float)step));
+        const float vhat = vv / (1.f - powf(beta2, (float)step));
+        params[p] -= lr * mhat / (sqrtf(vhat) + eps);
+    }
 }
+constexpr int kSumGrid = (kNParam + kSumP - 1) / kSumP + 1;
 
 // training target of a row: log2(1 + row_nnz) / 16
 __global__ void __launch_bounds__(256)
@@ -481,8 +537,7 @@ static msp_status launch_check2(const char* what) {
 
 struct msp_predictor {
     int device = 0;
-    msp::DevBuf params, m, v, grad, loss, bad, X, H1, H2, DZ1, DZ2, D, part, part_loss;
-    int batch_cap = 0;
+    msp::DevBuf params, m, v, grad, loss, bad, part, part_loss;
     float delta = 0.f;
     long long step = 0;
 };
@@ -517,8 +572,7 @@ extern "C" msp_status msp_predictor_destroy(msp_predictor* p) {
     if (!p) return MSP_OK;
     (void)hipSetDevice(p->device);
     for (DevBuf* b :
-         {&p->params, &p->m, &p->v, &p->grad, &p->loss, &p->bad, &p->X, &p->H1, &p->H2, &p->DZ1, &p->DZ2, &p->D,
-          &p->part, &p->part_loss})
+         {&p->params, &p->m, &p->v, &p->grad, &p->loss, &p->bad, &p->part, &p->part_loss})
         b->release();
     delete p;
     return MSP_OK;
@@ -657,39 +711,28 @@ extern "C" msp_status msp_predictor_load(msp_handle* h, msp_predictor* p, const 
     return MSP_OK;
 }
 
-static msp_status ensure_batch(msp_predictor* p, int batch) {
-    if (batch <= p->batch_cap) return MSP_OK;
-    msp_status s;
-    const size_t b = (size_t)batch;
-    if ((s = p->X.ensure(b * kNF * 4)) != MSP_OK || (s = p->H1.ensure(b * kH1 * 4)) != MSP_OK ||
-        (s = p->H2.ensure(b * kH2 * 4)) != MSP_OK || (s = p->DZ1.ensure(b * kH1 * 4)) != MSP_OK ||
-        (s = p->DZ2.ensure(b * kH2 * 4)) != MSP_OK || (s = p->D.ensure(b * 4)) != MSP_OK)
-        return s;
-    const size_t tiles = (b + kGradTS - 1) / kGradTS;
-    if ((s = p->part.ensure(tiles * kNParam * 8)) != MSP_OK || (s = p->part_loss.ensure(tiles * 8)) != MSP_OK)
-        return s;
-    p->batch_cap = batch;
-    return MSP_OK;
-}
-
-// one forward/backward + gradient reduction on batch rows idx[0..batch)
+// One forward and backward pass on batch rows idx[0..batch) and the gradient;
+// with `adam`, also the parameters' update (p->step counts this step).
 static msp_status grad_step(msp_handle* h, msp_predictor* p, const float* feats, const float* targets, int64_t n,
-                            const int32_t* idx, int batch, float* loss_dev) {
-    msp_status s = ensure_batch(p, batch);
-    if (s != MSP_OK) return s;
-    k_mlp_fwd_bwd<<<(batch + 255) / 256, 256, 0, h->stream>>>(
-        batch, n, idx, feats, targets, p->params.as<float>(), p->X.as<float>(), p->H1.as<float>(), p->H2.as<float>(),
-        p->DZ1.as<float>(), p->DZ2.as<float>(), p->D.as<float>(), p->bad.as<int>());
-    if ((s = launch_check2("k_mlp_fwd_bwd")) != MSP_OK) return s;
-    const int tiles = (batch + kGradTS - 1) / kGradTS;
-    k_mlp_grad_tile<<<tiles, 256, 0, h->stream>>>(batch, p->X.as<float>(), p->H1.as<float>(), p->H2.as<float>(),
-                                                  p->DZ1.as<float>(), p->DZ2.as<float>(), p->D.as<float>(),
-                                                  p->part.as<double>(), p->part_loss.as<double>());
-    if ((s = launch_check2("k_mlp_grad_tile")) != MSP_OK) return s;
-    k_mlp_grad_sum<<<(kNParam + 255) / 256, 256, 0, h->stream>>>(tiles, batch, p->part.as<double>(),
-                                                                  p->part_loss.as<double>(), p->grad.as<float>(),
-                                                                  loss_dev);
-    return launch_check2("k_mlp_grad_sum");
+                            const int32_t* idx, int batch, float* loss_dev, const msp_train_opts* adam) {
+    const int parts = std::min((batch + kTile - 1) / kTile, kTileWG);
+    msp_status s;
+    if ((s = p->part.ensure((size_t)parts * kPartRow * 8)) != MSP_OK ||
+        (s = p->part_loss.ensure((size_t)parts * 8)) != MSP_OK)
+        return s;
+    k_mlp_tiles<<<parts, 256, 0, h->stream>>>(batch, n, idx, feats, targets, p->params.as<float>(),
+                                              p->part.as<double>(), p->part_loss.as<double>(), p->bad.as<int>());
+    if ((s = launch_check2("k_mlp_tiles")) != MSP_OK) return s;
+    if (adam)
+        k_mlp_sum<true><<<kSumGrid, kSumP * kSumT, 0, h->stream>>>(
+            parts, batch, p->part.as<double>(), p->part_loss.as<double>(), p->grad.as<float>(), loss_dev,
+            p->params.as<float>(), p->m.as<float>(), p->v.as<float>(), (int)p->step, adam->lr, adam->beta1,
+            adam->beta2, adam->eps);
+    else
+        k_mlp_sum<false><<<kSumGrid, kSumP * kSumT, 0, h->stream>>>(
+            parts, batch, p->part.as<double>(), p->part_loss.as<double>(), p->grad.as<float>(), loss_dev, nullptr,
+            nullptr, nullptr, 0, 0.f, 0.f, 0.f, 0.f);
+    return launch_check2("k_mlp_sum");
 }
 
 // Sample indices outside [0, n) were flagged by the forward/backward kernel:
@@ -712,7 +755,7 @@ extern "C" msp_status msp_predictor_grad(msp_handle* h, msp_predictor* p, const 
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     msp_status s = p->loss.ensure(sizeof(float));
     if (s != MSP_OK) return s;
-    if ((s = grad_step(h, p, feats, targets, n, idx, batch, p->loss.as<float>())) != MSP_OK) return s;
+    if ((s = grad_step(h, p, feats, targets, n, idx, batch, p->loss.as<float>(), nullptr)) != MSP_OK) return s;
     if (grad_host &&
         (e = hipMemcpyAsync(grad_host, p->grad.ptr, kNParam * 4, hipMemcpyDeviceToHost, h->stream)) != hipSuccess)
         return hip_fail(e, "hipMemcpyAsync(grad)");
@@ -729,21 +772,20 @@ extern "C" msp_status msp_predictor_train(msp_handle* h, msp_predictor* p, const
         return fail(MSP_ERR_INVALID_ARG, "bad argument");
     hipError_t e = hipSetDevice(h->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
-    const float lr = o && o->lr > 0 ? o->lr : 1e-3f;
-    const float b1 = o && o->beta1 > 0 ? o->beta1 : 0.9f;
-    const float b2 = o && o->beta2 > 0 ? o->beta2 : 0.999f;
-    const float eps = o && o->eps > 0 ? o->eps : 1e-8f;
+    msp_train_opts a;
+    a.lr = o && o->lr > 0 ? o->lr : 1e-3f;
+    a.beta1 = o && o->beta1 > 0 ? o->beta1 : 0.9f;
+    a.beta2 = o && o->beta2 > 0 ? o->beta2 : 0.999f;
+    a.eps = o && o->eps > 0 ? o->eps : 1e-8f;
     msp_status s = p->loss.ensure((size_t)std::max(steps, 1) * sizeof(float));
     if (s != MSP_OK) return s;
     for (int t = 0; t < steps; ++t) {
-        if ((s = grad_step(h, p, feats, targets, n, batch_idx + (size_t)t * batch, batch, p->loss.as<float>() + t)) !=
-            MSP_OK)
-            return s;
         ++p->step;
-        k_adam<<<(kNParam + 255) / 256, 256, 0, h->stream>>>(p->params.as<float>(), p->grad.as<float>(),
-                                                             p->m.as<float>(), p->v.as<float>(), (int)p->step, lr, b1,
-                                                             b2, eps);
-        if ((s = launch_check2("k_adam")) != MSP_OK) return s;
+        if ((s = grad_step(h, p, feats, targets, n, batch_idx + (size_t)t * batch, batch, p->loss.as<float>() + t,
+                           &a)) != MSP_OK) {
+            --p->step;
+            return s;
+        }
     }
     if (losses_host && steps > 0 &&
         (e = hipMemcpyAsync(losses_host, p->loss.ptr, (size_t)steps * 4, hipMemcpyDeviceToHost, h->stream)) !=
