@@ -160,7 +160,8 @@ void release_extra(msp_handle* h);
 int count_unsupported_plans(int verbose);
 void sum_parts(const int (*part)[kPartStride], int out[kNB]);
 BinPlan symbolic_plan(const msp_tuning& t, bool force_spill);
-BinPlan numeric_plan(const msp_tuning& t, bool force_spill);
+// (rule: the bins as the learned product's capacity rule sees them)
+BinPlan numeric_plan(const msp_tuning& t, bool force_spill, bool rule = false);
 
 // The plain pipeline pieces, reused by the learned and batched forms.
 msp_status read_info(msp_handle* h);
@@ -202,5 +203,10 @@ msp_status launch_symbolic_bin(msp_handle* h, const BinSpec& s, Work wk, int row
 template <bool BATCH>
 msp_status launch_numeric_bin(msp_handle* h, const BinSpec& s, Work wk, int rows, const Operands& op,
                               const int64_t* crp, int32_t* ccol, void* cval, int32_t* cnt_out, const RowMap& mp);
+// After a numeric phase's bins: the rows its Block bins (of `rows` rows) left
+// to the hash kernel.
+template <bool BATCH>
+msp_status launch_sort_rest(msp_handle* h, int rows, const Operands& op, const int64_t* crp, int32_t* ccol, void* cval,
+                            int32_t* cnt_out, const RowMap& mp);
 
 }  // namespace msp

@@ -841,7 +841,10 @@ k_sym_bitmap(Work wk, long long ncols,
             s_bst[tid] = bst - (incl - len);
             __syncthreads();
             const int nact = (int)((a1 - c0) < BS ? (a1 - c0) : BS);
-            int t = -1;                     // owner of q: one search, then it only moves forward
+            // owner of q: one search, then it moves forward, unless the next
+            // product lies more than eight average entries on
+            const bool far = total < (long long)nact * (BS / 8);
+            int t = -1;
             // SU products per thread and round, their loads issued before any
             // is used: one workgroup per compute unit leaves few waves to hide
             // the gathers
@@ -853,8 +856,8 @@ k_sym_bitmap(Work wk, long long ncols,
                     const long long q = q0 + (long long)u * BS;
                     j[u] = -1;
                     if (q < total) {
-                        if (t < 0) t = owner_search(s_off, nact, q);
-                else while ((long long)s_off[t] <= q) ++t;
+                        if (t < 0 || far) t = owner_search(s_off, nact, q);
+                        else while ((long long)s_off[t] <= q) ++t;
                         j[u] = bcol[s_bst[t] + q];
                     }
                 }
@@ -2501,10 +2504,11 @@ k_num_block(Work wk,
             s_a[tid] = a;
             __syncthreads();
             const int nact = (int)((a1 - c0) < BS ? (a1 - c0) : BS);
-            int t = -1;                     // owner of q: one search, then it only moves forward
             for (long long q = tid; q < total; q += BS) {
-                if (t < 0) t = owner_search(s_off, nact, q);
-                else while ((long long)s_off[t] <= q) ++t;
+                // (searched for each product: past a thousand products lie many
+                // entries, and rows of short B rows are among those left to
+                // this kernel; a walk took 76 us for a row of 1030 entries)
+                const int t = owner_search(s_off, nact, q);
                 const long long bi = s_bst[t] + q;
                 const int32_t j = bcol[bi];
                 const double prod = s_a[t] * to_f64(bval[bi]);
@@ -3496,3 +3500,4 @@ k_validate(long long nrows, long long ncols, long long nnz, const int64_t* __res
 }  // namespace msp
 
 #include "wave_rows.hpp"
+#include "block_rows.hpp"

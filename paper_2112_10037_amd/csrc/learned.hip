@@ -887,7 +887,8 @@ extern "C" msp_status msp_spgemm_learned(msp_handle* h, const msp_predictor* p, 
         const int big = (opts && opts->force_spill) || np.table.nb <= 1 ? -1 : np.table.umax[np.table.nb - 1];
         k_capacity<<<blocks, 256, 0, h->stream>>>(m, x->feat.as<float>(), h->u.as<int32_t>(), x->lo.as<int32_t>(),
                                                   p->params.as<float>(), p->delta, x->cap.as<int32_t>(),
-                                                  x->cnt.as<int32_t>(), np.table, big,
+                                                  x->cnt.as<int32_t>(),
+                                                  numeric_plan(t, opts && opts->force_spill, true).table, big,
                                                   &h->info.as<DevInfo>()->learned_big,
                                                   &h->info.as<DevInfo>()->learned_big_hi);
         if ((s = launch_check2("k_capacity")) != MSP_OK) return cleanup(s);

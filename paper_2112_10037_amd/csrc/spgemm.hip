@@ -102,23 +102,20 @@ BinPlan symbolic_plan(const msp_tuning& t, bool force_spill) {
     return p;
 }
 
-BinPlan numeric_plan(const msp_tuning& t, bool force_spill) {
+BinPlan numeric_plan(const msp_tuning& t, bool force_spill, bool rule) {
     BinPlan p;
     memset(&p.table, 0, sizeof(p.table));
     p.table.nb = 1;
     if (!force_spill) {
         add_small_bins(p, t, std::min(t.block_rows, t.spill_nnz), true);
         int last = p.table.umax[p.table.nb - 1];
-        int list[4] = {512, 2048, 4096, t.spill_nnz};
-        std::sort(list, list + 4);
-        for (int i = 0; i < 4; ++i) {
-            const int u0 = list[i];
-            if (u0 > t.spill_nnz || u0 <= last) continue;
-            const int bs = u0 <= 512 ? 256 : (u0 <= 2048 ? 512 : 1024);
-            const int T = std::min(8192, next_pow2(u0) << t.hash_scale);
-            const int u = std::min(u0, T / 2);
-            if (u <= last) continue;
-            add_bin(p, u, BinSpec{Kind::Block, bs, T});
+        // (split at 1024 for the kernels alone: the capacity rule of the
+        // learned product works with 513..2048 as one bin)
+        int list[5] = {512, 1024, 2048, 4096, t.spill_nnz};
+        std::sort(list, list + 5);
+        for (int u : list) {
+            if (u > t.spill_nnz || u <= last || (u == 1024 && rule && t.spill_nnz > 1024)) continue;
+            add_bin(p, u, BinSpec{Kind::Block, u <= 1024 ? 128 : (u <= 2048 ? 256 : 512), kSortR});
             last = u;
         }
     }
@@ -150,8 +147,9 @@ static int win_lds(const msp_handle* h) {
 #define MSP_NUM_BATCH_SHAPES(X) X(32, 12) X(32, 8) X(32, 4) X(64, 8) X(64, 4) X(64, 2)
 #define MSP_SYM_BLOCK_SHAPES(X) \
     X(256, 1024) X(256, 2048) X(512, 4096) X(512, 8192) X(1024, 16384) X(1024, 32768)
-#define MSP_NUM_BLOCK_SHAPES(X) \
-    X(256, 512) X(256, 1024) X(256, 2048) X(512, 2048) X(512, 4096) X(512, 8192) X(1024, 8192)
+// workgroup threads of the numeric counting sort; every size takes kSortR
+// products a thread
+#define MSP_NUM_SORT_SHAPES(X) X(128) X(256) X(512)
 
 static bool spec_supported(const BinSpec& sp, bool numeric) {
     switch (sp.kind) {
@@ -170,8 +168,11 @@ static bool spec_supported(const BinSpec& sp, bool numeric) {
 #undef X
             return false;
         case Kind::Block:
-#define X(BS, T) if (sp.lanes == BS && sp.slots == T) return true;
-            if (numeric) { MSP_NUM_BLOCK_SHAPES(X) } else { MSP_SYM_BLOCK_SHAPES(X) }
+#define X(BS, T) if (!numeric && sp.lanes == BS && sp.slots == T) return true;
+            MSP_SYM_BLOCK_SHAPES(X)
+#undef X
+#define X(BS) if (numeric && sp.lanes == BS && sp.slots == kSortR) return true;
+            MSP_NUM_SORT_SHAPES(X)
 #undef X
             return false;
         case Kind::Bitmap: return !numeric;
@@ -457,14 +458,17 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
         MSP_NUM_ROW_SHAPES(X)
 #undef X
     } else if (s.kind == Kind::Block) {
-        const int grid = std::min(rows, 4 * h->num_cu);
-#define X(BS, T)                                                                                             \
-    if (s.lanes == BS && s.slots == T) {                                                                     \
-        k_num_block<BS, T, VT, BATCH><<<grid, BS, 0, st>>>(wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp,   \
-                                                           ccol, cval, cnt_out, info, mp, rq);              \
-        return launch_check("k_num_block");                                                                  \
+        // rows the sort does not take are listed in the bounds array, which the
+        // numeric pass has no other use for; launch_sort_rest takes them
+#define X(BS)                                                                                              \
+    if (s.lanes == BS) {                                                                                   \
+        const int grid = group_grid(h, (const void*)k_num_sort<BS, kSortR, VT, BATCH>, rows, 1, BS);      \
+        k_num_sort<BS, kSortR, VT, BATCH><<<grid, BS, 0, st>>>(                                            \
+            wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, ccol, cval, cnt_out, info, mp, rq,          \
+            h->u.as<int32_t>(), &info->sort_fb[0]);                                                        \
+        return launch_check("k_num_sort");                                                                 \
     }
-        MSP_NUM_BLOCK_SHAPES(X)
+        MSP_NUM_SORT_SHAPES(X)
 #undef X
     } else if (s.kind == Kind::Dense) {
         const long long n = op.ncols;
@@ -510,6 +514,28 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
     return fail(MSP_ERR_UNSUPPORTED, "no numeric kernel for bin shape (%d, %d)", s.lanes, s.slots);
 }
 
+// The rows that the workgroup sorts of a numeric phase left (at most `rows`),
+// through the LDS hash: once, after every bin of the phase.
+template <typename VT, bool BATCH>
+static msp_status launch_sort_rest_t(msp_handle* h, int rows, const Operands& op, const int64_t* crp, int32_t* ccol,
+                                     VT* cval, int32_t* cnt_out, const RowMap& mp) {
+    DevInfo* info = h->info.as<DevInfo>();
+    const Work wk{h->u.as<int32_t>(), 0, &info->sort_fb[0]};
+    k_num_block<1024, 8192, VT, BATCH><<<std::min(rows, h->num_cu), 1024, 0, h->stream>>>(
+        wk, op.arp, op.acol, (const VT*)op.aval, op.brp, op.bcol, (const VT*)op.bval, crp, ccol, cval, cnt_out, info,
+        mp, BATCH ? nullptr : &info->queue[1][kNB][0]);
+    return launch_check("k_num_block");
+}
+
+template <bool BATCH>
+msp_status launch_sort_rest(msp_handle* h, int rows, const Operands& op, const int64_t* crp, int32_t* ccol, void* cval,
+                            int32_t* cnt_out, const RowMap& mp) {
+    if (rows <= 0) return MSP_OK;
+    if (op.dtype == MSP_F64)
+        return launch_sort_rest_t<double, BATCH>(h, rows, op, crp, ccol, (double*)cval, cnt_out, mp);
+    return launch_sort_rest_t<float, BATCH>(h, rows, op, crp, ccol, (float*)cval, cnt_out, mp);
+}
+
 template <bool BATCH>
 msp_status launch_symbolic_bin(msp_handle* h, const BinSpec& s, Work wk, int rows, const Operands& op,
                                int32_t* rnnz, const RowMap& mp, const int32_t* ufilter, int umax) {
@@ -529,6 +555,8 @@ template msp_status launch_symbolic_bin<true>(msp_handle*, const BinSpec&, Work,
                                               const RowMap&, const int32_t*, int);
 template msp_status launch_numeric_bin<true>(msp_handle*, const BinSpec&, Work, int, const Operands&,
                                              const int64_t*, int32_t*, void*, int32_t*, const RowMap&);
+template msp_status launch_sort_rest<true>(msp_handle*, int, const Operands&, const int64_t*, int32_t*, void*,
+                                           int32_t*, const RowMap&);
 
 Operands operands_of(const msp_csr* A, const msp_csr* B) {
     Operands op;
@@ -721,12 +749,20 @@ static msp_status run_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, co
         }
     if (nonempty == 0) return MSP_OK;
     DevInfo* info = h->info.as<DevInfo>();
+    auto sort_rest = [&]() -> msp_status {
+        int rows = 0;
+        for (int b = 1; numeric && b <= nb; ++b)
+            if (plan.spec[b].kind == Kind::Block) rows += counts[b];
+        return launch_sort_rest<false>(h, rows, operands_of(A, B), crp, ccol, cval, cnt_out, RowMap{});
+    };
     auto rowq = [&](int b) { return &info->queue[numeric ? 1 : 0][b][0]; };
     // bin done_bin was already processed: its rows must not be taken again
     const bool done_rows = done_bin > 0 && counts[done_bin] > 0;
     if (!done_rows && (nonempty == 1 || all_group)) {
-        return numeric ? launch_numeric(h, plan.spec[last], m, nullptr, A, B, crp, ccol, cval, cnt_out, rowq(last))
-                       : launch_symbolic(h, plan.spec[last], m, nullptr, A, B, rnnz, rowq(last));
+        const msp_status r =
+            numeric ? launch_numeric(h, plan.spec[last], m, nullptr, A, B, crp, ccol, cval, cnt_out, rowq(last))
+                    : launch_symbolic(h, plan.spec[last], m, nullptr, A, B, rnnz, rowq(last));
+        return r == MSP_OK ? sort_rest() : r;
     }
     msp_status s = h->perm.ensure((size_t)m * 4);
     if (s != MSP_OK) return s;
@@ -796,7 +832,8 @@ static msp_status run_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, co
         if ((e = hipEventRecord(h->join_ev[i], h->side[i])) == hipSuccess)
             e = hipStreamWaitEvent(main_st, h->join_ev[i], 0);
     if (s != MSP_OK) return s;
-    return e == hipSuccess ? MSP_OK : hip_fail(e, "joining the side streams");
+    if (e != hipSuccess) return hip_fail(e, "joining the side streams");
+    return sort_rest();
 }
 
 msp_status run_symbolic_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, const BinPlan& plan,

@@ -116,3 +116,49 @@ def test_row_kernel_many_rows_per_wave(h, dtype):
     kb = rng.integers(0, 14, size=5_000)
     check_full(h, A, gen.erdos_renyi(5_000, 300_000, kb, seed=7, dtype=dtype))
     check_full(h, A, gen.erdos_renyi(5_000, 3_000, kb, seed=8, dtype=dtype))
+
+
+# name: (total products, A entries, distinct columns, first and last column)
+SORT_CASES = {
+    "cap_128": (1024, 40, 900, 0, 1_500_000),
+    "over_128": (1025, 40, 900, 0, 1_500_000),
+    "cap_256": (2048, 200, 1900, 0, 3000),
+    "over_256": (2049, 200, 1900, 0, 3000),
+    "cap_512": (4096, 300, 3900, 0, 1_500_000),
+    "over_512": (4097, 300, 3900, 0, 1_500_000),
+    "entries_128": (900, 128, 850, 0, 50_000),
+    "entries_129": (900, 129, 850, 0, 50_000),
+    "entries_767": (900, 767, 850, 0, 50_000),
+    "entries_768": (900, 768, 850, 0, 50_000),
+    "entries_3071": (3900, 3071, 2900, 0, 1_500_000),
+    "entries_3072": (3900, 3072, 2900, 0, 1_500_000),
+    "one_entry": (3000, 1, 3000, 0, 1_500_000),
+    "apart": (1500, 10, 60_000, 0, 1_500_000),
+    "bucket_256": (3000, 256, 2500, -1, 1_500_000),
+    "bucket_257": (3000, 257, 2500, -1, 1_500_000),
+}
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("name", sorted(SORT_CASES))
+def test_sort_kernel_edges(h, name, dtype):
+    """Rows of 513 to 4096 outputs at the workgroup sort's limits of products,
+    A entries and products in one bucket (first column -1: every B row starts
+    with column 0), with empty B rows among the entries."""
+    total, na, pool, lo, hi = SORT_CASES[name]
+    rng = np.random.default_rng(total + 7 * na)
+    arows, brows = [], []
+    for _ in range(9):
+        first = len(brows)
+        # an empty B row before, between and after; they are entries too
+        lens = np.zeros(na, np.int64)
+        full = [i for i in range(na) if not (16 < na < 900 and lo >= 0 and i in (0, na // 3, na - 1))]
+        lens[full] = _lengths(total, len(full))
+        cols = 1 + np.sort(rng.permutation(hi - 1)[:pool])
+        for length in lens:
+            pick = cols[rng.permutation(pool)[: length - (lo < 0)]] if length else cols[:0]
+            brows.append(np.concatenate([[0], pick]) if lo < 0 else pick)
+        arows.append(np.arange(first, first + na))
+    A = _csr(arows, len(brows), rng, dtype)
+    B = _csr(brows, hi + 1, rng, dtype)
+    check_full(h, A, B)
