@@ -378,4 +378,219 @@ k_num_sort(Work wk,
     if (err) atomicOr(&info->err, err);
 }
 
+// Symbolic, one workgroup per row of at most BS R products (positions in B
+// below 2^32): the products' columns in registers, each joins the list of its
+// column's hash slot with one LDS exchange and counts unless an earlier member
+// has its column.  Rows of more products (their bound was B's width) are
+// appended to fb_list for the bitmap kernel.  Rows above the records'
+// threshold leave their outputs per window, as every symbolic workgroup
+// kernel does.
+//
+// Bound by LDS, as k_num_sort.  On a sparse power-law matrix of 2^20 rows the
+// LDS hash before took 2077 us for the rows of 2049 to 8192 products (1041
+// here), 1487 for those up to 16,384 (1250) and 548 for those up to 2048
+// (564); a single row of 1030 short B rows took it 49 us, walking from product
+// to product (the rows above 2048 products of a power-law matrix of 171,000
+// rows: 123 and 68 us before, 50 and 30 here).
+template <int BS, int R, bool BATCH = false>
+__global__ void __launch_bounds__(BS, BS <= 256 ? 5 : 4)
+k_sym_list(Work wk,
+           const int64_t* __restrict__ arp, const int32_t* __restrict__ acol,
+           const int64_t* __restrict__ brp, const int32_t* __restrict__ bcol,
+           int32_t* __restrict__ row_nnz, DevInfo* info, RowMap mp, WinRec rec, unsigned* q,
+           int32_t* __restrict__ fb_list, int* fb_count) {
+    constexpr int CAP = BS * R, NW = BS / 64, WORDS = CAP / 64, H = CAP <= 2048 ? CAP : CAP / 2;
+    constexpr int WL = (WORDS + 63) / 64;                // mark words a lane
+    static_assert(CAP < 65536 && 64 % NW == 0, "16-bit members; a step's words lie in one lane register");
+    int nrows_bin;
+    const int32_t* perm;
+    work_rows(wk, &nrows_bin, &perm);
+    __shared__ __align__(16) int32_t head[H];
+    __shared__ int32_t lc[CAP];                          // members' columns; before them the entries' positions
+    __shared__ uint16_t lp[CAP];                         // the member before, 0xffff: none
+    __shared__ unsigned long long mark[WORDS];
+    __shared__ int s_wc[BATCH ? 1 : kWinMaxNw];
+    __shared__ int s_rslot;
+    __shared__ long long s_slot;
+    __shared__ int s_sum[NW], s_some[NW], s_cnt[NW];
+    uint32_t* const base = reinterpret_cast<uint32_t*>(lc);
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    struct Head {
+        int row;
+        long long a0, a1, bo;
+    };
+    auto head_of = [&](long long slot) {
+        Head h;
+        h.row = __builtin_amdgcn_readfirstlane(perm ? perm[slot] : (int)slot);
+        h.a0 = arp[h.row];
+        h.a1 = arp[h.row + 1];
+        h.bo = row_boff<BATCH>(mp, h.row);
+        return h;
+    };
+    auto load_entry = [&](const Head& h, int* k) {
+        if (h.a1 > h.a0) *k = acol[h.a0 + tid < h.a1 ? h.a0 + tid : h.a1 - 1];
+    };
+    auto load_bounds = [&](const Head& h, int k, long long* b0, long long* b1) {
+        if (h.a1 <= h.a0) return;
+        *b0 = brp[k + h.bo];
+        *b1 = brp[k + h.bo + 1];
+    };
+
+    block_draw(q, (long long)blockIdx.x - gridDim.x, &s_slot);
+    __syncthreads();
+    long long slot = s_slot;
+    if (slot < nrows_bin) {                              // uniform
+        Head cur = head_of(slot);
+        int k = 0, kn = 0;
+        long long b0 = 0, b1 = 0, b0n = 0, b1n = 0;
+        load_entry(cur, &k);
+        load_bounds(cur, k, &b0, &b1);
+        while (true) {
+            const long long na = cur.a1 - cur.a0;
+            // A entries, BS at a time (the first ones were loaded ahead)
+            for (int i = tid; i < WORDS; i += BS) mark[i] = 0ull;
+            for (int i = tid; i < H / 4; i += BS) reinterpret_cast<int4*>(head)[i] = make_int4(-1, -1, -1, -1);
+            int total = 0, entries = 0;
+            for (long long e0 = 0; e0 < na && total <= CAP; e0 += BS) {     // uniform
+                if (e0 > 0) {
+                    if (e0 + tid < na) {
+                        const long long kk = acol[cur.a0 + e0 + tid] + cur.bo;
+                        b0 = brp[kk];
+                        b1 = brp[kk + 1];
+                    }
+                    __syncthreads();                     // the wave sums before are read
+                }
+                int n = 0;
+                if (e0 + tid < na) n = (int)(b1 - b0 < CAP + 1 ? b1 - b0 : CAP + 1);
+                const int incl = wave_scan(n);
+                const uint64_t some = __ballot(n > 0);
+                if (lane == 63) {
+                    s_sum[wv] = incl;
+                    s_some[wv] = __builtin_popcountll(some);
+                }
+                __syncthreads();
+                int first = total + incl - n, idx = entries;
+#pragma unroll
+                for (int i = 0; i < NW; ++i) {
+                    if (i < wv) {
+                        first += s_sum[i];
+                        idx += s_some[i];
+                    }
+                    total = min(total + s_sum[i], 1 << 26);
+                    entries += s_some[i];
+                }
+                if (n > 0 && first + n <= CAP) {         // (then fewer than CAP entries lie before)
+                    idx = lanes_below(some, idx);
+                    base[idx] = (uint32_t)b0 - (uint32_t)first;
+                    const int last = first + n - 1;
+                    atomicOr(reinterpret_cast<uint32_t*>(mark) + (last >> 5), 1u << (last & 31));
+                }
+            }
+            const bool takes = total <= CAP;             // uniform
+            block_draw(q, slot, &s_slot);
+            __syncthreads();
+            const long long next = s_slot;
+            const bool more = next < nrows_bin;          // uniform
+            const Head nxt = head_of(more ? next : slot);
+            load_entry(nxt, &kn);
+            int c[R];
+            if (takes) {
+                // lane i of every wave: mark words i, 64 + i, ..., and the marks before them
+                int lo[WL], hi[WL], pre[WL], sum = 0;
+#pragma unroll
+                for (int j = 0; j < WL; ++j) {
+                    const unsigned long long w = 64 * j + lane < WORDS ? mark[64 * j + lane] : 0ull;
+                    lo[j] = (int)(uint32_t)w;
+                    hi[j] = (int)(uint32_t)(w >> 32);
+                    const int m = __builtin_popcountll(w), incl = wave_scan(m);
+                    pre[j] = sum + incl - m;
+                    sum += __builtin_amdgcn_readlane(incl, 63);
+                }
+#pragma unroll
+                for (int s = 0; s < R; ++s) {
+                    c[s] = 0;
+                    if ((s * NW + wv) * 64 < total) {    // wave-uniform
+                        const int p = (s * NW + wv) * 64 + lane, i = (s * NW & 63) + wv, j = s * NW / 64;
+                        const int e = lanes_below((uint32_t)__builtin_amdgcn_readlane(lo[j], i),
+                                                  (uint32_t)__builtin_amdgcn_readlane(hi[j], i),
+                                                  __builtin_amdgcn_readlane(pre[j], i));
+                        // lanes past the last product read it again
+                        const uint32_t at = base[min(e, entries - 1)] + (uint32_t)min(p, total - 1);
+                        c[s] = bcol[at];
+                    }
+                }
+            }
+            load_bounds(nxt, kn, &b0n, &b1n);
+            __syncthreads();                             // the entries' positions are read
+            if (takes) {
+                int prev[R];
+#pragma unroll
+                for (int s = 0; s < R; ++s) {
+                    const int p = (s * NW + wv) * 64 + lane;
+                    prev[s] = -1;
+                    if (p < total) {
+                        prev[s] = atomicExch(&head[hash_slot<H>(c[s])], p);
+                        lc[p] = c[s];
+                        lp[p] = (uint16_t)prev[s];
+                    }
+                }
+                __syncthreads();
+                uint32_t own = 0;                        // steps whose product counts
+#pragma unroll
+                for (int g = 0; g < R; g += 4) {
+                    // four products a lane at once, back through the lists
+                    int live = 0;
+#pragma unroll
+                    for (int s = g; s < g + 4; ++s) {
+                        own |= (uint32_t)((s * NW + wv) * 64 + lane < total) << s;
+                        live |= (prev[s] >= 0) << (s - g);
+                    }
+                    while (__ballot(live != 0)) {
+                        int x[4], y[4];
+#pragma unroll
+                        for (int s = g; s < g + 4; ++s) {
+                            x[s - g] = lc[max(prev[s], 0)];
+                            y[s - g] = lp[max(prev[s], 0)];
+                        }
+#pragma unroll
+                        for (int s = g; s < g + 4; ++s) {
+                            const bool on = (live >> (s - g)) & 1, same = x[s - g] == c[s];
+                            if (on && same) own &= ~(1u << s);
+                            if (on && (same || y[s - g] == 0xffff)) live &= ~(1 << (s - g));
+                            if (on) prev[s] = y[s - g];
+                        }
+                    }
+                }
+                const int cnt = __builtin_amdgcn_readlane(wave_scan(__builtin_popcount(own)), 63);
+                if (lane == 0) s_cnt[wv] = cnt;
+                __syncthreads();
+                int tot = 0;
+#pragma unroll
+                for (int i = 0; i < NW; ++i) tot += s_cnt[i];
+                if (tid == 0) row_nnz[cur.row] = tot;
+                if constexpr (!BATCH) {
+                    if (win_record_open((int*)rec.cnt, rec.nw, rec.thresh, rec.nrec, tot, s_wc, &s_rslot)) {
+#pragma unroll
+                        for (int s = 0; s < R; ++s)
+                            if ((own >> s) & 1u) atomicAdd(&s_wc[c[s] >> kWinLog], 1);
+                        win_record_close(rec, cur.row, s_wc, &s_rslot);
+                    }
+                }
+            } else if (tid == 0) {
+                fb_list[atomicAdd(fb_count, 1)] = cur.row;
+            }
+            if (!more) break;
+            slot = next;
+            cur = nxt;
+            k = kn;
+            b0 = b0n;
+            b1 = b1n;
+            __syncthreads();                             // the next row writes what this one still reads
+        }
+    }
+    block_slots_done(q);
+    (void)info;
+}
+
 }  // namespace msp

@@ -203,6 +203,10 @@ msp_status launch_symbolic_bin(msp_handle* h, const BinSpec& s, Work wk, int row
 template <bool BATCH>
 msp_status launch_numeric_bin(msp_handle* h, const BinSpec& s, Work wk, int rows, const Operands& op,
                               const int64_t* crp, int32_t* ccol, void* cval, int32_t* cnt_out, const RowMap& mp);
+// After a symbolic phase's bins: the rows its Block bins left to the bitmap
+// kernel (see spgemm.hip).
+template <bool BATCH>
+msp_status launch_list_rest(msp_handle* h, int rows, int most, const Operands& op, int32_t* rnnz, const RowMap& mp);
 // After a numeric phase's bins: the rows its Block bins (of `rows` rows) left
 // to the hash kernel.
 template <bool BATCH>

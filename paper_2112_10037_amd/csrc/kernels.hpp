@@ -730,73 +730,6 @@ struct GroupCfg {
     static constexpr int NG = BS / G;
 };
 
-// Symbolic, one workgroup of BS threads per row, T key slots (LDS).
-template <int BS, int T, bool BATCH = false>
-__global__ void __launch_bounds__(BS)
-k_sym_block(Work wk,
-            const int64_t* __restrict__ arp, const int32_t* __restrict__ acol,
-            const int64_t* __restrict__ brp, const int32_t* __restrict__ bcol,
-            int32_t* __restrict__ row_nnz, DevInfo* info, RowMap mp, WinRec rec,
-            unsigned* q) {
-    int nrows_bin;
-    const int32_t* perm;
-    work_rows(wk, &nrows_bin, &perm);
-    __shared__ long long s_slot;
-    __shared__ int32_t keys[T];
-    __shared__ int s_wc[BATCH ? 1 : kWinMaxNw];
-    __shared__ int s_rslot;
-    __shared__ long long s_off[BS];
-    __shared__ long long s_bst[BS];
-    __shared__ BlockScanSmem<BS> sm;
-    const int tid = threadIdx.x;
-    int err = 0;
-    for (long long slot = block_first(q, &s_slot); slot < nrows_bin; slot = block_next(q, slot, &s_slot)) {
-        const int row = perm ? perm[slot] : (int)slot;
-        const long long bo = row_boff<BATCH>(mp, row);
-        for (int s = tid; s < T; s += BS) keys[s] = kEmpty;
-        __syncthreads();
-        const long long a0 = arp[row], a1 = arp[row + 1];
-        long long cnt = 0;
-        for (long long c0 = a0; c0 < a1; c0 += BS) {
-            const long long p = c0 + tid;
-            long long len = 0, bst = 0;
-            if (p < a1) {
-                const long long k = acol[p] + bo;
-                bst = brp[k];
-                len = brp[k + 1] - bst;
-            }
-            long long total;
-            const long long incl = block_incl_scan<BS>(len, sm, &total);
-            s_off[tid] = incl;
-            s_bst[tid] = bst - (incl - len);
-            __syncthreads();
-            const int nact = (int)((a1 - c0) < BS ? (a1 - c0) : BS);
-            int t = -1;                     // owner of q: one search, then it only moves forward
-            for (long long q = tid; q < total; q += BS) {
-                if (t < 0) t = owner_search(s_off, nact, q);
-                else while ((long long)s_off[t] <= q) ++t;
-                const int32_t j = bcol[s_bst[t] + q];
-                cnt += hash_insert_key<T>(keys, j, &err);
-            }
-            __syncthreads();
-        }
-        const long long tot = block_sum<BS>(cnt, sm);
-        if (tid == 0) row_nnz[row] = (int32_t)tot;
-        if constexpr (!BATCH) {
-            if (win_record_open((int*)rec.cnt, rec.nw, rec.thresh, rec.nrec, tot, s_wc, &s_rslot)) {
-                for (int i = tid; i < T; i += BS) {
-                    const int32_t k = keys[i];
-                    if (k != kEmpty) atomicAdd(&s_wc[k >> kWinLog], 1);
-                }
-                win_record_close(rec, row, s_wc, &s_rslot);
-            }
-        }
-        __syncthreads();
-    }
-    block_slots_done(q);
-    if (err) atomicOr(&info->err, kErrProbe);
-}
-
 // Symbolic for the largest rows: an n-bit bitmap (LDS when it fits, else a
 // per-workgroup global slab), counting bits that an atomic OR newly sets.
 template <int BS, bool LDSBM, bool BATCH = false>

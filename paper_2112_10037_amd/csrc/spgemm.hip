@@ -88,14 +88,12 @@ BinPlan symbolic_plan(const msp_tuning& t, bool force_spill) {
     if (!force_spill) {
         add_small_bins(p, t, t.block_rows, false);
         static const int umax[4] = {512, 2048, 8192, 16384};
-        static const int bs[4] = {256, 512, 1024, 1024};
+        static const int bs[4] = {256, 256, 512, 1024};
         int last = p.table.umax[p.table.nb - 1];
         for (int i = 0; i < 4; ++i) {
-            int T = std::min(32768, next_pow2(umax[i]) << t.hash_scale);
-            int u = std::min(umax[i], T / 2);
-            if (u <= last) continue;
-            add_bin(p, u, BinSpec{Kind::Block, bs[i], T});
-            last = u;
+            if (umax[i] <= last) continue;
+            add_bin(p, umax[i], BinSpec{Kind::Block, bs[i], umax[i] <= 2048 ? 8 : 16});
+            last = umax[i];
         }
     }
     p.spec[p.table.nb] = BinSpec{Kind::Bitmap, 1024, 0};
@@ -145,8 +143,7 @@ static int win_lds(const msp_handle* h) {
 #define MSP_SYM_ROW_SHAPES(X) MSP_NUM_ROW_SHAPES(X) X(2048)
 #define MSP_SYM_BATCH_SHAPES(X) X(32, 16) X(64, 16) X(128, 8)
 #define MSP_NUM_BATCH_SHAPES(X) X(32, 12) X(32, 8) X(32, 4) X(64, 8) X(64, 4) X(64, 2)
-#define MSP_SYM_BLOCK_SHAPES(X) \
-    X(256, 1024) X(256, 2048) X(512, 4096) X(512, 8192) X(1024, 16384) X(1024, 32768)
+#define MSP_SYM_LIST_SHAPES(X) X(256, 8) X(512, 16) X(1024, 16)
 // workgroup threads of the numeric counting sort; every size takes kSortR
 // products a thread
 #define MSP_NUM_SORT_SHAPES(X) X(128) X(256) X(512)
@@ -168,8 +165,8 @@ static bool spec_supported(const BinSpec& sp, bool numeric) {
 #undef X
             return false;
         case Kind::Block:
-#define X(BS, T) if (!numeric && sp.lanes == BS && sp.slots == T) return true;
-            MSP_SYM_BLOCK_SHAPES(X)
+#define X(BS, R) if (!numeric && sp.lanes == BS && sp.slots == R) return true;
+            MSP_SYM_LIST_SHAPES(X)
 #undef X
 #define X(BS) if (numeric && sp.lanes == BS && sp.slots == kSortR) return true;
             MSP_NUM_SORT_SHAPES(X)
@@ -285,6 +282,10 @@ static msp_status launch_check(const char* what) {
     return MSP_OK;
 }
 
+// The list kernel keeps positions in B in 32 bits; without them its rows take
+// the bitmap kernel.
+static bool list_positions(const Operands& op) { return op.bnnz < (1LL << 32); }
+
 // symbolic kernel of one bin over the rows of `wk`; `rows` (the row count,
 // or an estimate when wk reads it from the device) sizes persistent grids
 template <bool BATCH>
@@ -326,17 +327,19 @@ static msp_status launch_symbolic_t(msp_handle* h, const BinSpec& s, Work wk, in
     }
         MSP_SYM_ROW_SHAPES(X)
 #undef X
-    } else if (s.kind == Kind::Block) {
-        const int grid = std::min(rows, 4 * h->num_cu);
-#define X(BS, T)                                                                                       \
-    if (s.lanes == BS && s.slots == T) {                                                               \
-        k_sym_block<BS, T, BATCH><<<grid, BS, 0, st>>>(wk, op.arp, op.acol, op.brp, op.bcol, rnnz, info, mp, rec, \
-                                                       rq);                                              \
-        return launch_check("k_sym_block");                                                            \
+    } else if (s.kind == Kind::Block && list_positions(op)) {
+        // rows past the lists go to the bounds array, which the symbolic pass
+        // has read by then; launch_list_rest takes them
+#define X(BS, R)                                                                                           \
+    if (s.lanes == BS && s.slots == R) {                                                                   \
+        const int grid = group_grid(h, (const void*)k_sym_list<BS, R, BATCH>, rows, 1, BS);               \
+        k_sym_list<BS, R, BATCH><<<grid, BS, 0, st>>>(wk, op.arp, op.acol, op.brp, op.bcol, rnnz, info, mp, rec, \
+                                                      rq, h->u.as<int32_t>(), &info->list_fb[0]);         \
+        return launch_check("k_sym_list");                                                                 \
     }
-        MSP_SYM_BLOCK_SHAPES(X)
+        MSP_SYM_LIST_SHAPES(X)
 #undef X
-    } else if (s.kind == Kind::Bitmap) {
+    } else if (s.kind == Kind::Bitmap || s.kind == Kind::Block) {
         const long long n = op.ncols;
         const long long words = (n + 31) / 32;
         const bool lds = words * 4 <= h->lds_per_block - kLdsReserve;
@@ -536,6 +539,19 @@ msp_status launch_sort_rest(msp_handle* h, int rows, const Operands& op, const i
     return launch_sort_rest_t<float, BATCH>(h, rows, op, crp, ccol, (float*)cval, cnt_out, mp);
 }
 
+// After a symbolic phase's bins: the rows its Block bins (of `rows` rows, with
+// bounds up to `most`) left to the bitmap kernel.  A row's bound is its product
+// count unless B is narrower (a batch's problems differ, so there it is always
+// launched).
+template <bool BATCH>
+msp_status launch_list_rest(msp_handle* h, int rows, int most, const Operands& op, int32_t* rnnz, const RowMap& mp) {
+    if (rows <= 0 || !list_positions(op) || (!BATCH && op.ncols > most)) return MSP_OK;
+    DevInfo* info = h->info.as<DevInfo>();
+    Work wk{h->u.as<int32_t>(), 0, &info->list_fb[0]};
+    wk.rowq = &info->queue[0][kNB][0];
+    return launch_symbolic_t<BATCH>(h, BinSpec{Kind::Bitmap, 1024, 0}, wk, std::min(rows, h->num_cu), op, rnnz, mp);
+}
+
 template <bool BATCH>
 msp_status launch_symbolic_bin(msp_handle* h, const BinSpec& s, Work wk, int rows, const Operands& op,
                                int32_t* rnnz, const RowMap& mp, const int32_t* ufilter, int umax) {
@@ -551,6 +567,7 @@ msp_status launch_numeric_bin(msp_handle* h, const BinSpec& s, Work wk, int rows
     return launch_numeric_t<float, BATCH>(h, s, wk, rows, op, crp, ccol, (float*)cval, cnt_out, mp);
 }
 
+template msp_status launch_list_rest<true>(msp_handle*, int, int, const Operands&, int32_t*, const RowMap&);
 template msp_status launch_symbolic_bin<true>(msp_handle*, const BinSpec&, Work, int, const Operands&, int32_t*,
                                               const RowMap&, const int32_t*, int);
 template msp_status launch_numeric_bin<true>(msp_handle*, const BinSpec&, Work, int, const Operands&,
@@ -749,11 +766,16 @@ static msp_status run_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, co
         }
     if (nonempty == 0) return MSP_OK;
     DevInfo* info = h->info.as<DevInfo>();
-    auto sort_rest = [&]() -> msp_status {
-        int rows = 0;
-        for (int b = 1; numeric && b <= nb; ++b)
-            if (plan.spec[b].kind == Kind::Block) rows += counts[b];
-        return launch_sort_rest<false>(h, rows, operands_of(A, B), crp, ccol, cval, cnt_out, RowMap{});
+    // what the Block bins left, after all bins
+    auto rest = [&]() -> msp_status {
+        int rows = 0, most = 0;
+        for (int b = 1; b <= nb; ++b)
+            if (plan.spec[b].kind == Kind::Block && counts[b] > 0) {
+                rows += counts[b];
+                most = plan.table.umax[b];
+            }
+        return numeric ? launch_sort_rest<false>(h, rows, operands_of(A, B), crp, ccol, cval, cnt_out, RowMap{})
+                       : launch_list_rest<false>(h, rows, most, operands_of(A, B), rnnz, RowMap{});
     };
     auto rowq = [&](int b) { return &info->queue[numeric ? 1 : 0][b][0]; };
     // bin done_bin was already processed: its rows must not be taken again
@@ -762,7 +784,7 @@ static msp_status run_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, co
         const msp_status r =
             numeric ? launch_numeric(h, plan.spec[last], m, nullptr, A, B, crp, ccol, cval, cnt_out, rowq(last))
                     : launch_symbolic(h, plan.spec[last], m, nullptr, A, B, rnnz, rowq(last));
-        return r == MSP_OK ? sort_rest() : r;
+        return r == MSP_OK ? rest() : r;
     }
     msp_status s = h->perm.ensure((size_t)m * 4);
     if (s != MSP_OK) return s;
@@ -833,7 +855,7 @@ static msp_status run_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, co
             e = hipStreamWaitEvent(main_st, h->join_ev[i], 0);
     if (s != MSP_OK) return s;
     if (e != hipSuccess) return hip_fail(e, "joining the side streams");
-    return sort_rest();
+    return rest();
 }
 
 msp_status run_symbolic_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, const BinPlan& plan,

@@ -70,6 +70,7 @@ struct DevInfo {
     int win_nrec;                         // window records the symbolic pass made
     int win_fb[2];                        // global-bin rows without a record: {count, 0}
     int sort_fb[2];                       // numeric rows the workgroup sort left to the hash: {count, 0}
+    int list_fb[2];                       // symbolic rows the workgroup lists left to the bitmap: {count, 0}
     int win_nbs;                          // B rows given a window index
     int win_nbms;                         // rows whose bitmap the symbolic pass stored
     int learned_big;                      // learned product: rows sent to the exact path by capacity

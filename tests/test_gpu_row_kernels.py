@@ -162,3 +162,41 @@ def test_sort_kernel_edges(h, name, dtype):
     A = _csr(arows, len(brows), rng, dtype)
     B = _csr(brows, hi + 1, rng, dtype)
     check_full(h, A, B)
+
+
+# name: (total products, A entries, distinct columns, columns of B)
+LIST_CASES = {
+    "cap_2048": (2048, 100, 1800, 1_200_000),
+    "over_2048": (2049, 100, 1800, 1_200_000),
+    "cap_8192": (8192, 700, 7000, 1_200_000),
+    "over_8192": (8193, 700, 7000, 1_200_000),
+    "cap_16384": (16384, 1500, 12_000, 1_200_000),
+    "over_16384": (16385, 1500, 12_000, 1_200_000),
+    "single_entries": (5000, 5000, 4000, 1_200_000),
+    "one_entry": (5000, 1, 5000, 1_200_000),
+    "width_bounds": (9000, 40, 3000, 3000),
+    "width_bounds_16k": (40_000, 40, 12_000, 12_000),
+}
+
+
+@pytest.mark.parametrize("name", sorted(LIST_CASES))
+def test_list_kernel_edges(h, name):
+    """Symbolic rows of 1025 to 16,384 products at the workgroup lists' limits,
+    rows bounded by B's width rather than their products, and both numeric
+    thresholds that leave window records."""
+    total, na, pool, n = LIST_CASES[name]
+    rng = np.random.default_rng(total + na)
+    arows, brows = [], []
+    for _ in range(7):
+        first = len(brows)
+        cols = np.sort(rng.permutation(n)[:pool])
+        for length in _lengths(total, na):
+            brows.append(cols[rng.permutation(pool)[:length]])
+        arows.append(np.arange(first, first + na))
+    A = _csr(arows, len(brows), rng, np.float32)
+    B = _csr(brows, n, rng, np.float32)
+    check_full(h, A, B)
+    check_full(h, A, B, tuning=(1, 0, 512, 128, 8))
+    nnz = h.symbolic(binding.DeviceCSR.from_host(A), binding.DeviceCSR.from_host(B))
+    import oracle
+    assert np.array_equal(nnz[0].cpu().numpy(), oracle.row_nnz(A, B))
