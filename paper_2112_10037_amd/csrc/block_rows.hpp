@@ -29,11 +29,6 @@ namespace msp {
 constexpr int kSortBucket = 256;
 constexpr int kSortR = 8;
 
-// Slot of the next row, drawn by thread 0 while the current row is worked on.
-__device__ __forceinline__ void block_draw(unsigned* q, long long slot, long long* s_slot) {
-    if (threadIdx.x == 0) *s_slot = q ? (long long)atomicAdd(q, 1u) : slot + gridDim.x;
-}
-
 template <int BS, int R>
 struct SortCfg {
     static constexpr int kCap = BS * R;                  // products

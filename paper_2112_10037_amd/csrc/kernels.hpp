@@ -130,6 +130,49 @@ __device__ __forceinline__ uint64_t group_ballot(bool p, int lane) {
 }
 
 // ---------------------------------------------------------------------------
+// Wave primitives by DPP (all 64 lanes active)
+// ---------------------------------------------------------------------------
+
+// One value per lane: inclusive prefix sum over the wave (all 64 lanes active).
+__device__ __forceinline__ int wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
+// Smallest and largest of a value over the wave (all 64 lanes active).
+__device__ __forceinline__ int wave_least(int x) {
+    x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x111, 0xf, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x112, 0xf, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x114, 0xf, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x118, 0xf, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x142, 0xa, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(x, 63);
+}
+__device__ __forceinline__ int wave_most(int x) {
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x111, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x112, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x114, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x118, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x142, 0xa, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(x, 63);
+}
+
+// Set bits of a wave-wide mask below this lane, plus `add`.
+__device__ __forceinline__ int lanes_below(uint32_t lo, uint32_t hi, int add) {
+    return (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, (uint32_t)add));
+}
+__device__ __forceinline__ int lanes_below(uint64_t m, int add) {
+    return lanes_below((uint32_t)m, (uint32_t)(m >> 32), add);
+}
+
+// ---------------------------------------------------------------------------
 // Workgroup primitives (BS threads)
 // ---------------------------------------------------------------------------
 
@@ -216,6 +259,11 @@ __device__ __forceinline__ long long block_next(unsigned* q, long long slot, lon
     if (threadIdx.x == 0) *s_slot = atomicAdd(q, 1u);
     __syncthreads();
     return *s_slot;
+}
+
+// Slot of the next row, drawn by thread 0 while the current row is worked on.
+__device__ __forceinline__ void block_draw(unsigned* q, long long slot, long long* s_slot) {
+    if (threadIdx.x == 0) *s_slot = q ? (long long)atomicAdd(q, 1u) : slot + gridDim.x;
 }
 
 // The last workgroup out resets the queue: every other workgroup has taken
@@ -3036,6 +3084,50 @@ k_bwin_index(long long brows, const int64_t* __restrict__ brp, const int32_t* __
     }
 }
 
+// Walk of a wave over consecutive products of a chunk of nonempty A entries:
+// off[t] is the number of the chunk's products up to and with entry t.  A
+// window takes up to 64 W products from q0 on: a bit for each entry that ends
+// in it goes into W mark words (this wave's LDS), and the entry of product
+// q0 + 64 s + lane is the window's first entry plus the marks below it (two
+// bit counts on a word that the wave shares).  No search, and the window's
+// products are independent of each other, so their loads are in flight
+// together.
+template <int W>
+struct WaveWindow {
+    int lo, hi, pre;            // lane s: word s of the marks, and the entries up to it
+    int next;                   // the next window's first entry
+
+    // the window from q0 < qe, whose product q0 belongs to entry t0; returns
+    // its products (it ends early after 64 entries)
+    __device__ __forceinline__ int open(const uint32_t* off, int nact, int t0, uint32_t q0, uint32_t qe,
+                                        unsigned long long* mark) {
+        const int lane = threadIdx.x & 63;
+        const int rel = t0 + lane < nact ? (int)min(off[t0 + lane] - q0, 64u * W + 1u) : 64 * W + 1;
+        int len = (int)min(qe - q0, 64u * W);
+        len = min(len, __builtin_amdgcn_readlane(rel, 63));   // (entries past these 64 stay for the next window)
+        if (lane < W) mark[lane] = 0ull;
+        lds_fence();
+        if (rel <= len) atomicOr(reinterpret_cast<uint32_t*>(mark) + ((rel - 1) >> 5), 1u << ((rel - 1) & 31));
+        lds_fence();
+        const unsigned long long w = lane < W ? mark[lane] : 0ull;
+        lo = (int)(uint32_t)w;
+        hi = (int)(uint32_t)(w >> 32);
+        const int c = __builtin_popcountll(w), incl = wave_scan(c);
+        pre = t0 + incl - c;
+        next = t0 + __builtin_amdgcn_readlane(incl, 63);
+        return len;
+    }
+    __device__ __forceinline__ int entry(int s) const {
+        return lanes_below((uint32_t)__builtin_amdgcn_readlane(lo, s), (uint32_t)__builtin_amdgcn_readlane(hi, s),
+                           __builtin_amdgcn_readlane(pre, s));
+    }
+};
+
+// Set bits of a word below bit b.
+__device__ __forceinline__ int bits_below(unsigned long long word, int b) {
+    return __builtin_popcountll((word << (63 - b)) << 1);
+}
+
 // Numeric pass of a global-bin row with a window record.  The row's windows
 // are grouped into slices whose LDS cost (kWinFixed per window, kWinOut per
 // output, known exactly from the record) fits the budget; the greedy
@@ -3049,16 +3141,26 @@ k_bwin_index(long long brows, const int64_t* __restrict__ brp, const int32_t* __
 //      total must equal the record's count;
 //   4. accumulation pass: each product adds into the FP64 accumulator at its
 //      column's rank (LDS atomics);
-//   5. the slice's columns are listed in rank order from the bitmap, and the
-//      slice goes out with coalesced stores at its first output's place in C.
+//   5. the sums go out with coalesced stores at the slice's first output's
+//      place in C, then the slice's columns, listed in rank order from the
+//      bitmap where the sums were.
 // The products are dealt to the waves in contiguous runs, so the lanes of a
 // wave gather neighbouring entries of one B row.  Rows without a valid
 // record are appended to fb_list (their count in info->win_fb[0]) for the
 // self-counting global-bin kernel.
-constexpr int kWinBS = 1024;                   // threads of the windowed kernel (one workgroup per CU)
-constexpr int kWinRU = 4;                      // products per lane and pipeline stage
-constexpr bool kWinPipe = false;               // gathers of the next stage issued before the current LDS work
-constexpr bool kWinOr32 = true;                // bitmap pass: 32-bit atomic ORs instead of 64-bit
+//
+// What bounds it: on an R-MAT graph of 2^19 vertices (FP32, 7.3e9 products)
+// 31.3 ms, of which, measured with parts left out, about 14 ms are the
+// accumulation pass, 9 ms the output (the columns' listing half of it), 3 ms
+// the bitmap pass and the rest the set-up of rows and slices.  Two workgroups
+// of 512 threads overlap one row's passes with the other's gathers (33.9 ms
+// with one of 1024 and twice the slice); before the marks, the prefetch of the
+// next row, the columns in the sums' place (slices up to 1.5 times as wide)
+// and the odd word stride of the ranks, 39.3 ms.  A sparse power-law matrix of
+// 2^20 rows: 10.9 -> 8.2 ms.  Listing columns with the ranks, a run of words
+// a thread, took 46.7 ms: a skewed row's bits lie in few threads' words.
+constexpr int kWinBS = 512;                    // threads of the windowed kernel (two workgroups per CU)
+constexpr int kWinRU = 4;                      // 64-product steps per window of a wave's walk
 constexpr bool kWinSwizzle = true;             // accumulator index swizzled within 32-entry groups
 
 // Accumulator slots of a slice of n outputs, and the slot of rank r: with
@@ -3081,291 +3183,385 @@ k_num_win(Work wk, int nw, const int64_t* __restrict__ arp, const int32_t* __res
     int nrows_bin;
     const int32_t* perm;
     work_rows(wk, &nrows_bin, &perm);
-    __shared__ long long s_slot;
     constexpr int RU = kWinRU;
-    // FP64 values double the pipeline's registers: the second stage is kept for FP32 only
-    constexpr bool PIPE = kWinPipe && sizeof(VT) == 4;
     constexpr int NWV = BS / 64;
     extern __shared__ __align__(16) unsigned long long dyn_win[];
-    __shared__ long long s_off[BS];
+    // the nonempty A entries of a chunk: products up to and with the entry,
+    // B position of its product q minus q, value
+    __shared__ uint32_t s_off[BS];
     __shared__ long long s_bst[BS];
-    __shared__ double s_a[BS];
-    __shared__ BlockScanSmem<BS> sm;
+    __shared__ VT s_a[BS];
+    __shared__ unsigned long long s_mark[NWV][RU];
+    __shared__ int s_sum[NWV], s_some[NWV];
     __shared__ int s_rk[kWinMaxNw + 1];         // outputs of the row before window w
     __shared__ int s_sb[kWinMaxNw + 1];         // first window of each slice
-    __shared__ int s_ns, s_rec;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    __shared__ int s_ns;
+    __shared__ long long s_slot;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nrec = min(__hip_atomic_load(rec.nrec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), rec.cap);
     bool bad = false;
-    for (long long slot = block_first(q, &s_slot); slot < nrows_bin; slot = block_next(q, slot, &s_slot)) {
-        const int row = perm ? perm[slot] : (int)slot;
-        const long long rp = crp[row], rlen = crp[row + 1] - rp;
-        if (tid == 0) {
-            int r = -1;
-            if (rlen > 0) {                             // (an empty row has nothing to write)
-                r = rec.islot[row];
-                if (r < 0 || r >= nrec || rec.row[r] != row) {
-                    r = -1;
-                    fb_list[atomicAdd(&info->win_fb[0], 1)] = row;
-                }
-            }
-            s_rec = r;
-        }
+
+    // exclusive prefix of one int per thread over the workgroup, and the
+    // total; one barrier, and the caller's next barrier frees s_sum
+    auto block_prefix = [&](int x, int* total) {
+        const int incl = wave_scan(x);
+        if (lane == 63) s_sum[wv] = incl;
         __syncthreads();
-        const int r = s_rec;
-        if (r >= 0) {
-            const int rbm = rec.bms ? rec.rec_bm[r] : -1;     // the row's stored bitmap, if any
-            const unsigned long long* sbm =
-                rbm >= 0 ? reinterpret_cast<const unsigned long long*>(rec.bms) + (long long)rbm * nw * kWinWords
-                         : nullptr;
-            // exclusive prefix of the window counts
-            const int c = tid < nw ? (int)rec.cnt[(long long)r * nw + tid] : 0;
-            long long tot;
-            const long long incl = block_incl_scan<BS>(c, sm, &tot);
-            if (tid < nw) s_rk[tid] = (int)(incl - c);
-            if (tid == 0) s_rk[nw] = (int)tot;
-            if (tot != rlen) bad = true;               // uniform
-            __syncthreads();
-            // slices: wave 0 takes, from each start, the longest run of windows that fits
-            if (wv == 0) {
-                int start = 0, ns = 0;
-                while (start < nw) {
-                    int e = start + 1;
-                    for (int b0 = start + 1; b0 <= nw; b0 += 64) {
-                        const int cand = b0 + lane;
-                        const bool fit = cand <= nw && (long long)kWinFixed * (cand - start) +
-                                                               (long long)kWinOut * (s_rk[cand] - s_rk[start]) +
-                                                               kWinSlack <= budget;
-                        const int run = leading_run(__ballot(fit));
-                        if (run > 0) e = b0 + run - 1;
-                        if (run < 64) break;
-                    }
-                    if (lane == 0) s_sb[ns] = start;
-                    ++ns;
-                    start = e;
-                }
-                if (lane == 0) {
-                    s_sb[ns] = nw;
-                    s_ns = ns;
-                }
-            }
-            __syncthreads();
-            const int ns = s_ns;
-            const long long a0 = arp[row], a1 = arp[row + 1];
-            const bool one_chunk = a1 - a0 <= BS;
-            // a one-chunk row keeps its thread's A entry across the slices
-            int my_bsl = -1;
-            long long my_s = 0, my_e = 0, my_cur = 0;
-            VT my_a = 0;
-            if (one_chunk && a0 + tid < a1) {
-                const long long p = a0 + tid;
-                const int k = acol[p];
-                my_a = aval[p];
-                my_s = brp[k];
-                my_e = brp[k + 1];
-                my_bsl = bslot[k];
-                my_cur = my_s;
-            }
-            for (int sl = 0; sl < ns && !bad; ++sl) {
-                const int w0 = s_sb[sl], w1 = s_sb[sl + 1];
-                const int nout = s_rk[w1] - s_rk[w0];
-                if (nout == 0) continue;                // uniform
-                const long long c_lo = (long long)w0 << kWinLog, c_hi = (long long)w1 << kWinLog;
-                const int nwd = (w1 - w0) * kWinWords;
-                unsigned long long* bm = dyn_win;
-                // word ranks within the slice (below 2^16: a slice holds at most budget / kWinOut outputs)
-                uint16_t* wr = reinterpret_cast<uint16_t*>(bm + nwd);
-                double* acc = reinterpret_cast<double*>(wr + nwd);            // nwd is a multiple of 64: 8-byte aligned
-                int32_t* colbuf = reinterpret_cast<int32_t*>(acc + win_acc_len(nout));
-                __syncthreads();                        // the previous slice is done with LDS
-                if (sbm) {
-                    for (int i = tid; i < nwd; i += BS) bm[i] = sbm[(long long)w0 * kWinWords + i];
-                } else {
-                    for (int i = tid; i < nwd; i += BS) bm[i] = 0ull;
-                }
+        int before = incl - x, all = 0;
+#pragma unroll
+        for (int i = 0; i < NWV; ++i) {
+            if (i == wv) before += all;
+            all += s_sum[i];
+        }
+        *total = all;
+        return before;
+    };
+
+    // A row's head, its record and its first A entries are loaded while the
+    // row before it is worked on, one dependent step at a time.
+    struct Row {
+        int row, r;                             // r: record, -1 for none
+        long long rp, rlen, a0, a1;
+        int cnt, rbm;                           // outputs in window tid; stored bitmap or -1
+        int k, bsl;                             // A entry tid (the last one past the end): column, index slot
+        VT a;
+        long long s, e;                         // and its B row
+    };
+    auto fetch_head = [&](Row& x, long long slot) {
+        x.row = __builtin_amdgcn_readfirstlane(perm ? perm[slot] : (int)slot);
+        x.rp = crp[x.row];
+        x.rlen = crp[x.row + 1] - x.rp;
+        x.a0 = arp[x.row];
+        x.a1 = arp[x.row + 1];
+        x.r = rec.islot[x.row];
+    };
+    auto fetch_entry = [&](Row& x) {
+        // (an empty row has nothing to write)
+        if (x.rlen <= 0 || x.r < 0 || x.r >= nrec || rec.row[x.r] != x.row) x.r = -1;
+        x.r = __builtin_amdgcn_readfirstlane(x.r);
+        x.k = 0;
+        x.a = (VT)0;
+        if (x.a1 > x.a0) {
+            const long long p = x.a0 + tid < x.a1 ? x.a0 + tid : x.a1 - 1;
+            x.k = acol[p];
+            x.a = aval[p];
+        }
+    };
+    auto fetch_part = [&](Row& x) {
+        x.cnt = 0;
+        x.rbm = -1;
+        x.s = x.e = 0;
+        x.bsl = -1;
+        if (x.r >= 0) {
+            if (tid < nw) x.cnt = (int)rec.cnt[(long long)x.r * nw + tid];
+            if (rec.bms) x.rbm = rec.rec_bm[x.r];
+        }
+        if (x.a1 > x.a0) {
+            x.s = brp[x.k];
+            x.e = brp[x.k + 1];
+            x.bsl = bslot[x.k];
+        }
+    };
+
+    block_draw(q, (long long)blockIdx.x - gridDim.x, &s_slot);
+    __syncthreads();
+    long long slot = s_slot;
+    if (slot < nrows_bin) {                             // uniform
+        Row cur, nxt;
+        fetch_head(cur, slot);
+        fetch_entry(cur);
+        fetch_part(cur);
+        while (true) {
+            __syncthreads();                            // the LDS of the row before and s_slot are read
+            block_draw(q, slot, &s_slot);
+            int tot;
+            const int c = cur.cnt;
+            const int rk0 = block_prefix(c, &tot);
+            const long long next = s_slot;
+            const bool more = next < nrows_bin;         // uniform
+            fetch_head(nxt, more ? next : slot);
+            int fetched = 1;                            // steps of the next row's loads
+            auto fetch = [&](int upto) {
+                if (fetched < 2 && upto >= 2) { fetch_entry(nxt); fetched = 2; }
+                if (fetched < 3 && upto >= 3) { fetch_part(nxt); fetched = 3; }
+            };
+            if (cur.r < 0) {
+                if (tid == 0 && cur.rlen > 0) fb_list[atomicAdd(&info->win_fb[0], 1)] = cur.row;
+            } else {
+                const long long rp = cur.rp, a0 = cur.a0, a1 = cur.a1;
+                if (tid < nw) s_rk[tid] = rk0;
+                if (tid == 0) s_rk[nw] = tot;
+                if (tot != cur.rlen) bad = true;        // uniform
                 __syncthreads();
-                // the part [lo, hi) of A entry p's B row in [c_lo, c_hi)
-                auto range = [&](long long s0, long long e0, int bsl, long long from, long long* lo, long long* hi) {
-                    if (bsl >= 0) {
-                        const int32_t* wp = wpos + (long long)bsl * (nw + 1);
-                        *lo = s0 + wp[w0];
-                        *hi = s0 + wp[w1];
-                    } else {
-                        *lo = lower_bound_col(bcol, from, e0, c_lo);
-                        *hi = lower_bound_col(bcol, *lo, e0, c_hi);
-                    }
-                };
-                // both passes walk the same products: PASS 0 sets bitmap bits,
-                // PASS 1 adds a * b at the column's rank
-                auto products = [&](auto pass_tag) {
-                    constexpr int PASS = decltype(pass_tag)::value;
-                    for (long long c0 = a0; c0 < a1; c0 += BS) {
-                        if (!(one_chunk && PASS == 1)) {     // a one-chunk row's ranges stay in LDS
-                            long long len = 0, bst = 0;
-                            double a = 0.0;
-                            const long long p = c0 + tid;
-                            if (p < a1) {
-                                long long lo, hi;
-                                if (one_chunk) {
-                                    range(my_s, my_e, my_bsl, my_cur, &lo, &hi);
-                                    my_cur = hi;
-                                    a = to_f64(my_a);
-                                } else {
-                                    const int k = acol[p];
-                                    a = to_f64(aval[p]);
-                                    const long long s0 = brp[k];
-                                    range(s0, brp[k + 1], bslot[k], s0, &lo, &hi);
-                                }
-                                bst = lo;
-                                len = hi - lo;
-                            }
-                            long long total;
-                            const long long incl = block_incl_scan<BS>(len, sm, &total);
-                            s_off[tid] = incl;
-                            s_bst[tid] = bst - (incl - len);
-                            s_a[tid] = a;
-                            __syncthreads();
+                // slices: wave 0 takes, from each start, the longest run of windows that fits
+                if (wv == 0) {
+                    int start = 0, ns = 0;
+                    while (start < nw) {
+                        int e = start + 1;
+                        for (int b0 = start + 1; b0 <= nw; b0 += 64) {
+                            const int cand = b0 + lane;
+                            const bool fit = cand <= nw && (long long)kWinFixed * (cand - start) +
+                                                                   (long long)kWinOut * (s_rk[cand] - s_rk[start]) +
+                                                                   kWinSlack <= budget;
+                            const int run = leading_run(__ballot(fit));
+                            if (run > 0) e = b0 + run - 1;
+                            if (run < 64) break;
                         }
-                        const long long total = s_off[BS - 1] > 0 ? s_off[BS - 1] : 0;
-                        const int nact = (int)((a1 - c0) < BS ? (a1 - c0) : BS);
-                        // contiguous runs of products per wave, whole 64-lane steps
-                        const long long per = ((total + NWV - 1) / NWV + 63) & ~63LL;
-                        const long long qb = (long long)wv * per;
-                        const long long qe = qb + per < total ? qb + per : total;
-                        // owner t of the lane's current product, with its end offset,
-                        // B base and value kept in registers (LDS reads only when t moves)
-                        int t = -1;
-                        long long t_end = 0, t_base = 0;
-                        VT t_a = 0;
-                        // two-stage pipeline: the gathers of the next RU products are
-                        // in flight while the current ones go into LDS
-                        int32_t jc[RU], jn[RU];
-                        VT vc[RU], vn[RU], ac[RU], an[RU];
-                        auto gather = [&](long long q0, int32_t* jj, VT* vv, VT* aa) {
-#pragma unroll
-                            for (int u = 0; u < RU; ++u) {
-                                const long long q = q0 + u * 64 + lane;
-                                jj[u] = -1;
-                                if (q < qe) {
-                                    if (t < 0 || t_end <= q) {
-                                        if (t < 0) t = owner_search(s_off, nact, q);
-                                        else do ++t; while (s_off[t] <= q);
-                                        t_end = s_off[t];
-                                        t_base = s_bst[t];
-                                        if constexpr (PASS == 1) t_a = (VT)s_a[t];
-                                    }
-                                    const long long bi = t_base + q;
-                                    jj[u] = bcol[bi];
-                                    if constexpr (PASS == 1) {
-                                        vv[u] = bval[bi];
-                                        aa[u] = t_a;
-                                    }
-                                }
-                            }
-                        };
-                        auto consume = [&](const int32_t* jj, const VT* vv, const VT* aa) {
-#pragma unroll
-                            for (int u = 0; u < RU; ++u) {
-                                if (jj[u] < 0) continue;
-                                const int jl = (int)(jj[u] - c_lo);
-                                const int w = jl >> 6;
-                                const unsigned long long bit = 1ull << (jl & 63);
-                                if constexpr (PASS == 0) {
-                                    if constexpr (kWinOr32)
-                                        atomicOr(reinterpret_cast<uint32_t*>(bm) + (jl >> 5), 1u << (jl & 31));
-                                    else
-                                        atomicOr(&bm[w], bit);
-                                } else {
-                                    const int rk = (int)wr[w] + __builtin_popcountll(bm[w] & (bit - 1ull));
-                                    atomicAdd(&acc[win_swz(rk)], to_f64(aa[u]) * to_f64(vv[u]));
-                                }
-                            }
-                        };
-                        if constexpr (PIPE) {
-                            if (qb < qe) gather(qb, jc, vc, ac);
-                            for (long long q0 = qb; q0 < qe; q0 += 64 * RU) {
-                                const bool more = q0 + 64 * RU < qe;      // wave-uniform
-                                if (more) gather(q0 + 64 * RU, jn, vn, an);
-                                consume(jc, vc, ac);
-#pragma unroll
-                                for (int u = 0; u < RU; ++u) {
-                                    jc[u] = jn[u];
-                                    vc[u] = vn[u];
-                                    ac[u] = an[u];
-                                }
-                            }
+                        if (lane == 0) s_sb[ns] = start;
+                        ++ns;
+                        start = e;
+                    }
+                    if (lane == 0) {
+                        s_sb[ns] = nw;
+                        s_ns = ns;
+                    }
+                }
+                const unsigned long long* sbm =
+                    cur.rbm >= 0 ? reinterpret_cast<const unsigned long long*>(rec.bms) +
+                                       (long long)cur.rbm * nw * kWinWords
+                                 : nullptr;
+                const bool one_chunk = a1 - a0 <= BS;
+                long long my_cur = cur.s;               // a one-chunk row's entry moves on with the slices
+                __syncthreads();
+                const int ns = s_ns;
+                for (int sl = 0; sl < ns && !bad; ++sl) {
+                    const int w0 = s_sb[sl], w1 = s_sb[sl + 1];
+                    const int nout = s_rk[w1] - s_rk[w0];
+                    if (nout == 0) continue;            // uniform
+                    const long long c_lo = (long long)w0 << kWinLog, c_hi = (long long)w1 << kWinLog;
+                    const int nwd = (w1 - w0) * kWinWords;
+                    unsigned long long* bm = dyn_win;
+                    // word ranks within the slice (below 2^16: a slice holds at most budget / kWinOut outputs)
+                    uint16_t* wr = reinterpret_cast<uint16_t*>(bm + nwd);
+                    double* acc = reinterpret_cast<double*>(wr + nwd);        // nwd is a multiple of 64: 8-byte aligned
+                    int32_t* colbuf = reinterpret_cast<int32_t*>(acc);        // once the sums are out
+                    __syncthreads();                    // the previous slice is done with LDS
+                    if (sbm) {
+                        const ulonglong2* src = reinterpret_cast<const ulonglong2*>(sbm + (long long)w0 * kWinWords);
+                        for (int i = tid; i < nwd / 2; i += BS) reinterpret_cast<ulonglong2*>(bm)[i] = src[i];
+                    } else {
+                        for (int i = tid; i < nwd / 2; i += BS)
+                            reinterpret_cast<ulonglong2*>(bm)[i] = make_ulonglong2(0ull, 0ull);
+                    }
+                    // the part [lo, hi) of an A entry's B row in [c_lo, c_hi)
+                    auto range = [&](long long s0, long long e0, int bsl, long long from, long long* lo,
+                                     long long* hi) {
+                        if (bsl >= 0) {
+                            const int32_t* wp = wpos + (long long)bsl * (nw + 1);
+                            *lo = s0 + wp[w0];
+                            *hi = s0 + wp[w1];
                         } else {
-                            for (long long q0 = qb; q0 < qe; q0 += 64 * RU) {
-                                gather(q0, jc, vc, ac);
-                                consume(jc, vc, ac);
+                            *lo = lower_bound_col(bcol, from, e0, c_lo);
+                            *hi = lower_bound_col(bcol, *lo, e0, c_hi);
+                        }
+                    };
+                    // the chunk of A entries from c0 on: its nonempty parts in the
+                    // slice; returns the products and their entries
+                    auto enter = [&](long long c0, int* nact) {
+                        long long lo = 0, hi = 0;
+                        VT a = (VT)0;
+                        const long long p = c0 + tid;
+                        if (p < a1) {
+                            if (one_chunk) {
+                                range(cur.s, cur.e, cur.bsl, my_cur, &lo, &hi);
+                                my_cur = hi;
+                                a = cur.a;
+                            } else {
+                                const int k = acol[p];
+                                a = aval[p];
+                                const long long s0 = brp[k];
+                                range(s0, brp[k + 1], bslot[k], s0, &lo, &hi);
+                            }
+                        }
+                        const int len = (int)(hi - lo);      // at most the slice's columns (2^21)
+                        const int incl = wave_scan(len);
+                        const uint64_t some = __ballot(len > 0);
+                        if (lane == 63) {
+                            s_sum[wv] = incl;
+                            s_some[wv] = __builtin_popcountll(some);
+                        }
+                        __syncthreads();
+                        uint32_t first = (uint32_t)(incl - len), total = 0;
+                        int idx = 0, all = 0;
+#pragma unroll
+                        for (int i = 0; i < NWV; ++i) {
+                            if (i == wv) {
+                                first += total;
+                                idx = all;
+                            }
+                            total += (uint32_t)s_sum[i];
+                            all += s_some[i];
+                        }
+                        if (len > 0) {
+                            idx = lanes_below(some, idx);
+                            s_off[idx] = first + (uint32_t)len;
+                            s_bst[idx] = lo - (long long)first;
+                            s_a[idx] = a;
+                        }
+                        __syncthreads();
+                        *nact = all;
+                        return total;
+                    };
+                    // Steps of one window of this wave's walk: columns, and with
+                    // VALS the values of B and A.  Lanes past the window's
+                    // products repeat its first one.
+                    int32_t jj[RU];
+                    VT vv[RU], aa[RU];
+                    auto gather = [&](const WaveWindow<RU>& win, int t0, int len, uint32_t q0, int nact, auto vals) {
+                        const long long at0 = s_bst[t0] + q0;
+#pragma unroll
+                        for (int g = 0; g < RU; g += 4)
+                            if (64 * g < len) {
+                                long long at[4];
+#pragma unroll
+                                for (int u = g; u < g + 4; ++u) {
+                                    const int e = min(win.entry(u), nact - 1);
+                                    at[u - g] = s_bst[e] + (q0 + (uint32_t)(64 * u + lane));
+                                    if constexpr (decltype(vals)::value) aa[u] = s_a[e];
+                                }
+#pragma unroll
+                                for (int u = g; u < g + 4; ++u) {
+                                    const long long bi = 64 * u + lane < len ? at[u - g] : at0;
+                                    jj[u] = bcol[bi];
+                                    if constexpr (decltype(vals)::value) vv[u] = bval[bi];
+                                }
+                            }
+                    };
+                    auto set_bits = [&](int len) {
+#pragma unroll
+                        for (int g = 0; g < RU; g += 4)
+                            if (64 * g < len)
+#pragma unroll
+                                for (int u = g; u < g + 4; ++u) {
+                                    const int jl = jj[u] - (int)c_lo;
+                                    atomicOr(reinterpret_cast<uint32_t*>(bm) + (jl >> 5), 1u << (jl & 31));
+                                }
+                    };
+                    auto add = [&](int len) {
+#pragma unroll
+                        for (int g = 0; g < RU; g += 4)
+                            if (64 * g < len) {
+                                unsigned long long word[4];
+                                int rk[4];
+#pragma unroll
+                                for (int u = g; u < g + 4; ++u) {
+                                    const int jl = jj[u] - (int)c_lo;
+                                    word[u - g] = bm[jl >> 6];
+                                    rk[u - g] = wr[jl >> 6];
+                                }
+#pragma unroll
+                                for (int u = g; u < g + 4; ++u) {
+                                    const int jl = jj[u] - (int)c_lo;
+                                    const int r = rk[u - g] + bits_below(word[u - g], jl & 63);
+                                    if (64 * u + lane < len)
+                                        atomicAdd(&acc[win_swz(r)], to_f64(aa[u]) * to_f64(vv[u]));
+                                }
+                            }
+                    };
+                    // the products of the chunk in LDS, contiguous runs per wave in
+                    // whole 64-lane steps: PASS 0 sets bitmap bits, PASS 1 adds a * b
+                    // at the column's rank
+                    auto products = [&](auto pass_tag, uint32_t total, int nact) {
+                        constexpr int PASS = decltype(pass_tag)::value;
+                        const uint32_t per = ((total + NWV - 1) / NWV + 63) & ~63u;
+                        const uint32_t qb = min((uint32_t)wv * per, total), qe = min(qb + per, total);
+                        if (qb < qe) {                       // wave-uniform
+                            WaveWindow<RU> win;
+                            win.next = owner_search(s_off, nact, (long long)qb);
+                            for (uint32_t q0 = qb; q0 < qe;) {
+                                const int t0 = win.next;
+                                const int len = win.open(s_off, nact, t0, q0, qe, s_mark[wv]);
+                                gather(win, t0, len, q0, nact, std::integral_constant<bool, PASS == 1>{});
+                                if constexpr (PASS == 0) set_bits(len);
+                                else add(len);
+                                q0 += (uint32_t)len;
                             }
                         }
                         __syncthreads();
+                    };
+                    // a one-chunk row's entries stay in LDS for both passes
+                    uint32_t total = 0;
+                    int nact = 0;
+                    if (one_chunk) {
+                        total = enter(a0, &nact);
+                        fetch(sl == 0 ? 2 : 3);
                     }
-                };
-                if (sbm && one_chunk) {
-                    // the bitmap came from the symbolic pass: the ranges the
-                    // accumulation pass reuses are all that is needed
-                    long long len = 0, bst = 0;
-                    double a = 0.0;
-                    if (a0 + tid < a1) {
-                        long long lo, hi;
-                        range(my_s, my_e, my_bsl, my_cur, &lo, &hi);
-                        my_cur = hi;
-                        a = to_f64(my_a);
-                        bst = lo;
-                        len = hi - lo;
+                    if (!sbm) {
+                        if (one_chunk) {
+                            products(std::integral_constant<int, 0>{}, total, nact);
+                        } else {
+                            for (long long c0 = a0; c0 < a1; c0 += BS) {
+                                total = enter(c0, &nact);
+                                products(std::integral_constant<int, 0>{}, total, nact);
+                            }
+                        }
+                    } else if (!one_chunk) {
+                        __syncthreads();                     // the stored bitmap is in LDS
                     }
-                    long long total;
-                    const long long incl = block_incl_scan<BS>(len, sm, &total);
-                    s_off[tid] = incl;
-                    s_bst[tid] = bst - (incl - len);
-                    s_a[tid] = a;
+                    // word ranks: thread tid takes E consecutive words (E odd: the
+                    // lanes' words lie in different banks)
+                    {
+                        const int E = ((nwd + BS - 1) / BS) | 1;
+                        const int i0 = min(tid * E, nwd), i1 = min(i0 + E, nwd);
+                        int loc = 0;
+                        for (int i = i0; i < i1; ++i) loc += __builtin_popcountll(bm[i]);
+                        int tw;
+                        int run = block_prefix(loc, &tw);
+                        for (int i = i0; i < i1; ++i) {
+                            wr[i] = (uint16_t)run;
+                            run += __builtin_popcountll(bm[i]);
+                        }
+                        if (tw != nout) bad = true;          // uniform
+                    }
+                    for (int i = tid; i < win_acc_len(nout); i += BS) acc[i] = 0.0;
                     __syncthreads();
-                } else if (!sbm) {
-                    products(std::integral_constant<int, 0>{});
-                }
-                // word ranks: thread tid takes E consecutive words
-                {
-                    const int E = (nwd + BS - 1) / BS;
-                    const int i0 = tid * E, i1 = min(i0 + E, nwd);
-                    int loc = 0;
-                    for (int i = i0; i < i1; ++i) loc += __builtin_popcountll(bm[i]);
-                    long long tw;
-                    long long run = block_incl_scan<BS>(loc, sm, &tw) - loc;
-                    for (int i = i0; i < i1; ++i) {
-                        wr[i] = (uint16_t)run;
-                        run += __builtin_popcountll(bm[i]);
+                    if (bad) break;
+                    fetch(3);
+                    if (one_chunk) {
+                        products(std::integral_constant<int, 1>{}, total, nact);
+                    } else {
+                        for (long long c0 = a0; c0 < a1; c0 += BS) {
+                            total = enter(c0, &nact);
+                            products(std::integral_constant<int, 1>{}, total, nact);
+                        }
                     }
-                    if (tw != nout) bad = true;         // uniform
-                }
-                for (int i = tid; i < win_acc_len(nout); i += BS) acc[i] = 0.0;
-                __syncthreads();
-                if (bad) break;
-                products(std::integral_constant<int, 1>{});
-                // columns in rank order (a thread per 32-bit half of a bitmap
-                // word: a dense word's bits take two lanes), then the slice out
-                // with coalesced stores
-                for (int i = tid; i < 2 * nwd; i += BS) {
-                    const unsigned long long word = bm[i >> 1];
-                    const int o = (i & 1) * 32;
-                    unsigned bits = (unsigned)(word >> o);
-                    int rk = (int)wr[i >> 1] + (o ? __builtin_popcount((unsigned)word) : 0);
-                    while (bits) {
-                        const int b = __builtin_ctz(bits);
-                        bits &= bits - 1u;
-                        colbuf[rk++] = (int32_t)(c_lo + (long long)i * 32 + b);
+                    // the sums out with coalesced stores; then the columns in rank
+                    // order (a thread per 32-bit half of a bitmap word: a dense
+                    // word's bits take two lanes) in the sums' place, and out
+                    const long long base = rp + s_rk[w0];
+                    for (int i = tid; i < nout; i += BS) cval[base + i] = (VT)acc[win_swz(i)];
+                    __syncthreads();
+                    if (nout < 2 * nwd) {
+                        for (int i = tid; i < nwd; i += BS) {
+                            unsigned long long word = bm[i];
+                            int rk = (int)wr[i];
+                            while (word) {
+                                const int b = __builtin_ctzll(word);
+                                word &= word - 1ull;
+                                colbuf[rk++] = (int)c_lo + i * 64 + b;
+                            }
+                        }
+                    } else
+                    for (int i = tid; i < 2 * nwd; i += BS) {
+                        const unsigned long long word = bm[i >> 1];
+                        const int o = (i & 1) * 32;
+                        unsigned bits = (unsigned)(word >> o);
+                        int rk = (int)wr[i >> 1] + (o ? __builtin_popcount((unsigned)word) : 0);
+                        while (bits) {
+                            const int b = __builtin_ctz(bits);
+                            bits &= bits - 1u;
+                            colbuf[rk++] = (int)c_lo + i * 32 + b;
+                        }
                     }
-                }
-                __syncthreads();
-                const long long base = rp + s_rk[w0];
-                for (int i = tid; i < nout; i += BS) {
-                    ccol[base + i] = colbuf[i];
-                    cval[base + i] = (VT)acc[win_swz(i)];
+                    __syncthreads();
+                    for (int i = tid; i < nout; i += BS) ccol[base + i] = colbuf[i];
                 }
             }
+            if (!more) break;
+            fetch(3);
+            slot = next;
+            cur = nxt;
         }
-        __syncthreads();                                // s_rec, s_rk and the LDS are reused by the next row
     }
     block_slots_done(q);
     if (bad && tid == 0) atomicOr(&info->err, kErrCount);

@@ -126,8 +126,8 @@ BinPlan numeric_plan(const msp_tuning& t, bool force_spill, bool rule) {
 // ---------------------------------------------------------------------------
 constexpr int kLdsReserve = 26 * 1024;     // static LDS of the symbolic bitmap kernel
 constexpr int kSliceReserve = 27 * 1024;   // static LDS of k_num_slice<kSliceBS>
-constexpr int kWinReserve = 30 * 1024;     // static LDS of k_num_win<kWinBS>
-constexpr int kWinPerCU = 1;               // workgroups of k_num_win per compute unit
+constexpr int kWinReserve = 16 * 1024;     // static LDS of k_num_win<kWinBS>
+constexpr int kWinPerCU = 2;               // workgroups of k_num_win per compute unit
 
 // Dynamic LDS of the windowed global-bin kernel (a share of the compute
 // unit's LDS for each of its workgroups), or 0 when a window of full
