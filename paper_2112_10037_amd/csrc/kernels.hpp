@@ -229,6 +229,45 @@ __device__ __forceinline__ int leading_run(uint64_t m) {
     return z ? __builtin_ctzll(z) : 64;
 }
 
+// Walk of a wave over consecutive products of a chunk of nonempty A entries:
+// off[t] is the number of the chunk's products up to and with entry t.  A
+// window takes up to 64 W products from q0 on: a bit for each entry that ends
+// in it goes into W mark words (this wave's LDS), and the entry of product
+// q0 + 64 s + lane is the window's first entry plus the marks below it (two
+// bit counts on a word that the wave shares).  No search, and the window's
+// products are independent of each other, so their loads are in flight
+// together.
+template <int W>
+struct WaveWindow {
+    int lo, hi, pre;            // lane s: word s of the marks, and the entries up to it
+    int next;                   // the next window's first entry
+
+    // the window from q0 < qe, whose product q0 belongs to entry t0; returns
+    // its products (it ends early after 64 entries)
+    __device__ __forceinline__ int open(const uint32_t* off, int nact, int t0, uint32_t q0, uint32_t qe,
+                                        unsigned long long* mark) {
+        const int lane = threadIdx.x & 63;
+        const int rel = t0 + lane < nact ? (int)min(off[t0 + lane] - q0, 64u * W + 1u) : 64 * W + 1;
+        int len = (int)min(qe - q0, 64u * W);
+        len = min(len, __builtin_amdgcn_readlane(rel, 63));   // (entries past these 64 stay for the next window)
+        if (lane < W) mark[lane] = 0ull;
+        lds_fence();
+        if (rel <= len) atomicOr(reinterpret_cast<uint32_t*>(mark) + ((rel - 1) >> 5), 1u << ((rel - 1) & 31));
+        lds_fence();
+        const unsigned long long w = lane < W ? mark[lane] : 0ull;
+        lo = (int)(uint32_t)w;
+        hi = (int)(uint32_t)(w >> 32);
+        const int c = __builtin_popcountll(w), incl = wave_scan(c);
+        pre = t0 + incl - c;
+        next = t0 + __builtin_amdgcn_readlane(incl, 63);
+        return len;
+    }
+    __device__ __forceinline__ int entry(int s) const {
+        return lanes_below((uint32_t)__builtin_amdgcn_readlane(lo, s), (uint32_t)__builtin_amdgcn_readlane(hi, s),
+                           __builtin_amdgcn_readlane(pre, s));
+    }
+};
+
 // XCD-aware block order: blocks are dealt round-robin to the 8 XCDs, so
 // block b runs on XCD b % 8.  Give XCD x the x-th contiguous eighth of the
 // logical blocks so that neighbouring rows (which share B rows) meet in the
@@ -778,8 +817,18 @@ struct GroupCfg {
     static constexpr int NG = BS / G;
 };
 
-// Symbolic for the largest rows: an n-bit bitmap (LDS when it fits, else a
-// per-workgroup global slab), counting bits that an atomic OR newly sets.
+// Symbolic for the largest rows: every product sets its column's bit in an
+// n-bit bitmap (LDS when it fits, else a per-workgroup global slab), and one
+// pass over the bitmap counts the bits, per window for the record.  The LDS
+// bitmap is whole windows long.
+//
+// Bound by the gathers of B's columns and, on rows of few products, by the
+// passes over the bitmap; two workgroups share a compute unit where two
+// bitmaps fit.  Measured on the rows past 16,384 products: R-MAT of 2^19
+// vertices 12.8 ms (a search-and-walk by every lane, ORs that return, one
+// workgroup) -> 9.9 ms, sparse power-law matrix of 2^20 rows 1.80 -> 1.11 ms.
+constexpr int kBitmapRU = 4;                   // 64-product steps per window of a wave's walk
+constexpr int kBitmapPart = 1 << 20;           // products of one A entry taken at a time (sums stay in 32 bits)
 template <int BS, bool LDSBM, bool BATCH = false>
 __global__ void __launch_bounds__(BS)
 k_sym_bitmap(Work wk, long long ncols,
@@ -787,105 +836,208 @@ k_sym_bitmap(Work wk, long long ncols,
              const int64_t* __restrict__ brp, const int32_t* __restrict__ bcol,
              int32_t* __restrict__ row_nnz, uint32_t* gslab, DevInfo* info, RowMap mp, WinRec rec,
              unsigned* q) {
+    constexpr int NWV = BS / 64, RU = kBitmapRU;
     int nrows_bin;
     const int32_t* perm;
     work_rows(wk, &nrows_bin, &perm);
-    __shared__ long long s_slot;
-    extern __shared__ uint32_t dyn_smem[];
+    extern __shared__ __align__(16) uint32_t dyn_smem[];
     __shared__ int s_wc[BATCH ? 1 : kWinMaxNw];
     __shared__ int s_rslot, s_bmslot;
-    __shared__ long long s_off[BS];
+    __shared__ uint32_t s_off[BS];              // nonempty A entries of a chunk, as in the windowed kernel
     __shared__ long long s_bst[BS];
-    __shared__ BlockScanSmem<BS> sm;
-    const int tid = threadIdx.x;
+    __shared__ unsigned long long s_mark[NWV][RU];
+    __shared__ int s_sum[NWV], s_some[NWV];
+    __shared__ long long s_slot;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const long long words = (ncols + 31) >> 5;
+    const long long padded = (words + kWin / 32 - 1) / (kWin / 32) * (kWin / 32);
     uint32_t* bm = LDSBM ? dyn_smem : gslab + (long long)blockIdx.x * words;
-    for (long long slot = block_first(q, &s_slot); slot < nrows_bin; slot = block_next(q, slot, &s_slot)) {
-        const int row = perm ? perm[slot] : (int)slot;
-        const long long bo = row_boff<BATCH>(mp, row);
-        for (long long w = tid; w < words; w += BS) bm[w] = 0u;
-        __syncthreads();
-        const long long a0 = arp[row], a1 = arp[row + 1];
-        long long cnt = 0, prod_row = 0;
-        for (long long c0 = a0; c0 < a1; c0 += BS) {
-            const long long p = c0 + tid;
-            long long len = 0, bst = 0;
-            if (p < a1) {
-                const long long k = acol[p] + bo;
-                bst = brp[k];
-                len = brp[k + 1] - bst;
+
+    // the next row's head, first entries and their B rows are loaded while a
+    // row is worked on
+    struct Row {
+        int row, k;
+        long long a0, a1, bo, s, e;
+    };
+    auto fetch_head = [&](Row& x, long long slot) {
+        x.row = __builtin_amdgcn_readfirstlane(perm ? perm[slot] : (int)slot);
+        x.a0 = arp[x.row];
+        x.a1 = arp[x.row + 1];
+        x.bo = row_boff<BATCH>(mp, x.row);
+    };
+    auto fetch_entry = [&](Row& x) {
+        x.k = 0;
+        if (x.a1 > x.a0) x.k = acol[x.a0 + tid < x.a1 ? x.a0 + tid : x.a1 - 1];
+    };
+    auto fetch_part = [&](Row& x) {
+        x.s = x.e = 0;
+        if (x.a1 > x.a0) {
+            x.s = brp[x.k + x.bo];
+            x.e = brp[x.k + x.bo + 1];
+        }
+    };
+    block_draw(q, (long long)blockIdx.x - gridDim.x, &s_slot);
+    __syncthreads();
+    long long slot = s_slot;
+    if (slot < nrows_bin) {                              // uniform
+        Row cur, nxt;
+        fetch_head(cur, slot);
+        fetch_entry(cur);
+        fetch_part(cur);
+        while (true) {
+            if constexpr (LDSBM) {
+                for (long long w = tid; w < padded / 4; w += BS)
+                    reinterpret_cast<uint4*>(bm)[w] = make_uint4(0, 0, 0, 0);
+            } else {
+                for (long long w = tid; w < words; w += BS) bm[w] = 0u;
             }
-            long long total;
-            const long long incl = block_incl_scan<BS>(len, sm, &total);
-            prod_row += total;
-            s_off[tid] = incl;
-            s_bst[tid] = bst - (incl - len);
             __syncthreads();
-            const int nact = (int)((a1 - c0) < BS ? (a1 - c0) : BS);
-            // owner of q: one search, then it moves forward, unless the next
-            // product lies more than eight average entries on
-            const bool far = total < (long long)nact * (BS / 8);
-            int t = -1;
-            // SU products per thread and round, their loads issued before any
-            // is used: one workgroup per compute unit leaves few waves to hide
-            // the gathers
-            constexpr int SU = 4;
-            for (long long q0 = tid; q0 < total; q0 += SU * BS) {
-                int32_t j[SU];
-#pragma unroll
-                for (int u = 0; u < SU; ++u) {
-                    const long long q = q0 + (long long)u * BS;
-                    j[u] = -1;
-                    if (q < total) {
-                        if (t < 0 || far) t = owner_search(s_off, nact, q);
-                        else while ((long long)s_off[t] <= q) ++t;
-                        j[u] = bcol[s_bst[t] + q];
+            block_draw(q, slot, &s_slot);
+            long long prod_row = 0, next = 0;
+            bool more = false, first_part = true;
+            for (long long c0 = cur.a0; c0 < cur.a1 || first_part; c0 += BS) {
+                long long s = 0, e = 0;
+                if (c0 + tid < cur.a1) {
+                    if (c0 == cur.a0) {
+                        s = cur.s;
+                        e = cur.e;
+                    } else {
+                        const long long k = acol[c0 + tid] + cur.bo;
+                        s = brp[k];
+                        e = brp[k + 1];
                     }
                 }
-#pragma unroll
-                for (int u = 0; u < SU; ++u) {
-                    if (j[u] < 0) continue;
-                    const uint32_t bit = 1u << (j[u] & 31);
-                    // the slab is this workgroup's own: workgroup scope suffices
-                    const uint32_t old = LDSBM ? atomicOr(&bm[j[u] >> 5], bit)
-                                               : __hip_atomic_fetch_or(&bm[j[u] >> 5], bit, __ATOMIC_RELAXED,
-                                                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-                    cnt += (old & bit) ? 0 : 1;
-                }
-            }
-            __syncthreads();
-        }
-        const long long tot = block_sum<BS>(cnt, sm);
-        if (tid == 0) row_nnz[row] = (int32_t)tot;
-        if constexpr (!BATCH) {
-            if (win_record_open((int*)rec.cnt, rec.nw, rec.thresh, rec.nrec, tot, s_wc, &s_rslot)) {
-                // a wave sums 64 consecutive words (half a window) with one atomic
-                const int lane = tid & 63;
-                for (long long w0 = (long long)(tid >> 6) * 64; w0 < words; w0 += BS) {
-                    const long long w = w0 + lane;
-                    int c = 0;
-                    if (w < words) c = __builtin_popcount(LDSBM ? bm[w] : load_coherent(bm + w));
-#pragma unroll
-                    for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d);
-                    if (lane == 0 && c) atomicAdd(&s_wc[(int)(w0 >> (kWinLog - 5))], c);
-                }
-                // the bitmap itself for a row with many products per column
-                int bm_slot = -1;
-                if (rec.bms && prod_row >= rec.bms_min_prod) {
-                    if (tid == 0) s_bmslot = atomicAdd(rec.nbms, 1);
+                bool again;
+                do {
+                    // the next products of every entry of the chunk
+                    const int len = (int)(e - s < kBitmapPart ? e - s : kBitmapPart);
+                    const int incl = wave_scan(len);
+                    const uint64_t some = __ballot(len > 0), rest = __ballot(e - s > kBitmapPart);
+                    if (lane == 63) {
+                        s_sum[wv] = incl;
+                        s_some[wv] = __builtin_popcountll(some) | (rest ? 1 << 16 : 0);
+                    }
                     __syncthreads();
-                    bm_slot = s_bmslot < rec.bms_cap ? s_bmslot : -1;
-                    if (bm_slot >= 0) {
-                        const long long sw = (long long)rec.nw * (kWin / 32);   // words of whole windows
-                        uint32_t* dst = rec.bms + (long long)bm_slot * sw;
-                        for (long long w = tid; w < sw; w += BS)
-                            dst[w] = w < words ? (LDSBM ? bm[w] : load_coherent(bm + w)) : 0u;
+                    if (first_part) {                    // the next row's head
+                        next = s_slot;
+                        more = next < nrows_bin;         // uniform
+                        fetch_head(nxt, more ? next : slot);
                     }
-                }
-                win_record_close(rec, row, s_wc, &s_rslot, bm_slot);
+                    uint32_t first = (uint32_t)(incl - len), total = 0;
+                    int idx = 0, nact = 0;
+                    again = false;
+#pragma unroll
+                    for (int i = 0; i < NWV; ++i) {
+                        if (i == wv) {
+                            first += total;
+                            idx = nact;
+                        }
+                        total += (uint32_t)s_sum[i];
+                        nact += s_some[i] & 0xffff;
+                        again = again || (s_some[i] >> 16);
+                    }
+                    prod_row += total;
+                    if (len > 0) {
+                        idx = lanes_below(some, idx);
+                        s_off[idx] = first + (uint32_t)len;
+                        s_bst[idx] = s - (long long)first;
+                        s += len;
+                    }
+                    __syncthreads();
+                    if (first_part) fetch_entry(nxt);
+                    const uint32_t per = ((total + NWV - 1) / NWV + 63) & ~63u;
+                    const uint32_t qb = min((uint32_t)wv * per, total), qe = min(qb + per, total);
+                    if (qb < qe) {                       // wave-uniform
+                        WaveWindow<RU> win;
+                        win.next = owner_search(s_off, nact, (long long)qb);
+                        for (uint32_t q0 = qb; q0 < qe;) {
+                            const int t0 = win.next;
+                            const int n = win.open(s_off, nact, t0, q0, qe, s_mark[wv]);
+                            // lanes past the window's products set its first one's bit again
+                            const long long at0 = s_bst[t0] + q0;
+                            int32_t j[RU];
+                            long long at[RU];
+#pragma unroll
+                            for (int u = 0; u < RU; ++u)
+                                at[u] = s_bst[min(win.entry(u), nact - 1)] + (q0 + (uint32_t)(64 * u + lane));
+#pragma unroll
+                            for (int u = 0; u < RU; ++u) j[u] = bcol[64 * u + lane < n ? at[u] : at0];
+#pragma unroll
+                            for (int u = 0; u < RU; ++u) {
+                                const uint32_t bit = 1u << (j[u] & 31);
+                                // the slab is this workgroup's own: workgroup scope suffices
+                                if constexpr (LDSBM) atomicOr(&bm[j[u] >> 5], bit);
+                                else __hip_atomic_fetch_or(&bm[j[u] >> 5], bit, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                            }
+                            q0 += (uint32_t)n;
+                        }
+                    }
+                    if (first_part) fetch_part(nxt);
+                    first_part = false;
+                    if constexpr (!LDSBM) __threadfence();   // the slab's bits are in before they are counted
+                    __syncthreads();
+                } while (again);
             }
+            // count: a half-wave takes a window, four words a lane
+            int cnt = 0;
+            for (long long w0 = (long long)wv * 256; w0 < padded; w0 += BS * 4) {
+                const long long w = w0 + lane * 4;
+                int c = 0;
+                if constexpr (LDSBM) {
+                    if (w < padded) {
+                        const uint4 x = *reinterpret_cast<const uint4*>(bm + w);
+                        c = __builtin_popcount(x.x) + __builtin_popcount(x.y) + __builtin_popcount(x.z) +
+                            __builtin_popcount(x.w);
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (w + i < words) c += __builtin_popcount(load_coherent(bm + w + i));
+                }
+                const int incl = wave_scan(c);
+                const int lower = __builtin_amdgcn_readlane(incl, 31), both = __builtin_amdgcn_readlane(incl, 63);
+                cnt += both;
+                if constexpr (!BATCH) {
+                    const long long win = w >> (kWinLog - 5);
+                    if (lane == 31 && win < kWinMaxNw) s_wc[win] = lower;
+                    if (lane == 63 && win < kWinMaxNw) s_wc[win] = both - lower;
+                }
+            }
+            if (lane == 0) s_sum[wv] = cnt;
+            __syncthreads();
+            int tot = 0;
+#pragma unroll
+            for (int i = 0; i < NWV; ++i) tot += s_sum[i];
+            if (tid == 0) row_nnz[cur.row] = tot;
+            if constexpr (!BATCH) {
+                if (rec.cnt && tot > rec.thresh) {       // uniform
+                    // the record, and the bitmap itself for a row with many products per column
+                    const bool store = rec.bms && prod_row >= rec.bms_min_prod;
+                    if (tid == 0) {
+                        s_rslot = atomicAdd(rec.nrec, 1);
+                        s_bmslot = store ? atomicAdd(rec.nbms, 1) : -1;
+                    }
+                    __syncthreads();
+                    const int bm_slot = store && s_bmslot < rec.bms_cap ? s_bmslot : -1;
+                    if (bm_slot >= 0) {
+                        uint32_t* dst = rec.bms + (long long)bm_slot * padded;
+                        if constexpr (LDSBM) {
+                            for (long long w = tid; w < padded / 4; w += BS)
+                                reinterpret_cast<uint4*>(dst)[w] = reinterpret_cast<const uint4*>(bm)[w];
+                        } else {
+                            for (long long w = tid; w < padded; w += BS)
+                                dst[w] = w < words ? load_coherent(bm + w) : 0u;
+                        }
+                    }
+                    win_record_close(rec, cur.row, s_wc, &s_rslot, bm_slot);
+                }
+            }
+            if (!more) break;
+            slot = next;
+            cur = nxt;
+            __syncthreads();                             // the next row writes what this one still reads
         }
-        __syncthreads();
     }
     block_slots_done(q);
     (void)info;
@@ -3083,45 +3235,6 @@ k_bwin_index(long long brows, const int64_t* __restrict__ brp, const int32_t* __
         }
     }
 }
-
-// Walk of a wave over consecutive products of a chunk of nonempty A entries:
-// off[t] is the number of the chunk's products up to and with entry t.  A
-// window takes up to 64 W products from q0 on: a bit for each entry that ends
-// in it goes into W mark words (this wave's LDS), and the entry of product
-// q0 + 64 s + lane is the window's first entry plus the marks below it (two
-// bit counts on a word that the wave shares).  No search, and the window's
-// products are independent of each other, so their loads are in flight
-// together.
-template <int W>
-struct WaveWindow {
-    int lo, hi, pre;            // lane s: word s of the marks, and the entries up to it
-    int next;                   // the next window's first entry
-
-    // the window from q0 < qe, whose product q0 belongs to entry t0; returns
-    // its products (it ends early after 64 entries)
-    __device__ __forceinline__ int open(const uint32_t* off, int nact, int t0, uint32_t q0, uint32_t qe,
-                                        unsigned long long* mark) {
-        const int lane = threadIdx.x & 63;
-        const int rel = t0 + lane < nact ? (int)min(off[t0 + lane] - q0, 64u * W + 1u) : 64 * W + 1;
-        int len = (int)min(qe - q0, 64u * W);
-        len = min(len, __builtin_amdgcn_readlane(rel, 63));   // (entries past these 64 stay for the next window)
-        if (lane < W) mark[lane] = 0ull;
-        lds_fence();
-        if (rel <= len) atomicOr(reinterpret_cast<uint32_t*>(mark) + ((rel - 1) >> 5), 1u << ((rel - 1) & 31));
-        lds_fence();
-        const unsigned long long w = lane < W ? mark[lane] : 0ull;
-        lo = (int)(uint32_t)w;
-        hi = (int)(uint32_t)(w >> 32);
-        const int c = __builtin_popcountll(w), incl = wave_scan(c);
-        pre = t0 + incl - c;
-        next = t0 + __builtin_amdgcn_readlane(incl, 63);
-        return len;
-    }
-    __device__ __forceinline__ int entry(int s) const {
-        return lanes_below((uint32_t)__builtin_amdgcn_readlane(lo, s), (uint32_t)__builtin_amdgcn_readlane(hi, s),
-                           __builtin_amdgcn_readlane(pre, s));
-    }
-};
 
 // Set bits of a word below bit b.
 __device__ __forceinline__ int bits_below(unsigned long long word, int b) {

@@ -124,7 +124,8 @@ BinPlan numeric_plan(const msp_tuning& t, bool force_spill, bool rule) {
 // ---------------------------------------------------------------------------
 // kernel tables
 // ---------------------------------------------------------------------------
-constexpr int kLdsReserve = 26 * 1024;     // static LDS of the symbolic bitmap kernel
+constexpr int kLdsReserve = 18 * 1024;     // static LDS of k_sym_bitmap<1024>
+constexpr int kLdsReserveHalf = 10 * 1024; // and of k_sym_bitmap<512>
 constexpr int kSliceReserve = 27 * 1024;   // static LDS of k_num_slice<kSliceBS>
 constexpr int kWinReserve = 16 * 1024;     // static LDS of k_num_win<kWinBS>
 constexpr int kWinPerCU = 2;               // workgroups of k_num_win per compute unit
@@ -211,7 +212,8 @@ int count_unsupported_plans(int verbose) {
 msp_status configure_kernels(msp_handle* h) {
     // allow the bitmap kernels the device's full LDS for their dynamic part
     const int dyn = std::max(0, h->lds_per_block - kLdsReserve);
-    void* fns[] = {(void*)k_sym_bitmap<1024, true, false>, (void*)k_sym_bitmap<1024, true, true>};
+    void* fns[] = {(void*)k_sym_bitmap<1024, true, false>, (void*)k_sym_bitmap<1024, true, true>,
+                   (void*)k_sym_bitmap<512, true, false>, (void*)k_sym_bitmap<512, true, true>};
     for (void* f : fns) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
         if (e != hipSuccess) {
@@ -286,6 +288,20 @@ static msp_status launch_check(const char* what) {
 // the bitmap kernel.
 static bool list_positions(const Operands& op) { return op.bnnz < (1LL << 32); }
 
+// LDS bytes of the symbolic bitmap (whole windows).
+static long long bitmap_bytes(long long ncols) {
+    return ((ncols + 31) / 32 + kWin / 32 - 1) / (kWin / 32) * (kWin / 32) * 4;
+}
+
+// Rows of a symbolic Block bin that take the lists: all but those past 8192
+// products when the bitmap fits the LDS (on an R-MAT graph of 2^19 vertices
+// its rows of 8193 to 16,384 products take 2968 us in the lists of 1024
+// threads, which fill the LDS of a compute unit, 1.3 ms in the bitmap).
+static bool takes_lists(const msp_handle* h, const BinSpec& s, const Operands& op) {
+    return list_positions(op) &&
+           (s.lanes * s.slots <= 8192 || bitmap_bytes(op.ncols) > h->lds_per_block - kLdsReserve);
+}
+
 // symbolic kernel of one bin over the rows of `wk`; `rows` (the row count,
 // or an estimate when wk reads it from the device) sizes persistent grids
 template <bool BATCH>
@@ -327,7 +343,7 @@ static msp_status launch_symbolic_t(msp_handle* h, const BinSpec& s, Work wk, in
     }
         MSP_SYM_ROW_SHAPES(X)
 #undef X
-    } else if (s.kind == Kind::Block && list_positions(op)) {
+    } else if (s.kind == Kind::Block && takes_lists(h, s, op)) {
         // rows past the lists go to the bounds array, which the symbolic pass
         // has read by then; launch_list_rest takes them
 #define X(BS, R)                                                                                           \
@@ -342,18 +358,24 @@ static msp_status launch_symbolic_t(msp_handle* h, const BinSpec& s, Work wk, in
     } else if (s.kind == Kind::Bitmap || s.kind == Kind::Block) {
         const long long n = op.ncols;
         const long long words = (n + 31) / 32;
-        const bool lds = words * 4 <= h->lds_per_block - kLdsReserve;
-        const int grid = std::min(rows, (lds ? 1 : 2) * h->num_cu);
+        // whole windows of LDS; two workgroups a compute unit while two bitmaps
+        // fit, so that one row's passes over its bitmap overlap the other's gathers
+        const long long lds_bytes = bitmap_bytes(n);
+        const bool lds = lds_bytes <= h->lds_per_block - kLdsReserve;
+        const bool half = lds_bytes <= h->lds_per_block / 2 - kLdsReserveHalf;
+        const int grid = std::min(rows, (lds && !half ? 1 : 2) * h->num_cu);
         uint32_t* slab = nullptr;
         if (!lds) {
             msp_status r = h->sbm.ensure((size_t)grid * words * 4);
             if (r != MSP_OK) return r;
             slab = h->sbm.as<uint32_t>();
         }
-        if (lds)
-            k_sym_bitmap<1024, true, BATCH><<<grid, 1024, words * 4, st>>>(wk, n, op.arp, op.acol, op.brp, op.bcol,
-                                                                           rnnz, slab, info, mp, rec,
-                                                                           rq);
+        if (half)
+            k_sym_bitmap<512, true, BATCH><<<grid, 512, lds_bytes, st>>>(wk, n, op.arp, op.acol, op.brp, op.bcol, rnnz,
+                                                                         slab, info, mp, rec, rq);
+        else if (lds)
+            k_sym_bitmap<1024, true, BATCH><<<grid, 1024, lds_bytes, st>>>(wk, n, op.arp, op.acol, op.brp, op.bcol,
+                                                                           rnnz, slab, info, mp, rec, rq);
         else
             k_sym_bitmap<1024, false, BATCH><<<grid, 1024, 0, st>>>(wk, n, op.arp, op.acol, op.brp, op.bcol, rnnz,
                                                                     slab, info, mp, rec, rq);
