@@ -1391,12 +1391,13 @@ constexpr int kScanTile = kScanBS * kScanPer;
 // product count, and when the bound u = min(products, ncols) falls in the
 // merge bin (0 < u <= umax) they are the merge's heads, so the row's
 // distinct columns are counted right away.  Rows with more A entries sum
-// their B-row lengths with the whole wave and, in the merge bin, take the
-// hash fallback.  Every row's bound and bin count are recorded as the
+// their B-row lengths with eight lanes or the workgroup and, in the merge
+// bin, take the hash fallback.  Every row's bound and bin count are recorded as the
 // statistics pass records them; rows of the other bins are left for their
 // own kernels.
+constexpr int kFusedWide = 512;                    // A entries past which a workgroup sums the row
 template <int K, typename IT, bool BATCH = false>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 8)
 k_sym_fused(int m, long long ncols, const int64_t* __restrict__ arp, const int32_t* __restrict__ acol,
             const int64_t* __restrict__ brp, const int32_t* __restrict__ bcol, int32_t* __restrict__ u_out,
             int32_t* __restrict__ row_nnz, BinTable bins, int umax, DevInfo* info, BinTable nbins,
@@ -1407,9 +1408,12 @@ k_sym_fused(int m, long long ncols, const int64_t* __restrict__ arp, const int32
     __shared__ int s_unknown;
     __shared__ int s_na;
     __shared__ int32_t fb_keys[4][kMergeFT + 1];
+    __shared__ unsigned char s_row[4][64];
+    __shared__ int s_nwide, s_wide[256];
+    __shared__ long long s_w0, s_w1, s_wbo;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (threadIdx.x < kNB) { hist[threadIdx.x] = 0; nhist[threadIdx.x] = 0; }
-    if (threadIdx.x == 0) { s_unknown = 0; s_na = 0; }
+    if (threadIdx.x == 0) { s_unknown = 0; s_na = 0; s_nwide = 0; }
     __syncthreads();
     const long long r0 = ((long long)blockIdx.x * 4 + w) * 64;
     const long long row = r0 + lane;
@@ -1426,20 +1430,69 @@ k_sym_fused(int m, long long ncols, const int64_t* __restrict__ arp, const int32
     }
     const bool shortrow = valid && a1 - a0 <= K;
     long long prod = 0;
-    // rows with more than K A entries: the wave sums their B-row lengths
-    uint64_t lr = __ballot(valid && !shortrow);
-    while (lr) {                                       // wave-uniform
-        const int r = __builtin_ctzll(lr);
-        lr &= lr - 1;
-        const long long la0 = __shfl(a0, r), la1 = __shfl(a1, r), lbo = __shfl(bo, r);
+    // Rows with more than K A entries sum their B-row lengths, eight rows at a
+    // time with eight lanes each and four entries a lane in flight; rows past
+    // kFusedWide entries one after the other with the workgroup, four entries
+    // a thread in flight (all rows of a workgroup's tile wait for its longest).
+    // The pass is bound by these dependent gathers.  One row at a time, one
+    // entry a lane, it took 70 us on 260,000 rows of 16 entries, 78 on 300,000
+    // rows of 27 and 1602 on an R-MAT graph of 2^19 vertices; so it takes 32,
+    // 32 and 940 (1092 with the long rows on one wave).  More in flight costs
+    // registers and with them waves: eight a lane, 92 registers, slowed a
+    // million rows of 5 entries from 37 us to 45.
+    const bool wide = valid && a1 - a0 > kFusedWide;
+    const bool some = valid && !shortrow && !wide;
+    const uint64_t sm = __ballot(some);
+    if (sm) {                                          // wave-uniform
+        const int mine = __builtin_popcountll(sm & ((1ull << lane) - 1ull));
+        if (some) s_row[w][mine] = (unsigned char)lane;
+        lds_fence();
+        const int ns = __builtin_popcountll(sm);
+        for (int i0 = 0; i0 < ns; i0 += 8) {
+            const int i = i0 + (lane >> 3);
+            const int r = s_row[w][i < ns ? i : i0];
+            const long long la0 = __shfl(a0, r), la1 = __shfl(a1, r), lbo = __shfl(bo, r);
+            long long s = 0;
+            for (long long p = la0 + (lane & 7); p < la1; p += 32) {
+                IT kk[4], l[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    kk[u] = (IT)(gat(acol, (IT)(p + 8 * u < la1 ? p + 8 * u : la1 - 1)) + lbo);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) l[u] = (IT)(gat(brp, (IT)(kk[u] + 1)) - gat(brp, kk[u]));
+#pragma unroll
+                for (int u = 0; u < 4; ++u) s += p + 8 * u < la1 ? (long long)l[u] : 0;
+            }
+#pragma unroll
+            for (int d = 4; d > 0; d >>= 1) s += __shfl_xor(s, d);
+            const long long got = __shfl(s, (mine & 7) * 8);
+            if (some && mine >= i0 && mine < i0 + 8) prod = got;
+        }
+    }
+    if (wide) s_wide[atomicAdd(&s_nwide, 1)] = threadIdx.x;
+    __syncthreads();
+    for (int i = 0; i < s_nwide; ++i) {                // uniform
+        const int o = s_wide[i];
+        if (threadIdx.x == o) { s_w0 = a0; s_w1 = a1; s_wbo = bo; }
+        __syncthreads();
+        const long long la0 = s_w0, la1 = s_w1, lbo = s_wbo;
         long long s = 0;
-        for (long long p = la0 + lane; p < la1; p += 64) {
-            const long long kk = acol[p] + lbo;
-            s += brp[kk + 1] - brp[kk];
+        for (long long p = la0 + threadIdx.x; p < la1; p += 1024) {
+            IT kk[4], l[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                kk[u] = (IT)(gat(acol, (IT)(p + 256 * u < la1 ? p + 256 * u : la1 - 1)) + lbo);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) l[u] = (IT)(gat(brp, (IT)(kk[u] + 1)) - gat(brp, kk[u]));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s += p + 256 * u < la1 ? (long long)l[u] : 0;
         }
 #pragma unroll
         for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d);
-        if (lane == r) prod = s;
+        if (lane == 0) s_sum[w] = s;
+        __syncthreads();
+        if (threadIdx.x == o) prod = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+        __syncthreads();
     }
     // short rows: B-row bounds, which are also the merge's heads; IT is
     // 32-bit when the byte offsets into acol, brp and bcol fit 32 bits

@@ -200,3 +200,17 @@ def test_list_kernel_edges(h, name):
     nnz = h.symbolic(binding.DeviceCSR.from_host(A), binding.DeviceCSR.from_host(B))
     import oracle
     assert np.array_equal(nnz[0].cpu().numpy(), oracle.row_nnz(A, B))
+
+
+@pytest.mark.parametrize("wide", [1, 300])
+def test_fused_sums_of_long_rows(h, wide):
+    """The statistics pass's three sums: rows around 4 and 8 A entries (heads),
+    around 32 and 512 (eight lanes), and from 513 on (the workgroup), in tiles
+    of 256 rows with one or with every row long; last tile partly filled."""
+    rng = np.random.default_rng(wide)
+    k = rng.choice([0, 3, 4, 5, 8, 9, 31, 32, 33, 64, 65], size=900)
+    k[rng.permutation(900)[:6]] = [511, 512, 513, 1024, 1025, 4000]
+    k[256: 256 + wide] = 513 + rng.integers(0, 1100, size=wide)
+    A = gen.erdos_renyi(900, 6_000, k, seed=9)
+    B = gen.erdos_renyi(6_000, 40_000, rng.choice([0, 0, 0, 1, 1, 2, 7], size=6_000), seed=10)
+    check_full(h, A, B)
