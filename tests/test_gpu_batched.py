@@ -285,3 +285,25 @@ def test_work_queue_rows_validation(h):
     got = plan.result(1).to_host()
     assert np.array_equal(got.col, ref[1]) and np.array_equal(got.val, ref[2])
     plan.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_results_copied_from_any_offset(h, dtype):
+    """Copies whose arrays start at every word of a 16-byte line and end in
+    every remainder of four words, the smallest ones, one of more words than
+    a launch of the full grid takes at once, and an empty result."""
+    rng = np.random.default_rng(21)
+    sizes = [1, 1, 2, 3, 5, 1, 4, 7, 6, 0, 9, 1200, 3, 2048]
+    A, B = [], []
+    for i, n in enumerate(sizes):
+        B.append(gen.erdos_renyi(max(n, 1), 4000, rng.integers(0, 4, size=max(n, 1)), seed=30 + i, dtype=dtype))
+        A.append(gen.erdos_renyi(max(n, 1), max(n, 1), 1 if n else 0, seed=60 + i, dtype=dtype))
+    n = 400_000
+    rp = np.arange(n + 1, dtype=np.int64)
+    A.append(gen.CSR(n, n, rp, np.arange(n, dtype=np.int32), np.ones(n, dtype)))
+    B.append(gen.erdos_renyi(n, 50_000, 7, seed=99, dtype=dtype))
+    plan = binding.Batch(h, binding.PackedBatch.from_host(A), binding.PackedBatch.from_host(B))
+    plan.execute()
+    for p in range(len(A)):
+        _check(plan.result(p), oracle.spgemm(A[p], B[p]), dtype)
+    plan.close()
