@@ -313,9 +313,8 @@ static msp_status run_stage(msp_batch* b, int si, bool eager) {
             MSP_OK)
             return s;
     if (S.sym_scatter) {
-        k_zero_words<<<1, 256, 0, st>>>(&info->cursor[0][0], kParts * kPartStride);
         k_scatter<<<(M + 255) / 256, 256, 0, st>>>(M, h->u.as<int32_t>(), S.sp.table, &info->sym_part[0][0], 256,
-                                                   &info->cursor[0][0], h->perm.as<int32_t>());
+                                                   &info->cursor[0][0][0], h->perm.as<int32_t>());
         if ((s = launch_ok("k_scatter")) != MSP_OK) return s;
         int listed = 0;
         for (int bn = 1; bn <= S.sp.table.nb; ++bn) {
@@ -388,9 +387,8 @@ static msp_status run_stage(msp_batch* b, int si, bool eager) {
                                           S.op, S.crp.as<int64_t>(), ccol, cval, nullptr, S.mp)) != MSP_OK)
             return s;
     } else if (S.num_planned) {
-        k_zero_words<<<1, 256, 0, st>>>(&info->cursor[0][0], kParts * kPartStride);
         k_scatter<<<(M + 255) / 256, 256, 0, st>>>(M, h->rnnz.as<int32_t>(), S.np.table, &info->num_part[0][0],
-                                                   kScanTile, &info->cursor[0][0], h->perm.as<int32_t>());
+                                                   kScanTile, &info->cursor[1][0][0], h->perm.as<int32_t>());
         if ((s = launch_ok("k_scatter")) != MSP_OK) return s;
         int sorted = 0;
         for (int bn = 1; bn <= S.np.table.nb; ++bn) {

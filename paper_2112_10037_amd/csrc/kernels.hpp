@@ -326,7 +326,7 @@ static __global__ void k_zero_words(int* p, int n) {
 // Clear the device info block of a new call; the error bits the previous
 // call's numeric kernels left there go to the host's pending word first
 // (pending may be null).  One workgroup.
-static __global__ void __launch_bounds__(256) k_zero_info(int* p, int n, int* pending) {
+static __global__ void __launch_bounds__(1024) k_zero_info(int* p, int n, int* pending) {
     if (threadIdx.x == 0 && pending) {
         // only the numeric kernels' bits: input-check bits were reported by
         // the call that set them
@@ -334,7 +334,7 @@ static __global__ void __launch_bounds__(256) k_zero_info(int* p, int n, int* pe
         if (e) __hip_atomic_store(pending, e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < n; i += 256) p[i] = 0;
+    for (int i = threadIdx.x; i < n; i += 1024) p[i] = 0;
 }
 
 // ===========================================================================
@@ -359,23 +359,6 @@ __device__ __forceinline__ int wave_hist_add(int* hist, int b) {
         todo &= ~same;
     }
     return rank;
-}
-
-// As wave_hist_add with a weight per lane (lanes with b < 0 add nothing).
-// Wave-uniform control flow required.
-__device__ __forceinline__ void wave_hist_add_w(int* hist, int b, int w) {
-    const int lane = threadIdx.x & 63;
-    uint64_t todo = __ballot(b >= 0);
-    while (todo) {
-        const int leader = __builtin_ctzll(todo);
-        const int bl = __shfl(b, leader);
-        const uint64_t same = __ballot(b == bl);
-        int x = b == bl ? w : 0;
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d);
-        if (lane == leader) atomicAdd(&hist[bl], x);
-        todo &= ~same;
-    }
 }
 
 // One wave per 64 consecutive rows.  The wave walks the A entries of its
@@ -1671,7 +1654,12 @@ k_scan_fused(int m, const int32_t* __restrict__ cnt, const long long* __restrict
     }
     if (other) {
         // one flag raised by the fused pass's workgroups that left rows for
-        // other bins; workgroup 0 sums the symbolic bin sizes for the host
+        // other bins; workgroup 0 sums the symbolic bin sizes for the host and
+        // clears the numeric ones, which the full scan counts afresh
+        if (hs && tile == 0) {
+            static_assert(kParts * kPartStride == 2 * kWsBS, "two counters a thread");
+            reinterpret_cast<int2*>(&info->num_part[0][0])[threadIdx.x] = make_int2(0, 0);
+        }
         if (hs && tile == 0 && threadIdx.x < 64) {
             const int t = threadIdx.x;
             int c = 0;
@@ -2334,23 +2322,29 @@ k_scan_lookback(int m, const int32_t* __restrict__ cnt, unsigned long long* tile
     }
     // the tile's numeric bin histogram (before the tile publishes its state)
     if (bins.nb > 0) {
-        // a thread's rows usually share one bin: one weighted add then
-        const int b0 = base < m ? bin_of(bins, v[0]) : -1;
-        int nv = 0;
-        bool same = true;
+        // A thread counts its rows in four bits a bin; the wave's count of a
+        // bin is then four ballots, with no LDS round trip a bin and row.
+        // (A loop over the distinct bins of each eighth of the tile: 17.3 us
+        // on 300,000 27-point rows, so 14.3.)
+        static_assert(kScanPer < 16 && kNB <= 32, "four bits a bin, two words");
+        unsigned long long p0 = 0, p1 = 0;
 #pragma unroll
         for (int i = 0; i < kScanPer; ++i)
             if (base + i < m) {
-                ++nv;
-                same = same && bin_of(bins, v[i]) == b0;
+                const int b = bin_of(bins, v[i]);
+                const unsigned long long one = 1ull << (4 * (b & 15));
+                if (b < 16) p0 += one;
+                else p1 += one;
             }
-        if (__ballot(!same) == 0) {
-            wave_hist_add_w(hist, b0, nv);
-        } else {
+        int mine = 0;
+        for (int b = 0; b <= bins.nb; ++b) {             // uniform
+            const int c = (int)((b < 16 ? p0 : p1) >> (4 * (b & 15))) & 15;
+            int n = 0;
 #pragma unroll
-            for (int i = 0; i < kScanPer; ++i)
-                wave_hist_add(hist, base + i < m ? bin_of(bins, v[i]) : -1);
+            for (int j = 0; j < 4; ++j) n += __builtin_popcountll(__ballot((c >> j) & 1)) << j;
+            if ((int)(threadIdx.x & 63) == b) mine = n;
         }
+        if (mine) atomicAdd(&hist[threadIdx.x & 63], mine);
     }
     long long tot;
     const long long incl = block_incl_scan<kScanBS>(s, sm, &tot);   // (its barriers complete hist, s_neg)

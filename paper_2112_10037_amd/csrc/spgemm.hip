@@ -635,7 +635,7 @@ static msp_status launch_numeric(msp_handle* h, const BinSpec& s, int rows, cons
 // ---------------------------------------------------------------------------
 msp_status zero_info(msp_handle* h) {
     const int words = (int)(sizeof(DevInfo) / 4);
-    k_zero_info<<<1, 256, 0, h->stream>>>((int*)h->info.ptr, words, h->dpending);
+    k_zero_info<<<1, 1024, 0, h->stream>>>((int*)h->info.ptr, words, h->dpending);
     return launch_check("k_zero_info");
 }
 
@@ -811,9 +811,7 @@ static msp_status run_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, co
     msp_status s = h->perm.ensure((size_t)m * 4);
     if (s != MSP_OK) return s;
     int32_t* perm = h->perm.as<int32_t>();
-    int* cursor = &info->cursor[0][0];
-    k_zero_words<<<1, 256, 0, h->stream>>>(cursor, kParts * kPartStride);
-    if ((s = launch_check("k_zero_words")) != MSP_OK) return s;
+    int* cursor = &info->cursor[numeric ? 1 : 0][0][0];
     k_scatter<<<(m + 255) / 256, 256, 0, h->stream>>>(
         m, key, plan.table, numeric ? &info->num_part[0][0] : &info->sym_part[0][0],
         numeric ? kScanTile : 256, cursor, perm);
@@ -1053,12 +1051,9 @@ static msp_status symbolic_phase(msp_handle* h, const msp_csr* A, const msp_csr*
             *scanned = true;
             return MSP_OK;
         }
-        // other symbolic bins have rows: run them (the merge bin is done);
-        // the full scan counts the numeric bins afresh
+        // other symbolic bins have rows: run them (the merge bin is done)
         int counts[kNB];
         for (int b = 0; b < kNB; ++b) counts[b] = h->hsum->counts[b];
-        k_zero_words<<<1, 256, 0, h->stream>>>(&info->num_part[0][0], kParts * kPartStride);
-        if ((s = launch_check("k_zero_words")) != MSP_OK) return s;
         if ((s = setup_records(h, A, B, sp, counts, np)) != MSP_OK) return s;
         h->prof.begin(MSP_PHASE_SYMBOLIC, h->stream);
         s = run_symbolic_bins(h, A, B, sp, counts, h->rnnz.as<int32_t>(), 1);

@@ -88,7 +88,9 @@ struct DevInfo {
     unsigned queue[2][kNB + 1][2];
     int sym_part[kParts][kPartStride];    // rows per symbolic bin, per partition
     int num_part[kParts][kPartStride];    // rows per numeric bin, per partition
-    int cursor[kParts][kPartStride];      // scatter cursors
+    // scatter cursors per phase (symbolic, numeric): each phase scatters at
+    // most once between two clearings of this block
+    int cursor[2][kParts][kPartStride];
     long long ssum[kSupers];              // rows' counts per super-tile of the fused symbolic pass
 };
 
