@@ -11,6 +11,8 @@
 #include <unordered_map>
 #include <vector>
 
+#include <climits>
+
 #include "internal.hpp"
 #include "kernels.hpp"
 #include "msp.h"
@@ -45,7 +47,8 @@ static void add_bin(BinPlan& p, int umax, BinSpec s) {
 // Small bins.  From 33 outputs a row takes a whole wave: one step of 64 lanes
 // holds a row of 64 products.  (In batches of eight rows a wave, 4096 rows of
 // 64 products took 16.3 us in the symbolic pass and 13.7 us in the numeric one
-// as lane groups of 32; a wave each 4.6 and 10.3 us.)  Shorter rows, when the
+// as lane groups of 32; a wave each 4.6 and 10.3 us.  Many rows of at most 64
+// outputs go back to batches and groups at launch: kManyRows.)  Shorter rows, when the
 // merge is off: wave-local row batches (k_sym_wave, k_num_wave) of at most R
 // rows with T key slots, lane groups (k_num_group) for larger tables.
 static int sym_batch_rows(int T) { return T <= 64 ? 16 : 1024 / T; }
@@ -142,7 +145,19 @@ static int win_lds(const msp_handle* h) {
 #define MSP_NUM_GROUP_SHAPES(X) X(16, 128) X(32, 128)
 #define MSP_NUM_ROW_SHAPES(X) X(128) X(256) X(512) X(1024)
 #define MSP_SYM_ROW_SHAPES(X) MSP_NUM_ROW_SHAPES(X) X(2048)
-#define MSP_SYM_BATCH_SHAPES(X) X(32, 16) X(64, 16) X(128, 8)
+#define MSP_SYM_BATCH_SHAPES(X) X(32, 16) X(64, 16) X(128, 8) X(256, 4)
+// From so many rows the shortest whole-wave bin (128 slots) goes to several
+// rows a wave instead: 200,000 rows of 36 to 56 products take a call of 458 us
+// with a wave a row and 246 with lane groups and batches, 4096 rows of 64
+// products 55 and 84 (few rows are bound by the latency of one, many by the
+// lanes that a short row leaves idle).
+constexpr int kManyRows = 16384;
+static bool symbolic_in_batches(const BinSpec& s, int rows, long long ncols) {
+    // Rows of 256 slots, too, when B's columns are so few that most rows have
+    // more products than the wave's registers take: 800,000 rows of 200
+    // products over 90 columns 935 us a row each, 373 in batches.
+    return s.kind == Kind::Group && ((s.slots == 128 && rows >= kManyRows) || (s.slots <= 256 && ncols <= s.slots / 2));
+}
 #define MSP_NUM_BATCH_SHAPES(X) X(32, 12) X(32, 8) X(32, 4) X(64, 8) X(64, 4) X(64, 2)
 #define MSP_SYM_LIST_SHAPES(X) X(256, 8) X(512, 16) X(1024, 16)
 // workgroup threads of the numeric counting sort; every size takes kSortR
@@ -324,9 +339,9 @@ static msp_status launch_symbolic_t(msp_handle* h, const BinSpec& s, Work wk, in
             k_sym_merge<8, BATCH><<<grid, 256, 0, st>>>(wk, op.arp, op.acol, op.brp, op.bcol, ufilter, umax, rnnz,
                                                         info, mp);
         return launch_check("k_sym_merge");
-    } else if (s.kind == Kind::Batch) {
+    } else if (s.kind == Kind::Batch || symbolic_in_batches(s, rows, BATCH ? LLONG_MAX : (long long)op.ncols)) {
 #define X(T, R)                                                                                        \
-    if (s.slots == T && s.lanes == R) {                                                                \
+    if (s.slots == T && (s.lanes == R || s.kind == Kind::Group)) {                                     \
         const int grid = group_grid(h, (const void*)k_sym_wave<T, R, BATCH>, rows, 4 * R);            \
         k_sym_wave<T, R, BATCH><<<grid, 256, 0, st>>>(wk, op.arp, op.acol, op.brp, op.bcol, rnnz, info, mp); \
         return launch_check("k_sym_wave");                                                            \
@@ -463,8 +478,9 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
         MSP_NUM_BATCH_SHAPES(X)
 #undef X
     } else if (s.kind == Kind::Group) {
+        const int lanes = s.lanes == 64 && s.slots == 128 && rows >= kManyRows ? 32 : s.lanes;
 #define X(G, T)                                                                                            \
-    if (s.lanes == G && s.slots == T) {                                                                    \
+    if (lanes == G && s.slots == T) {                                                                      \
         const int grid = group_grid(h, (const void*)k_num_group<G, T, VT, BATCH>, rows, 256 / G);         \
         k_num_group<G, T, VT, BATCH><<<grid, 256, 0, st>>>(wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, \
                                                            ccol, cval, cnt_out, info, mp);                \

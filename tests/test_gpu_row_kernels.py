@@ -214,3 +214,33 @@ def test_fused_sums_of_long_rows(h, wide):
     A = gen.erdos_renyi(900, 6_000, k, seed=9)
     B = gen.erdos_renyi(6_000, 40_000, rng.choice([0, 0, 0, 1, 1, 2, 7], size=6_000), seed=10)
     check_full(h, A, B)
+
+
+@pytest.mark.parametrize("ncols", [33, 64, 65, 128, 511, 1000, 1024, 43_008, 43_009, 900_000])
+def test_symbolic_rows_past_the_registers(h, ncols):
+    """More products than a row's columns allow in registers, or more A entries
+    than lanes: windows of 1024 products entered, filled and passed, B rows
+    that are empty, short or as long as B is wide, the bitmap's last column and
+    the first width without it."""
+    rng = np.random.default_rng(ncols)
+    kb = rng.choice([0, 1, 2, 9, 30, min(ncols, 900)], size=600, p=[0.2, 0.3, 0.2, 0.2, 0.08, 0.02])
+    B = gen.erdos_renyi(600, ncols, np.minimum(kb, ncols), seed=41)
+    B.col[B.row_ptr[1:][np.diff(B.row_ptr) > 0] - 1] = ncols - 1
+    ka = rng.choice([1, 7, 20, 63, 64, 65, 90, 128, 129, 300], size=700)
+    A = gen.erdos_renyi(700, 600, ka, seed=42)
+    check_full(h, A, B)
+    check_full(h, A, B, tuning=(1, 0, 4096, 1024, 8))
+
+
+@pytest.mark.parametrize("rows", [16_383, 16_384, 17_001])
+@pytest.mark.parametrize("ncols", [64, 65, 128, 129, 60_000])
+def test_many_short_rows(h, ncols, rows):
+    """Both sides of the row count from which the shortest whole-wave bin takes
+    several rows a wave, and of the column counts below which the symbolic pass
+    does; every row has 33 to 64 outputs, or more where B is wide enough."""
+    rng = np.random.default_rng(rows)
+    A = gen.erdos_renyi(rows, 700, rng.choice([6, 7], size=rows), seed=51)
+    B = gen.erdos_renyi(700, ncols, 8, seed=52)
+    check_full(h, A, B)
+    A = gen.erdos_renyi(rows, 700, rng.choice([8, 30], size=rows), seed=53)
+    check_full(h, A, B)
