@@ -155,7 +155,7 @@ constexpr int kManyRows = 16384;
 static bool symbolic_in_batches(const BinSpec& s, int rows, long long ncols) {
     // Rows of 256 slots, too, when B's columns are so few that most rows have
     // more products than the wave's registers take: 800,000 rows of 200
-    // products over 90 columns 935 us a row each, 373 in batches.
+    // products over 90 columns 935 us with a wave a row, 373 in batches.
     return s.kind == Kind::Group && ((s.slots == 128 && rows >= kManyRows) || (s.slots <= 256 && ncols <= s.slots / 2));
 }
 #define MSP_NUM_BATCH_SHAPES(X) X(32, 12) X(32, 8) X(32, 4) X(64, 8) X(64, 4) X(64, 2)
