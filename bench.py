@@ -57,7 +57,7 @@ MEASURED_TRAFFIC = {
     ("rmat20", (1, 0, 2048, 1024, 8)): {"bytes": 350098073402, "sources_sha256": "1263d4858f1712fb7087ae5c807c546148ab4ccaa21c36e4e030f20db324f3f7"},
     ("rmat20", (1, 0, 1024, 1024, 8)): {"bytes": 350993861306, "sources_sha256": "a58847084f2b78983284bafdec280f84aaae1b56ae666730da3cc90a43e7295a"},
 }
-KERNEL_SOURCES = ["kernels.hpp", "wave_rows.hpp", "block_rows.hpp", "types.hpp", "spgemm.hip", "msp_api.hip", "internal.hpp"]
+KERNEL_SOURCES = ["kernels.hpp", "wave_rows.hpp", "block_rows.hpp", "list_walk.hpp", "types.hpp", "spgemm.hip", "msp_api.hip", "internal.hpp"]
 
 
 def _code_only(text: str) -> str:

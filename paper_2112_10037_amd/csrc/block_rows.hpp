@@ -2,6 +2,8 @@
 // products in registers (R a thread) while they are ordered in LDS.
 #pragma once
 
+#include "list_walk.hpp"
+
 namespace msp {
 
 // Numeric, one workgroup per row of at most BS R products and fewer than 3/4 as
@@ -536,26 +538,16 @@ k_sym_list(Work wk,
                 for (int g = 0; g < R; g += 4) {
                     // four products a lane at once, back through the lists
                     int live = 0;
+                    uint32_t four = 0;
 #pragma unroll
                     for (int s = g; s < g + 4; ++s) {
-                        own |= (uint32_t)((s * NW + wv) * 64 + lane < total) << s;
+                        four |= (uint32_t)((s * NW + wv) * 64 + lane < total) << (s - g);
                         live |= (prev[s] >= 0) << (s - g);
                     }
-                    while (__ballot(live != 0)) {
-                        int x[4], y[4];
-#pragma unroll
-                        for (int s = g; s < g + 4; ++s) {
-                            x[s - g] = lc[max(prev[s], 0)];
-                            y[s - g] = lp[max(prev[s], 0)];
-                        }
-#pragma unroll
-                        for (int s = g; s < g + 4; ++s) {
-                            const bool on = (live >> (s - g)) & 1, same = x[s - g] == c[s];
-                            if (on && same) own &= ~(1u << s);
-                            if (on && (same || y[s - g] == 0xffff)) live &= ~(1 << (s - g));
-                            if (on) prev[s] = y[s - g];
-                        }
-                    }
+                    while (__ballot(live != 0))
+                        list_step<4>(c + g, prev + g, live, four, [&](int m) { return lc[m]; },
+                                     [&](int m) { return (int)lp[m]; });
+                    own |= four << g;
                 }
                 const int cnt = __builtin_amdgcn_readlane(wave_scan(__builtin_popcount(own)), 63);
                 if (lane == 0) s_cnt[wv] = cnt;
