@@ -93,9 +93,7 @@ k_num_sort(Work wk,
         *b1 = brp[k + h.bo + 1];
     };
 
-    block_draw(q, (long long)blockIdx.x - gridDim.x, &s_slot);
-    __syncthreads();
-    long long slot = s_slot;
+    long long slot = block_open(q, &s_slot);
     if (slot < nrows_bin) {                                // uniform
         Head cur = head_of(slot);
         int k = 0, kn = 0;
@@ -434,9 +432,7 @@ k_sym_list(Work wk,
         *b1 = brp[k + h.bo + 1];
     };
 
-    block_draw(q, (long long)blockIdx.x - gridDim.x, &s_slot);
-    __syncthreads();
-    long long slot = s_slot;
+    long long slot = block_open(q, &s_slot);
     if (slot < nrows_bin) {                              // uniform
         Head cur = head_of(slot);
         int k = 0, kn = 0;

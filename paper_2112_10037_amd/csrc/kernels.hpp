@@ -305,6 +305,17 @@ __device__ __forceinline__ void block_draw(unsigned* q, long long slot, long lon
     if (threadIdx.x == 0) *s_slot = q ? (long long)atomicAdd(q, 1u) : slot + gridDim.x;
 }
 
+// A workgroup's first slot by the same draws.  Every wave has read the ticket
+// when this returns: a row that takes no turn of the caller's loops (an empty
+// one) comes to the next draw without another barrier.
+__device__ __forceinline__ long long block_open(unsigned* q, long long* s_slot) {
+    block_draw(q, (long long)blockIdx.x - gridDim.x, s_slot);
+    __syncthreads();
+    const long long slot = *s_slot;
+    __syncthreads();
+    return slot;
+}
+
 // The last workgroup out resets the queue: every other workgroup has taken
 // its last slot by then, and the next launch on the stream finds zeros.
 __device__ __forceinline__ void block_slots_done(unsigned* q) {

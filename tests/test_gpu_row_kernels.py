@@ -8,7 +8,7 @@ import pytest
 
 from paper_2112_10037_amd import binding, gen
 
-from gpu_util import check_full
+from gpu_util import check_full, check_rows, run
 
 pytestmark = pytest.mark.gpu
 
@@ -244,3 +244,33 @@ def test_many_short_rows(h, ncols, rows):
     check_full(h, A, B)
     A = gen.erdos_renyi(rows, 700, rng.choice([8, 30], size=rows), seed=53)
     check_full(h, A, B)
+
+
+@pytest.mark.parametrize("first", ["empty", "entries"])
+@pytest.mark.parametrize("total,na", [(900, 40), (3900, 300), (7000, 60), (12_000, 60)])
+def test_workgroup_rows_start_without_a_walk(h, total, na, first):
+    """Every row in one bin of the workgroup kernels, so they are taken in
+    their natural order, and a workgroup's first row takes no turn of the walk
+    over A entries: empty rows, or rows of more A entries (most select empty B
+    rows) than the numeric sort takes.  More rows than a first round has."""
+    rng = np.random.default_rng(total)
+    ncols, rows = 2_000_000, 2600
+    none = np.arange(4000, 8000)                     # empty B rows
+    lens = _lengths(total, na)
+    brows = [np.sort(rng.integers(0, ncols, size=2 * length))[::2] for length in np.tile(lens, 4000 // na)]
+    brows = [np.unique(r) for r in brows] + [np.zeros(0, np.int64)] * (8000 - na * (4000 // na))
+    arows = []
+    for i in range(rows):
+        base = int(rng.integers(0, 4000 // na)) * na
+        row = np.arange(base, base + na)
+        if i < 1100 or i % 7 == 0:                   # (at most four workgroups a compute unit start on the first ones)
+            row = row[:0] if first == "empty" else np.concatenate([row, none])
+        arows.append(row)
+    A = _csr(arows, len(brows), rng, np.float32)
+    B = _csr(brows, ncols, rng, np.float32)
+    C = run(h, A, B)
+    check_rows(C, A, B, [0, 1, 7, 1099, 1100, 1101, 2598, 2599])
+    import oracle
+    nnz = h.symbolic(binding.DeviceCSR.from_host(A), binding.DeviceCSR.from_host(B))[0]
+    assert np.array_equal(nnz.cpu().numpy(), oracle.row_nnz(A, B))
+    assert np.array_equal(np.diff(C.row_ptr.cpu().numpy()), oracle.row_nnz(A, B))
