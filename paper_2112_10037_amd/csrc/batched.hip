@@ -489,6 +489,7 @@ extern "C" msp_status msp_batch_create(msp_handle* h, const msp_batch_csr* R, co
     in->alloc_ctx = h->alloc_ctx;
     in->num_cu = h->num_cu;
     in->lds_per_block = h->lds_per_block;
+    in->narrow_positions = h->narrow_positions;
     in->tuning = effective_tuning(h, opts);
     auto bail = [&](msp_status r) { release_batch(b); return r; };
     // private stream (default priority): the eager run and the capture

@@ -373,11 +373,14 @@ k_num_sort(Work wk,
     if (err) atomicOr(&info->err, err);
 }
 
-// Symbolic, one workgroup per row of at most BS R products (positions in B
-// below 2^32): the products' columns in registers, each joins the list of its
-// column's hash slot with one LDS exchange and counts unless an earlier member
-// has its column.  Rows of more products (their bound was B's width) are
-// appended to fb_list for the bitmap kernel.  Rows above the records'
+// Symbolic, one workgroup per row of at most BS R products: the products'
+// columns in registers, each joins the list of its column's hash slot with one
+// LDS exchange and counts unless an earlier member has its column.  An A
+// entry's position in B (less its first product's number) waits in its
+// members' place: 32 bits of it where the members' columns will lie and, with
+// WIDE (B of 2^32 entries or more), 16 above them in their predecessors'.
+// Rows of more products (their bound was B's width) are appended to fb_list for
+// the bitmap kernel.  Rows above the records'
 // threshold leave their outputs per window, as every symbolic workgroup
 // kernel does.
 //
@@ -387,7 +390,7 @@ k_num_sort(Work wk,
 // (564); a single row of 1030 short B rows took it 49 us, walking from product
 // to product (the rows above 2048 products of a power-law matrix of 171,000
 // rows: 123 and 68 us before, 50 and 30 here).
-template <int BS, int R, bool BATCH = false>
+template <int BS, int R, bool WIDE, bool BATCH = false>
 __global__ void __launch_bounds__(BS, BS <= 256 ? 5 : 4)
 k_sym_list(Work wk,
            const int64_t* __restrict__ arp, const int32_t* __restrict__ acol,
@@ -402,7 +405,7 @@ k_sym_list(Work wk,
     work_rows(wk, &nrows_bin, &perm);
     __shared__ __align__(16) int32_t head[H];
     __shared__ int32_t lc[CAP];                          // members' columns; before them the entries' positions
-    __shared__ uint16_t lp[CAP];                         // the member before, 0xffff: none
+    __shared__ uint16_t lp[CAP];                         // the member before (kListEnd: none); before, positions' bits 32-47
     __shared__ unsigned long long mark[WORDS];
     __shared__ int s_wc[BATCH ? 1 : kWinMaxNw];
     __shared__ int s_rslot;
@@ -475,7 +478,9 @@ k_sym_list(Work wk,
                 }
                 if (n > 0 && first + n <= CAP) {         // (then fewer than CAP entries lie before)
                     idx = lanes_below(some, idx);
-                    base[idx] = (uint32_t)b0 - (uint32_t)first;
+                    const long long at = b0 - first;
+                    base[idx] = (uint32_t)at;
+                    if constexpr (WIDE) lp[idx] = (uint16_t)(at >> 32);
                     const int last = first + n - 1;
                     atomicOr(reinterpret_cast<uint32_t*>(mark) + (last >> 5), 1u << (last & 31));
                 }
@@ -509,8 +514,11 @@ k_sym_list(Work wk,
                                                   (uint32_t)__builtin_amdgcn_readlane(hi[j], i),
                                                   __builtin_amdgcn_readlane(pre[j], i));
                         // lanes past the last product read it again
-                        const uint32_t at = base[min(e, entries - 1)] + (uint32_t)min(p, total - 1);
-                        c[s] = bcol[at];
+                        const int i0 = min(e, entries - 1);
+                        if constexpr (WIDE)
+                            c[s] = bcol[list_position(base[i0], lp[i0], min(p, total - 1))];
+                        else
+                            c[s] = bcol[base[i0] + (uint32_t)min(p, total - 1)];
                     }
                 }
             }

@@ -111,6 +111,7 @@ struct msp_handle {
     void* alloc_ctx = nullptr;
     int num_cu = 256;
     int lds_per_block = 65536;
+    long long narrow_positions = 1LL << 32;  // entries of B from which a position takes more than 32 bits
     msp_tuning tuning{};
     msp::DevBuf info, u, rnnz, perm, tiles, sbm, prod;
     msp::DevBuf bsum;               // 256-row workgroup totals of the fused symbolic pass

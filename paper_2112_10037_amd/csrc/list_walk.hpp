@@ -1,4 +1,4 @@
-// The walk back through the lists of k_sym_list, also built for the host (its
+// The positions and the walk back through the lists of k_sym_list, also built for the host (its
 // indices are checked there against the arrays they go into).
 #pragma once
 
@@ -13,6 +13,13 @@
 namespace msp {
 
 constexpr int kListEnd = 0xffff;      // 16-bit predecessor of a list's first member
+
+// Position in B of a row's product q from the 48 bits kept of its A entry's
+// (the entry's first position less its first product's number, which may be
+// below 0).
+MSP_LIST_FN long long list_position(uint32_t lo, uint16_t hi, int q) {
+    return (long long)(((uint64_t)hi << 32 | lo) + (uint64_t)q & 0xffffffffffffull);
+}
 
 // One step back for N products of a lane.  prev[i] is the member of the list
 // that product i meets next (below 0: none left; bit i of `live` is then

@@ -299,22 +299,28 @@ static msp_status launch_check(const char* what) {
     return MSP_OK;
 }
 
-// The list kernel keeps positions in B in 32 bits; without them its rows take
-// the bitmap kernel.
-static bool list_positions(const Operands& op) { return op.bnnz < (1LL << 32); }
-
 // LDS bytes of the symbolic bitmap (whole windows).
 static long long bitmap_bytes(long long ncols) {
     return ((ncols + 31) / 32 + kWin / 32 - 1) / (kWin / 32) * (kWin / 32) * 4;
 }
 
-// Rows of a symbolic Block bin that take the lists: all but those past 8192
-// products when the bitmap fits the LDS (on an R-MAT graph of 2^19 vertices
-// its rows of 8193 to 16,384 products take 2968 us in the lists of 1024
-// threads, which fill the LDS of a compute unit, 1.3 ms in the bitmap).
-static bool takes_lists(const msp_handle* h, const BinSpec& s, const Operands& op) {
-    return list_positions(op) &&
-           (s.lanes * s.slots <= 8192 || bitmap_bytes(op.ncols) > h->lds_per_block - kLdsReserve);
+// What takes the rows of a symbolic Block or Bitmap bin.  The slab is one area
+// of the handle's for every workgroup of a launch, so it is the Bitmap bin's
+// alone: a phase's other bins may run beside it on other streams.
+enum class SymRoute { List, HalfBitmap, Bitmap, Slab };
+
+// Block bins take the lists, all but the rows past 8192 products when the
+// bitmap fits the LDS (on an R-MAT graph of 2^19 vertices its rows of 8193 to
+// 16,384 products take 2968 us in the lists of 1024 threads, which fill the LDS
+// of a compute unit, 1.3 ms in the bitmap).  The bitmap is whole windows of
+// LDS; two workgroups a compute unit while two bitmaps fit, so that one row's
+// passes over its bitmap overlap the other's gathers.
+static SymRoute symbolic_route(const BinSpec& s, const Operands& op, int lds) {
+    const long long bytes = bitmap_bytes(op.ncols);
+    const bool fits = bytes <= lds - kLdsReserve;
+    if (s.kind == Kind::Block && (s.lanes * s.slots <= 8192 || !fits)) return SymRoute::List;
+    if (bytes <= lds / 2 - kLdsReserveHalf) return SymRoute::HalfBitmap;
+    return fits ? SymRoute::Bitmap : SymRoute::Slab;
 }
 
 // symbolic kernel of one bin over the rows of `wk`; `rows` (the row count,
@@ -358,37 +364,37 @@ static msp_status launch_symbolic_t(msp_handle* h, const BinSpec& s, Work wk, in
     }
         MSP_SYM_ROW_SHAPES(X)
 #undef X
-    } else if (s.kind == Kind::Block && takes_lists(h, s, op)) {
-        // rows past the lists go to the bounds array, which the symbolic pass
-        // has read by then; launch_list_rest takes them
+    } else if (s.kind == Kind::Block || s.kind == Kind::Bitmap) {
+        const SymRoute route = symbolic_route(s, op, h->lds_per_block);
+        if (route == SymRoute::List) {
+            // rows past the lists go to the bounds array, which the symbolic pass
+            // has read by then; launch_list_rest takes them
+            const bool wide = op.bnnz >= h->narrow_positions;
 #define X(BS, R)                                                                                           \
     if (s.lanes == BS && s.slots == R) {                                                                   \
-        const int grid = group_grid(h, (const void*)k_sym_list<BS, R, BATCH>, rows, 1, BS);               \
-        k_sym_list<BS, R, BATCH><<<grid, BS, 0, st>>>(wk, op.arp, op.acol, op.brp, op.bcol, rnnz, info, mp, rec, \
-                                                      rq, h->u.as<int32_t>(), &info->list_fb[0]);         \
+        const auto fn = wide ? k_sym_list<BS, R, true, BATCH> : k_sym_list<BS, R, false, BATCH>;          \
+        const int grid = group_grid(h, (const void*)fn, rows, 1, BS);                                      \
+        fn<<<grid, BS, 0, st>>>(wk, op.arp, op.acol, op.brp, op.bcol, rnnz, info, mp, rec, rq,             \
+                                h->u.as<int32_t>(), &info->list_fb[0]);                                    \
         return launch_check("k_sym_list");                                                                 \
     }
-        MSP_SYM_LIST_SHAPES(X)
+            MSP_SYM_LIST_SHAPES(X)
 #undef X
-    } else if (s.kind == Kind::Bitmap || s.kind == Kind::Block) {
+            return fail(MSP_ERR_UNSUPPORTED, "no symbolic kernel for bin shape (%d, %d)", s.lanes, s.slots);
+        }
         const long long n = op.ncols;
-        const long long words = (n + 31) / 32;
-        // whole windows of LDS; two workgroups a compute unit while two bitmaps
-        // fit, so that one row's passes over its bitmap overlap the other's gathers
-        const long long lds_bytes = bitmap_bytes(n);
-        const bool lds = lds_bytes <= h->lds_per_block - kLdsReserve;
-        const bool half = lds_bytes <= h->lds_per_block / 2 - kLdsReserveHalf;
-        const int grid = std::min(rows, (lds && !half ? 1 : 2) * h->num_cu);
+        const long long words = (n + 31) / 32, lds_bytes = bitmap_bytes(n);
+        const int grid = std::min(rows, (route == SymRoute::Bitmap ? 1 : 2) * h->num_cu);
         uint32_t* slab = nullptr;
-        if (!lds) {
+        if (route == SymRoute::Slab) {
             msp_status r = h->sbm.ensure((size_t)grid * words * 4);
             if (r != MSP_OK) return r;
             slab = h->sbm.as<uint32_t>();
         }
-        if (half)
+        if (route == SymRoute::HalfBitmap)
             k_sym_bitmap<512, true, BATCH><<<grid, 512, lds_bytes, st>>>(wk, n, op.arp, op.acol, op.brp, op.bcol, rnnz,
                                                                          slab, info, mp, rec, rq);
-        else if (lds)
+        else if (route == SymRoute::Bitmap)
             k_sym_bitmap<1024, true, BATCH><<<grid, 1024, lds_bytes, st>>>(wk, n, op.arp, op.acol, op.brp, op.bcol,
                                                                            rnnz, slab, info, mp, rec, rq);
         else
@@ -583,7 +589,7 @@ msp_status launch_sort_rest(msp_handle* h, int rows, const Operands& op, const i
 // launched).
 template <bool BATCH>
 msp_status launch_list_rest(msp_handle* h, int rows, int most, const Operands& op, int32_t* rnnz, const RowMap& mp) {
-    if (rows <= 0 || !list_positions(op) || (!BATCH && op.ncols > most)) return MSP_OK;
+    if (rows <= 0 || (!BATCH && op.ncols > most)) return MSP_OK;
     DevInfo* info = h->info.as<DevInfo>();
     Work wk{h->u.as<int32_t>(), 0, &info->list_fb[0]};
     wk.rowq = &info->queue[0][kNB][0];
@@ -1284,6 +1290,24 @@ extern "C" msp_status msp_share_stats_get(msp_handle* h, msp_share_stats* out) {
 }
 
 extern "C" long long msp_internal_summary_fallbacks(const msp_handle* h) { return h ? h->summary_fallbacks : -1; }
+
+// For tests of the dispatch (no device needed): what takes symbolic rows of
+// `bound` outputs at most, by the default tuning on a compute unit of 160 KB
+// LDS (0: a smaller kernel, else 1 + SymRoute).
+extern "C" int msp_internal_symbolic_route(long long ncols, long long bnnz, int bound) {
+    const msp::BinPlan p = msp::symbolic_plan(msp::default_tuning(), false);
+    const msp::BinSpec& s = p.spec[msp::bin_of(p.table, bound)];
+    if (s.kind != msp::Kind::Block && s.kind != msp::Kind::Bitmap) return 0;
+    msp::Operands op{};
+    op.ncols = ncols;
+    op.bnnz = bnnz;
+    return 1 + (int)msp::symbolic_route(s, op, 160 * 1024);
+}
+
+// For tests: entries of B from which positions in it take more than 32 bits.
+extern "C" void msp_internal_set_narrow_positions(msp_handle* h, long long entries) {
+    if (h) h->narrow_positions = entries;
+}
 
 extern "C" int msp_internal_unsupported_plans(int verbose) { return msp::count_unsupported_plans(verbose); }
 

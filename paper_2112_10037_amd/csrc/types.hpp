@@ -199,7 +199,7 @@ __device__ __forceinline__ long long row_boff(const RowMap& mp, long long g) {
     else return 0;
 }
 
-__device__ __forceinline__ int bin_of(const BinTable& t, long long u) {
+__host__ __device__ __forceinline__ int bin_of(const BinTable& t, long long u) {
     if (u <= 0) return 0;
     for (int b = 1; b < t.nb; ++b)
         if (u <= t.umax[b]) return b;

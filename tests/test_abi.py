@@ -33,6 +33,23 @@ def test_every_tuning_plan_has_a_kernel():
     assert lib.msp_internal_unsupported_plans(0) == 0
 
 
+def test_only_the_bitmap_bin_takes_the_slab():
+    """A phase's bins may run at the same time, and the bitmap slab is one area
+    of the handle: rows of up to 16,384 products never take it, whatever the
+    width and the size of B."""
+    lib = ctypes.CDLL(binding.LIB_PATH)
+    route = lib.msp_internal_symbolic_route
+    route.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
+    LIST, HALF, BITMAP, SLAB = 1, 2, 3, 4
+    for nnz in (10 ** 6, (1 << 32) - 1, 1 << 32, 1 << 36):
+        for ncols in (20_000, 500_000, 1_000_000, 1_200_000, 2 ** 31 - 1):
+            for bound in (1025, 2048, 2049, 8192):
+                assert route(ncols, nnz, bound) == LIST
+            assert route(ncols, nnz, 16_384) == (LIST if ncols > 1_100_000 else BITMAP if ncols > 570_000 else HALF)
+            assert route(ncols, nnz, 16_385) == (SLAB if ncols > 1_100_000 else BITMAP if ncols > 570_000 else HALF)
+    assert route(10 ** 9, 1 << 32, 1024) == 0
+
+
 def test_status_strings_and_null_handle():
     lib = binding.load()
     for code in range(9):

@@ -3,6 +3,8 @@ the register and sort limits, column spans at the bitmap's, buckets at their
 fullest, empty B rows, more A entries than lanes.  Structure identical,
 values within the repository's bounds (1e-12 FP64, 1e-5 FP32 times the sum of
 |a||b|: a row of at most 1024 FP64 additions is off by less than 1024 2^-53)."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -274,3 +276,40 @@ def test_workgroup_rows_start_without_a_walk(h, total, na, first):
     nnz = h.symbolic(binding.DeviceCSR.from_host(A), binding.DeviceCSR.from_host(B))[0]
     assert np.array_equal(nnz.cpu().numpy(), oracle.row_nnz(A, B))
     assert np.array_equal(np.diff(C.row_ptr.cpu().numpy()), oracle.row_nnz(A, B))
+
+
+@pytest.fixture(scope="module")
+def wide():
+    """A handle that keeps positions in B as if B had 2^32 entries or more."""
+    hh = binding.Handle(0)
+    f = hh._lib.msp_internal_set_narrow_positions
+    f.argtypes = [ctypes.c_void_p, ctypes.c_longlong]
+    f(hh._h, 0)
+    yield hh
+    hh.close()
+
+
+@pytest.mark.parametrize("name", sorted(LIST_CASES))
+def test_list_kernel_edges_with_wide_positions(wide, name):
+    test_list_kernel_edges(wide, name)
+
+
+@pytest.mark.parametrize("batch", [False, True])
+@pytest.mark.parametrize("ncols", [1_200_000, 20_000])
+def test_lists_side_by_side_with_wide_positions(wide, ncols, batch):
+    """Few rows in each of the symbolic lists' bins and in the bitmap bin, which
+    run at the same time, with more columns than the LDS bitmap holds."""
+    rng = np.random.default_rng(ncols)
+    B = gen.erdos_renyi(40_000, ncols, 25, seed=61)
+    A = gen.erdos_renyi(300, 40_000, rng.choice([3, 50, 200, 400, 900], size=300), seed=62)
+    if not batch:
+        check_full(wide, A, B)
+        return
+    plan = binding.Batch(wide, *[binding.PackedBatch.from_host([x, x]) for x in (A, B)])
+    plan.execute()
+    import oracle
+    ref = oracle.spgemm(A, B)
+    for p in range(2):
+        got = plan.result(p).to_host()
+        oracle.compare(got.row_ptr, got.col, got.val, ref, 1e-12)
+    plan.close()

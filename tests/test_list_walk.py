@@ -61,7 +61,16 @@ static int walk(int R, int total, int distinct, int heads) {
     return bad ? bad : (count == (distinct < total ? distinct : total) ? 0 : -1);
 }
 
-int main(int, char** a) { std::printf("%d\n", walk(atoi(a[1]), atoi(a[2]), atoi(a[3]), atoi(a[4]))); }
+// the position of product q of an entry that starts at b0 with product `first`
+static long long position(long long b0, int first, int q) {
+    const long long at = b0 - first;
+    return msp::list_position((uint32_t)at, (uint16_t)(at >> 32), q);
+}
+
+int main(int n, char** a) {
+    if (n == 4) std::printf("%lld\n", position(atoll(a[1]), atoi(a[2]), atoi(a[3])));
+    else std::printf("%d\n", walk(atoi(a[1]), atoi(a[2]), atoi(a[3]), atoi(a[4])));
+}
 """
 
 
@@ -84,3 +93,10 @@ def test_list_walk_stays_inside(harness, R, total, distinct, heads):
     out = subprocess.run([harness, str(R), str(total), str(distinct), str(heads)], capture_output=True, text=True,
                          check=True)
     assert int(out.stdout) == 0
+
+
+@pytest.mark.parametrize("b0", [0, 5, (1 << 32) - 3, 1 << 32, (1 << 32) + 100, (1 << 37) + 12_345])
+@pytest.mark.parametrize("first,q", [(0, 0), (0, 9000), (7, 7), (16_383, 16_383), (9000, 9007)])
+def test_list_positions_keep_their_upper_bits(harness, b0, first, q):
+    out = subprocess.run([harness, str(b0), str(first), str(q)], capture_output=True, text=True, check=True)
+    assert int(out.stdout) == b0 + (q - first)
