@@ -316,16 +316,19 @@ static msp_status run_stage(msp_batch* b, int si, bool eager) {
         k_scatter<<<(M + 255) / 256, 256, 0, st>>>(M, h->u.as<int32_t>(), S.sp.table, &info->sym_part[0][0], 256,
                                                    &info->cursor[0][0][0], h->perm.as<int32_t>());
         if ((s = launch_ok("k_scatter")) != MSP_OK) return s;
-        int listed = 0;
+        int listed = 0, most = 0;
         for (int bn = 1; bn <= S.sp.table.nb; ++bn) {
             if (!((S.sym_planned >> bn) & 1u) || (bn == 1 && S.sym_merge_all)) continue;
             if ((s = launch_symbolic_bin<true>(h, S.sp.spec[bn], Work{h->perm.as<int32_t>(), 0, wsym + 2 * bn},
                                                S.sym_rows[bn], S.op, h->rnnz.as<int32_t>(), S.mp, nullptr, 0)) !=
                 MSP_OK)
                 return s;
-            if (S.sp.spec[bn].kind == Kind::Block) listed += S.sym_rows[bn];
+            if (S.sp.spec[bn].kind == Kind::Block) {
+                listed += S.sym_rows[bn];
+                most = S.sp.table.umax[bn];
+            }
         }
-        if ((s = launch_list_rest<true>(h, listed, 0, S.op, h->rnnz.as<int32_t>(), S.mp)) != MSP_OK) return s;
+        if ((s = launch_list_rest<true>(h, listed, most, S.op, h->rnnz.as<int32_t>(), S.mp)) != MSP_OK) return s;
     }
     // 3. prefix sum (fresh tile states every replay) with the numeric histogram
     if (fused) {

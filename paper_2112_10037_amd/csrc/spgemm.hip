@@ -585,15 +585,18 @@ msp_status launch_sort_rest(msp_handle* h, int rows, const Operands& op, const i
 
 // After a symbolic phase's bins: the rows its Block bins (of `rows` rows, with
 // bounds up to `most`) left to the bitmap kernel.  A row's bound is its product
-// count unless B is narrower (a batch's problems differ, so there it is always
-// launched).
+// count unless B is narrower, so a row with more products than its bin's lists
+// take has at most `most` columns: without so narrow a B there is none, and in a
+// batch, whose problems differ, the bitmap needs no more than that.
 template <bool BATCH>
 msp_status launch_list_rest(msp_handle* h, int rows, int most, const Operands& op, int32_t* rnnz, const RowMap& mp) {
     if (rows <= 0 || (!BATCH && op.ncols > most)) return MSP_OK;
     DevInfo* info = h->info.as<DevInfo>();
     Work wk{h->u.as<int32_t>(), 0, &info->list_fb[0]};
     wk.rowq = &info->queue[0][kNB][0];
-    return launch_symbolic_t<BATCH>(h, BinSpec{Kind::Bitmap, 1024, 0}, wk, std::min(rows, h->num_cu), op, rnnz, mp);
+    Operands narrow = op;
+    narrow.ncols = std::min<long long>(op.ncols, most);
+    return launch_symbolic_t<BATCH>(h, BinSpec{Kind::Bitmap, 1024, 0}, wk, std::min(rows, h->num_cu), narrow, rnnz, mp);
 }
 
 template <bool BATCH>

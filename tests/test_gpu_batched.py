@@ -307,3 +307,28 @@ def test_results_copied_from_any_offset(h, dtype):
     for p in range(len(A)):
         _check(plan.result(p), oracle.spgemm(A[p], B[p]), dtype)
     plan.close()
+
+
+def test_rows_past_the_lists_need_no_wide_bitmap(h):
+    """A batch of a problem of 2^31 - 1 columns and one whose rows have more
+    products than the symbolic lists take: those are at most 16,384 columns
+    wide, and the plan's memory does not grow with the other's width."""
+    import torch
+    narrow = gen.erdos_renyi(2000, 15_000, 50, seed=81)
+    A = gen.erdos_renyi(400, 2000, 500, seed=82)         # 25,000 products a row
+    few = gen.erdos_renyi(300, 18_000, 60, seed=83)
+    spread = np.arange(18_000, dtype=np.int64) * 119_304 + 10
+    wide = gen.CSR(300, 2 ** 31 - 1, few.row_ptr, spread[few.col].astype(np.int32), few.val)
+    A1 = gen.erdos_renyi(400, 300, 40, seed=84)          # 2400
+    pa, pb = binding.PackedBatch.from_host([A1, A]), binding.PackedBatch.from_host([wide, narrow])
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    plan = binding.Batch(h, pa, pb)
+    assert before - torch.cuda.mem_get_info()[0] < 1 << 30
+    plan.execute()
+    for p, (x, y) in enumerate([(A1, few), (A, narrow)]):
+        got = plan.result(p).to_host()
+        col = got.col if p else np.searchsorted(spread, got.col).astype(np.int32)
+        assert p or np.array_equal(spread[col], got.col)
+        oracle.compare(got.row_ptr, col, got.val, oracle.spgemm(x, y), 1e-12)
+    plan.close()
