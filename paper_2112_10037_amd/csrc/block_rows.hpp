@@ -315,10 +315,14 @@ k_num_sort(Work wk,
                         }
                     __syncthreads();
                     if (!cnt_out && total == expect) {     // no two products in one column
+                        bool twice = false;
                         for (int j = tid; j < total; j += BS) {
-                            ccol[rp + j] = sc[j];
+                            const int x = sc[j];
+                            twice = twice || (j > 0 && sc[j - 1] == x);
+                            ccol[rp + j] = x;
                             cval[rp + j] = (VT)sv[j];
                         }
+                        if (twice) err |= kErrCount;       // (the symbolic count was too high)
                     } else {
                         // each column's sum at its rank; a wave takes R 64-entry steps in a row
                         int heads = 0;

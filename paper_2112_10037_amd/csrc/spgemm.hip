@@ -1307,6 +1307,24 @@ extern "C" int msp_internal_symbolic_route(long long ncols, long long bnnz, int 
     return 1 + (int)msp::symbolic_route(s, op, 160 * 1024);
 }
 
+// For tests of the numeric kernels' checks: the numeric pass of A B with row
+// counts given by the caller (C's arrays hold their sum).
+extern "C" msp_status msp_internal_numeric(msp_handle* h, const msp_csr* A, const msp_csr* B, const int32_t* row_nnz,
+                                           msp_csr_out* C) {
+    msp_status s = check_pair(A, B);
+    if (s != MSP_OK) return s;
+    const int m = (int)A->nrows;
+    const BinPlan np = numeric_plan(h->tuning, false);
+    if ((s = h->u.ensure((size_t)std::max(m, 1) * 4)) != MSP_OK || (s = zero_info(h)) != MSP_OK) return s;
+    const int seq = ++h->sum_seq;
+    if ((s = run_scan(h, m, row_nnz, C->row_ptr, &np, seq)) != MSP_OK) return s;
+    if ((s = wait_summary(h, seq, true, h->info.as<DevInfo>()->num_part)) != MSP_OK) return s;
+    if (h->hsum->nnz > C->nnz) return fail(MSP_ERR_INVALID_ARG, "C is too small");
+    int counts[kNB];
+    for (int b = 0; b < kNB; ++b) counts[b] = h->hsum->counts[b];
+    return run_numeric_bins(h, A, B, np, counts, row_nnz, C->row_ptr, C->col, C->val, nullptr);
+}
+
 // For tests: entries of B from which positions in it take more than 32 bits.
 extern "C" void msp_internal_set_narrow_positions(msp_handle* h, long long entries) {
     if (h) h->narrow_positions = entries;

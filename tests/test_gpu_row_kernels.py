@@ -10,7 +10,7 @@ import pytest
 
 from paper_2112_10037_amd import binding, gen
 
-from gpu_util import check_full, check_rows, run
+from gpu_util import TOL, check_full, check_rows, run, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -313,3 +313,46 @@ def test_lists_side_by_side_with_wide_positions(wide, ncols, batch):
         got = plan.result(p).to_host()
         oracle.compare(got.row_ptr, got.col, got.val, ref, 1e-12)
     plan.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("total,na,lo,hi", [(200, 20, 0, 40_000), (300, 20, 0, 2_000_000), (600, 40, 0, 2_000_000),
+                                            (900, 40, 0, 2_000_000), (1900, 100, 0, 3000), (3900, 300, 0, 2_000_000)])
+def test_counts_that_are_too_high_are_reported(h, total, na, lo, hi, dtype):
+    """Row counts of a symbolic pass that missed one merge: as many as the
+    products, where two of them share a column."""
+    import torch
+    rng = np.random.default_rng(total)
+    arows, brows = [], []
+    for _ in range(8):
+        first = len(brows)
+        cols = lo + np.sort(rng.permutation(hi - lo)[:total])
+        part = np.split(cols[rng.permutation(total)], np.cumsum(_lengths(total, na))[:-1])
+        part[1][0] = part[0][0]                       # two products in one column
+        brows += part
+        arows.append(np.arange(first, first + na))
+    A = _csr(arows, len(brows), rng, dtype)
+    B = _csr(brows, hi + 1, rng, dtype)
+    import oracle
+    right = oracle.row_nnz(A, B)
+    assert np.array_equal(right, np.full(8, total - 1))
+    da, db = to_dev(A), to_dev(B)
+    run_numeric = h._lib.msp_internal_numeric
+    run_numeric.argtypes = [ctypes.c_void_p, ctypes.POINTER(binding.c_csr), ctypes.POINTER(binding.c_csr),
+                            ctypes.c_void_p, ctypes.POINTER(binding.c_csr_out)]
+    for counts, good in [(right, True), (right + 1, False)]:
+        n = int(counts.sum())
+        cnt = torch.from_numpy(counts.astype(np.int32)).cuda()
+        rp = torch.empty(9, dtype=torch.int64, device="cuda")
+        col = torch.empty(n, dtype=torch.int32, device="cuda")
+        val = torch.empty(n, dtype=da.val.dtype, device="cuda")
+        torch.cuda.synchronize()
+        out = binding.c_csr_out(8, hi + 1, n, rp.data_ptr(), col.data_ptr(), val.data_ptr(), da.c().dtype)
+        assert run_numeric(h._h, ctypes.byref(da.c()), ctypes.byref(db.c()), cnt.data_ptr(), ctypes.byref(out)) == 0
+        if good:
+            h.sync()
+            oracle.compare(rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy(), oracle.spgemm(A, B),
+                           TOL[np.dtype(dtype)])
+        else:
+            with pytest.raises(binding.MspError):
+                h.sync()
