@@ -393,18 +393,14 @@ static msp_status run_stage(msp_batch* b, int si, bool eager) {
         k_scatter<<<(M + 255) / 256, 256, 0, st>>>(M, h->rnnz.as<int32_t>(), S.np.table, &info->num_part[0][0],
                                                    kScanTile, &info->cursor[1][0][0], h->perm.as<int32_t>());
         if ((s = launch_ok("k_scatter")) != MSP_OK) return s;
-        int sorted = 0;
         for (int bn = 1; bn <= S.np.table.nb; ++bn) {
             if (!((S.num_planned >> bn) & 1u)) continue;
-            if ((s = launch_numeric_bin<true>(h, S.np.spec[bn],
-                                              Work{h->perm.as<int32_t>(), 0, wnum + 2 * bn, queue(bn), b->queue_rows},
-                                              S.num_rows[bn], S.op, S.crp.as<int64_t>(), ccol, cval, nullptr,
-                                              S.mp)) != MSP_OK)
+            Work wk{h->perm.as<int32_t>(), 0, wnum + 2 * bn, queue(bn), b->queue_rows};
+            wk.left = &info->sort_fb[bn][0];
+            if ((s = launch_numeric_bin<true>(h, S.np.spec[bn], wk, S.num_rows[bn], S.op, S.crp.as<int64_t>(), ccol,
+                                              cval, nullptr, S.mp)) != MSP_OK)
                 return s;
-            if (S.np.spec[bn].kind == Kind::Block) sorted += S.num_rows[bn];
         }
-        if ((s = launch_sort_rest<true>(h, sorted, S.op, S.crp.as<int64_t>(), ccol, cval, nullptr, S.mp)) != MSP_OK)
-            return s;
     }
     k_fold_err<<<1, 64, 0, st>>>(info, flag);
     return launch_ok("k_fold_err");

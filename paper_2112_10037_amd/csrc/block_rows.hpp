@@ -15,7 +15,11 @@ namespace msp {
 // a skewed matrix's full buckets hold up few waves.  Sums over equal columns,
 // now neighbours, go out in order.  A row of one nonempty B row is its copy,
 // scaled.  Rows past those limits, or with more than kSortBucket products in
-// a bucket, are appended to fb_list (count in fb_count) for the hash kernel.
+// a bucket, go into the bin's own part of fb_list (count and place in fb) for a
+// hash kernel with a table of the bin's size: rows whose products merge several
+// to an output can be most of a bin.  Such rows cost little here, so they are
+// listed kLeft at a time and drawn `per` at a time (60,000 of them 711 us one by
+// one).
 //
 // The walk finds a product's A entry as the row kernels of one wave do: a mark
 // per entry at its last product, counted below the lane.
@@ -30,6 +34,7 @@ namespace msp {
 // workgroups too 1139, 765 and 524 us.
 constexpr int kSortBucket = 256;
 constexpr int kSortR = 8;
+constexpr int kLeft = 16;
 
 template <int BS, int R>
 struct SortCfg {
@@ -46,8 +51,8 @@ k_num_sort(Work wk,
            const int64_t* __restrict__ arp, const int32_t* __restrict__ acol, const VT* __restrict__ aval,
            const int64_t* __restrict__ brp, const int32_t* __restrict__ bcol, const VT* __restrict__ bval,
            const int64_t* __restrict__ crp, int32_t* __restrict__ ccol, VT* __restrict__ cval,
-           int32_t* __restrict__ cnt_out, DevInfo* info, RowMap mp, unsigned* q, int32_t* __restrict__ fb_list,
-           int* fb_count) {
+           int32_t* __restrict__ cnt_out, DevInfo* info, RowMap mp, unsigned* q, int per,
+           int32_t* __restrict__ fb_list, int* fb) {
     using Cfg = SortCfg<BS, R>;
     constexpr int CAP = Cfg::kCap, NB = Cfg::kBuckets, NW = BS / 64, WORDS = Cfg::kWords;
     int nrows_bin;
@@ -61,6 +66,7 @@ k_num_sort(Work wk,
     VT* const av = reinterpret_cast<VT*>(area + (Cfg::kEntries + 1) * 8);
     __shared__ unsigned long long mark[WORDS];
     __shared__ long long s_slot;
+    __shared__ int s_left[kLeft];                        // rows to list (thread 0's)
     __shared__ int s_sum[NW], s_some[NW], s_min[NW], s_max[NW], s_tot[NW], s_most[NW], s_heads[NW];
     const uint16_t* const cs = reinterpret_cast<const uint16_t*>(cw);
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -93,7 +99,25 @@ k_num_sort(Work wk,
         *b1 = brp[k + h.bo + 1];
     };
 
-    long long slot = block_open(q, &s_slot);
+    // (a batch's bin has its place in the row list on the device)
+    const int place = wk.dev ? wk.dev[1] : 0;
+    fb_list += place;
+    if (blockIdx.x == 0 && tid == 0) fb[1] = place;
+    int nleft = 0;
+    auto leave = [&](int row) {                            // thread 0
+        if (row >= 0) s_left[nleft++] = row;
+        if (nleft == kLeft || (row < 0 && nleft > 0)) {
+            const int to = atomicAdd(&fb[0], nleft);
+            for (int i = 0; i < nleft; ++i) fb_list[to + i] = s_left[i];
+            nleft = 0;
+        }
+    };
+
+    SlotRun run;
+    run.draw(q, per, (long long)blockIdx.x - gridDim.x, &s_slot);
+    __syncthreads();
+    long long slot = s_slot;
+    __syncthreads();                                       // (a row may come to the next draw without another)
     if (slot < nrows_bin) {                                // uniform
         Head cur = head_of(slot);
         int k = 0, kn = 0;
@@ -147,7 +171,7 @@ k_num_sort(Work wk,
                 }
             }
             const bool takes = na <= Cfg::kEntries && total <= CAP;   // uniform
-            block_draw(q, slot, &s_slot);
+            run.draw(q, per, slot, &s_slot);
             __syncthreads();
             const long long next = s_slot;
             const bool more = next < nrows_bin;            // uniform
@@ -362,7 +386,7 @@ k_num_sort(Work wk,
                     done = true;
                 }
             }
-            if (!done && tid == 0) fb_list[atomicAdd(fb_count, 1)] = row;
+            if (!done && tid == 0) leave(row);
             if (!more) break;
             slot = next;
             cur = nxt;
@@ -373,6 +397,7 @@ k_num_sort(Work wk,
             __syncthreads();                               // the next row writes what this one still reads
         }
     }
+    if (tid == 0) leave(-1);
     block_slots_done(q);
     if (err) atomicOr(&info->err, err);
 }

@@ -37,7 +37,7 @@ struct BinSpec {
     Kind kind = Kind::None;
     int lanes = 0;      // K lists for Merge, rows per batch R for Batch, G for Group,
                         // BS for Block/Bitmap/Dense
-    int slots = 0;      // T (hash slots) for Group/Block
+    int slots = 0;      // T (hash slots) for Group and numeric Block; R (products a thread) for symbolic Block
     int share = 0;      // Merge, numeric: rows per batch that share staged B rows (0: off)
 };
 
@@ -208,10 +208,5 @@ msp_status launch_numeric_bin(msp_handle* h, const BinSpec& s, Work wk, int rows
 // kernel (see spgemm.hip).
 template <bool BATCH>
 msp_status launch_list_rest(msp_handle* h, int rows, int most, const Operands& op, int32_t* rnnz, const RowMap& mp);
-// After a numeric phase's bins: the rows its Block bins (of `rows` rows) left
-// to the hash kernel.
-template <bool BATCH>
-msp_status launch_sort_rest(msp_handle* h, int rows, const Operands& op, const int64_t* crp, int32_t* ccol, void* cval,
-                            int32_t* cnt_out, const RowMap& mp);
 
 }  // namespace msp

@@ -116,7 +116,9 @@ BinPlan numeric_plan(const msp_tuning& t, bool force_spill, bool rule) {
         std::sort(list, list + 5);
         for (int u : list) {
             if (u > t.spill_nnz || u <= last || (u == 1024 && rule && t.spill_nnz > 1024)) continue;
-            add_bin(p, u, BinSpec{Kind::Block, u <= 1024 ? 128 : (u <= 2048 ? 256 : 512), kSortR});
+            // the sort's threads, and the table of the hash for the rows it leaves
+            add_bin(p, u, BinSpec{Kind::Block, u <= 1024 ? 128 : (u <= 2048 ? 256 : 512),
+                                  std::min(8192, next_pow2(u) << t.hash_scale)});
             last = u;
         }
     }
@@ -160,9 +162,10 @@ static bool symbolic_in_batches(const BinSpec& s, int rows, long long ncols) {
 }
 #define MSP_NUM_BATCH_SHAPES(X) X(32, 12) X(32, 8) X(32, 4) X(64, 8) X(64, 4) X(64, 2)
 #define MSP_SYM_LIST_SHAPES(X) X(256, 8) X(512, 16) X(1024, 16)
-// workgroup threads of the numeric counting sort; every size takes kSortR
-// products a thread
+// workgroup threads of the numeric counting sort (every size takes kSortR
+// products a thread), and threads and table of the hash behind it
 #define MSP_NUM_SORT_SHAPES(X) X(128) X(256) X(512)
+#define MSP_NUM_BLOCK_SHAPES(X) X(256, 512) X(256, 1024) X(512, 2048) X(512, 4096) X(1024, 8192)
 
 static bool spec_supported(const BinSpec& sp, bool numeric) {
     switch (sp.kind) {
@@ -184,9 +187,16 @@ static bool spec_supported(const BinSpec& sp, bool numeric) {
 #define X(BS, R) if (!numeric && sp.lanes == BS && sp.slots == R) return true;
             MSP_SYM_LIST_SHAPES(X)
 #undef X
-#define X(BS) if (numeric && sp.lanes == BS && sp.slots == kSortR) return true;
-            MSP_NUM_SORT_SHAPES(X)
+            if (numeric) {
+                bool sort = false, hash = false;
+#define X(BS) sort = sort || sp.lanes == BS;
+                MSP_NUM_SORT_SHAPES(X)
 #undef X
+#define X(BS, T) hash = hash || sp.slots == T;
+                MSP_NUM_BLOCK_SHAPES(X)
+#undef X
+                return sort && hash;
+            }
             return false;
         case Kind::Bitmap: return !numeric;
         case Kind::Dense: return numeric;
@@ -506,16 +516,31 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
 #undef X
     } else if (s.kind == Kind::Block) {
         // rows the sort does not take are listed in the bounds array, which the
-        // numeric pass has no other use for; launch_sort_rest takes them
+        // numeric pass has no other use for, where the bin's rows are in the row
+        // list; the hash takes them behind it on the same stream (and from the
+        // same row queue, which the sort leaves at zero)
+        int32_t* const list = h->u.as<int32_t>() + (wk.perm ? wk.perm - h->perm.as<int32_t>() : 0);
 #define X(BS)                                                                                              \
     if (s.lanes == BS) {                                                                                   \
         const int grid = group_grid(h, (const void*)k_num_sort<BS, kSortR, VT, BATCH>, rows, 1, BS);      \
+        const int per = std::max(1, std::min(8, rows / (8 * grid)));                                       \
         k_num_sort<BS, kSortR, VT, BATCH><<<grid, BS, 0, st>>>(                                            \
-            wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, ccol, cval, cnt_out, info, mp, rq,          \
-            h->u.as<int32_t>(), &info->sort_fb[0]);                                                        \
-        return launch_check("k_num_sort");                                                                 \
+            wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, ccol, cval, cnt_out, info, mp, rq, per, list, \
+            wk.left);                                                                                      \
+        const msp_status r = launch_check("k_num_sort");                                                   \
+        if (r != MSP_OK) return r;                                                                         \
     }
         MSP_NUM_SORT_SHAPES(X)
+#undef X
+        const Work rest{list, 0, wk.left};
+#define X(BS, T)                                                                                           \
+    if (s.slots == T) {                                                                                    \
+        const int grid = group_grid(h, (const void*)k_num_block<BS, T, VT, BATCH>, rows, 1, BS);          \
+        k_num_block<BS, T, VT, BATCH><<<grid, BS, 0, st>>>(rest, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, \
+                                                           ccol, cval, cnt_out, info, mp, rq);             \
+        return launch_check("k_num_block");                                                                \
+    }
+        MSP_NUM_BLOCK_SHAPES(X)
 #undef X
     } else if (s.kind == Kind::Dense) {
         const long long n = op.ncols;
@@ -561,28 +586,6 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
     return fail(MSP_ERR_UNSUPPORTED, "no numeric kernel for bin shape (%d, %d)", s.lanes, s.slots);
 }
 
-// The rows that the workgroup sorts of a numeric phase left (at most `rows`),
-// through the LDS hash: once, after every bin of the phase.
-template <typename VT, bool BATCH>
-static msp_status launch_sort_rest_t(msp_handle* h, int rows, const Operands& op, const int64_t* crp, int32_t* ccol,
-                                     VT* cval, int32_t* cnt_out, const RowMap& mp) {
-    DevInfo* info = h->info.as<DevInfo>();
-    const Work wk{h->u.as<int32_t>(), 0, &info->sort_fb[0]};
-    k_num_block<1024, 8192, VT, BATCH><<<std::min(rows, h->num_cu), 1024, 0, h->stream>>>(
-        wk, op.arp, op.acol, (const VT*)op.aval, op.brp, op.bcol, (const VT*)op.bval, crp, ccol, cval, cnt_out, info,
-        mp, BATCH ? nullptr : &info->queue[1][kNB][0]);
-    return launch_check("k_num_block");
-}
-
-template <bool BATCH>
-msp_status launch_sort_rest(msp_handle* h, int rows, const Operands& op, const int64_t* crp, int32_t* ccol, void* cval,
-                            int32_t* cnt_out, const RowMap& mp) {
-    if (rows <= 0) return MSP_OK;
-    if (op.dtype == MSP_F64)
-        return launch_sort_rest_t<double, BATCH>(h, rows, op, crp, ccol, (double*)cval, cnt_out, mp);
-    return launch_sort_rest_t<float, BATCH>(h, rows, op, crp, ccol, (float*)cval, cnt_out, mp);
-}
-
 // After a symbolic phase's bins: the rows its Block bins (of `rows` rows, with
 // bounds up to `most`) left to the bitmap kernel.  A row's bound is its product
 // count unless B is narrower, so a row with more products than its bin's lists
@@ -619,8 +622,6 @@ template msp_status launch_symbolic_bin<true>(msp_handle*, const BinSpec&, Work,
                                               const RowMap&, const int32_t*, int);
 template msp_status launch_numeric_bin<true>(msp_handle*, const BinSpec&, Work, int, const Operands&,
                                              const int64_t*, int32_t*, void*, int32_t*, const RowMap&);
-template msp_status launch_sort_rest<true>(msp_handle*, int, const Operands&, const int64_t*, int32_t*, void*,
-                                           int32_t*, const RowMap&);
 
 Operands operands_of(const msp_csr* A, const msp_csr* B) {
     Operands op;
@@ -649,9 +650,11 @@ static msp_status launch_symbolic(msp_handle* h, const BinSpec& s, int rows, con
 
 static msp_status launch_numeric(msp_handle* h, const BinSpec& s, int rows, const int32_t* perm,
                                  const msp_csr* A, const msp_csr* B, const int64_t* crp,
-                                 int32_t* ccol, void* cval, int32_t* cnt_out, unsigned* rowq) {
+                                 int32_t* ccol, void* cval, int32_t* cnt_out, int bin) {
+    DevInfo* info = h->info.as<DevInfo>();
     Work wk{perm, rows, nullptr};
-    wk.rowq = rowq;
+    wk.rowq = &info->queue[1][bin][0];
+    wk.left = &info->sort_fb[bin][0];
     return launch_numeric_bin<false>(h, s, wk, rows, operands_of(A, B), crp, ccol, cval, cnt_out, RowMap{});
 }
 
@@ -813,24 +816,24 @@ static msp_status run_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, co
         }
     if (nonempty == 0) return MSP_OK;
     DevInfo* info = h->info.as<DevInfo>();
-    // what the Block bins left, after all bins
+    // what the symbolic Block bins left, after all bins
     auto rest = [&]() -> msp_status {
+        if (numeric) return MSP_OK;
         int rows = 0, most = 0;
         for (int b = 1; b <= nb; ++b)
             if (plan.spec[b].kind == Kind::Block && counts[b] > 0) {
                 rows += counts[b];
                 most = plan.table.umax[b];
             }
-        return numeric ? launch_sort_rest<false>(h, rows, operands_of(A, B), crp, ccol, cval, cnt_out, RowMap{})
-                       : launch_list_rest<false>(h, rows, most, operands_of(A, B), rnnz, RowMap{});
+        return launch_list_rest<false>(h, rows, most, operands_of(A, B), rnnz, RowMap{});
     };
-    auto rowq = [&](int b) { return &info->queue[numeric ? 1 : 0][b][0]; };
+    auto symq = [&](int b) { return &info->queue[0][b][0]; };
     // bin done_bin was already processed: its rows must not be taken again
     const bool done_rows = done_bin > 0 && counts[done_bin] > 0;
     if (!done_rows && (nonempty == 1 || all_group)) {
         const msp_status r =
-            numeric ? launch_numeric(h, plan.spec[last], m, nullptr, A, B, crp, ccol, cval, cnt_out, rowq(last))
-                    : launch_symbolic(h, plan.spec[last], m, nullptr, A, B, rnnz, rowq(last));
+            numeric ? launch_numeric(h, plan.spec[last], m, nullptr, A, B, crp, ccol, cval, cnt_out, last)
+                    : launch_symbolic(h, plan.spec[last], m, nullptr, A, B, rnnz, symq(last));
         return r == MSP_OK ? rest() : r;
     }
     msp_status s = h->perm.ensure((size_t)m * 4);
@@ -854,14 +857,14 @@ static msp_status run_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, co
         first[b] = start;
         start += counts[b];
     }
-    auto launch = [&](int b, unsigned* q) {
-        return numeric ? launch_numeric(h, plan.spec[b], counts[b], perm + first[b], A, B, crp, ccol, cval, cnt_out, q)
-                       : launch_symbolic(h, plan.spec[b], counts[b], perm + first[b], A, B, rnnz, q);
+    auto launch = [&](int b) {
+        return numeric ? launch_numeric(h, plan.spec[b], counts[b], perm + first[b], A, B, crp, ccol, cval, cnt_out, b)
+                       : launch_symbolic(h, plan.spec[b], counts[b], perm + first[b], A, B, rnnz, symq(b));
     };
     const Kind gk = plan.spec[nb].kind;
     int alone = -1;
     if ((gk == Kind::Dense || gk == Kind::Bitmap) && nb != done_bin && counts[nb] >= h->num_cu) {
-        if ((s = launch(nb, rowq(nb))) != MSP_OK) return s;
+        if ((s = launch(nb)) != MSP_OK) return s;
         alone = nb;
     }
     auto todo = [&](int b) { return counts[b] > 0 && b != done_bin && b != alone; };
@@ -891,7 +894,7 @@ static msp_status run_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, co
             if (nwide == 0) --w;                     // worker 0 is the handle's stream
         }
         h->stream = w < 0 ? main_st : h->side[w];
-        s = launch(b, rowq(b));
+        s = launch(b);
     }
     h->stream = main_st;
     // join whatever was forked, also after a failed launch
@@ -1305,6 +1308,16 @@ extern "C" int msp_internal_symbolic_route(long long ncols, long long bnnz, int 
     op.ncols = ncols;
     op.bnnz = bnnz;
     return 1 + (int)msp::symbolic_route(s, op, 160 * 1024);
+}
+
+// For tests of the dispatch: slots of the hash behind the workgroup sort for
+// numeric rows of `nnz` outputs (0: another kernel's).
+extern "C" int msp_internal_numeric_table(int nnz, int hash_scale) {
+    msp_tuning t = msp::default_tuning();
+    t.hash_scale = hash_scale;
+    const msp::BinPlan p = msp::numeric_plan(t, false);
+    const msp::BinSpec& s = p.spec[msp::bin_of(p.table, nnz)];
+    return s.kind == msp::Kind::Block ? s.slots : 0;
 }
 
 // For tests of the numeric kernels' checks: the numeric pass of A B with row

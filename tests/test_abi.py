@@ -50,6 +50,17 @@ def test_only_the_bitmap_bin_takes_the_slab():
     assert route(10 ** 9, 1 << 32, 1024) == 0
 
 
+def test_rows_past_the_sort_hash_in_tables_of_their_size():
+    """Rows of 513 to 4096 outputs whose products merge go to a hash of twice
+    (hash_scale 2: four times) their bin's outputs, not to the largest one."""
+    lib = ctypes.CDLL(binding.LIB_PATH)
+    for nnz, top in [(513, 1024), (1024, 1024), (1025, 2048), (2048, 2048), (2049, 4096), (4096, 4096)]:
+        for scale in (1, 2):
+            assert lib.msp_internal_numeric_table(nnz, scale) == min(8192, top << scale)
+    assert lib.msp_internal_numeric_table(512, 1) == 0
+    assert lib.msp_internal_numeric_table(4097, 1) == 0
+
+
 def test_status_strings_and_null_handle():
     lib = binding.load()
     for code in range(9):

@@ -8,7 +8,7 @@ import ctypes
 import numpy as np
 import pytest
 
-from paper_2112_10037_amd import binding, gen
+from paper_2112_10037_amd import binding, gen, learned
 
 from gpu_util import TOL, check_full, check_rows, run, to_dev
 
@@ -356,3 +356,52 @@ def test_counts_that_are_too_high_are_reported(h, total, na, lo, hi, dtype):
         else:
             with pytest.raises(binding.MspError):
                 h.sync()
+
+
+def _pair(monkeypatch, test, h, *args):
+    """The first matrices that an edge case above multiplies."""
+    pairs = []
+    monkeypatch.setitem(globals(), "check_full", lambda h, A, B, **kw: pairs.append((A, B)))
+    test(h, *args)
+    return pairs[0]
+
+
+EDGES = sorted([("row", n) for n in CASES] + [("sort", n) for n in SORT_CASES])
+
+
+@pytest.mark.parametrize("less", [0, 1])
+@pytest.mark.parametrize("kind,name", EDGES)
+def test_edges_by_capacity(h, monkeypatch, kind, name, less):
+    """The edge cases in rooms of exactly the first row's outputs, or one less
+    (rows that do not fit are computed again)."""
+    test = test_row_kernel_edges if kind == "row" else test_sort_kernel_edges
+    A, B = _pair(monkeypatch, test, h, name, np.float64)
+    import oracle
+    ref = oracle.spgemm(A, B)
+    room = int(ref[0][1]) - less
+    pred = binding.Predictor(h, learned.fixed_capacity_params(np.log2(room - 0.5) / 16.0))
+    C, _ = h.spgemm_learned(pred, to_dev(A), to_dev(B))
+    got = C.to_host()
+    oracle.compare(got.row_ptr, got.col, got.val, ref, 1e-12)
+    pred.close()
+
+
+@pytest.mark.parametrize("kind,name,dtype", [(*e, t) for e in EDGES for t in (np.float64, np.float32)]
+                         + [("list", n, np.float32) for n in sorted(LIST_CASES)])
+def test_edges_in_a_batch(h, monkeypatch, kind, name, dtype):
+    """The edge cases as the second problem of a batch, replayed twice."""
+    if kind == "list":
+        A, B = _pair(monkeypatch, test_list_kernel_edges, h, name)
+    else:
+        test = test_row_kernel_edges if kind == "row" else test_sort_kernel_edges
+        A, B = _pair(monkeypatch, test, h, name, dtype)
+    import oracle
+    A0 = gen.erdos_renyi(130, 90, 5, seed=91, dtype=dtype)
+    B0 = gen.erdos_renyi(90, 500, 4, seed=92, dtype=dtype)
+    plan = binding.Batch(h, binding.PackedBatch.from_host([A0, A]), binding.PackedBatch.from_host([B0, B]))
+    for _ in range(2):
+        plan.execute()
+        for p, (x, y) in enumerate([(A0, B0), (A, B)]):
+            got = plan.result(p).to_host()
+            oracle.compare(got.row_ptr, got.col, got.val, oracle.spgemm(x, y), TOL[np.dtype(dtype)])
+    plan.close()
