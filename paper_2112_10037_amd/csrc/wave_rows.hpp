@@ -604,23 +604,31 @@ k_num_row(Work wk,
                         }
                     lds_fence();
                     int n = 0;
-                    // each column's sum at its rank
-                    for (int j0 = 0; j0 < total; j0 += 64) {
-                        const int j = j0 + lane;
-                        int x = -1;
-                        bool head = false;
-                        if (j < total) {
-                            x = sc[j];
-                            head = j == 0 || sc[j - 1] != x;
+                    if (T <= 512 && !cnt_out && total == expect) {    // no two products in one column
+                        n = total;
+                        for (int j = lane; j < total; j += 64) {
+                            ccol[rp + j] = sc[j];
+                            cval[rp + j] = (VT)sv[j];
                         }
-                        const uint64_t heads = __ballot(head);
-                        const int rank = lanes_below(heads, n);
-                        n += __builtin_popcountll(heads);
-                        if (head && rank < expect) {
-                            double y = sv[j];
-                            for (int i = j + 1; i < total && sc[i] == x; ++i) y += sv[i];
-                            ccol[rp + rank] = x;
-                            cval[rp + rank] = (VT)y;
+                    } else {
+                        // each column's sum at its rank
+                        for (int j0 = 0; j0 < total; j0 += 64) {
+                            const int j = j0 + lane;
+                            int x = -1;
+                            bool head = false;
+                            if (j < total) {
+                                x = sc[j];
+                                head = j == 0 || sc[j - 1] != x;
+                            }
+                            const uint64_t heads = __ballot(head);
+                            const int rank = lanes_below(heads, n);
+                            n += __builtin_popcountll(heads);
+                            if (head && rank < expect) {
+                                double y = sv[j];
+                                for (int i = j + 1; i < total && sc[i] == x; ++i) y += sv[i];
+                                ccol[rp + rank] = x;
+                                cval[rp + rank] = (VT)y;
+                            }
                         }
                     }
                     if (cnt_out) {
