@@ -18,8 +18,8 @@ namespace msp {
 // a bucket, go into the bin's own part of fb_list (count and place in fb) for a
 // hash kernel with a table of the bin's size: rows whose products merge several
 // to an output can be most of a bin.  Such rows cost little here, so they are
-// listed kLeft at a time and drawn `per` at a time (60,000 of them 711 us one by
-// one).
+// listed kLeft at a time and drawn several at a time (60,000 of them 711 us one
+// by one).
 //
 // The walk finds a product's A entry as the row kernels of one wave do: a mark
 // per entry at its last product, counted below the lane.
@@ -36,6 +36,71 @@ constexpr int kSortBucket = 256;
 constexpr int kSortR = 8;
 constexpr int kLeft = 16;
 
+// The rows of a workgroup of the sort, its first wave's, in LDS: the slots drawn from
+// the queue and the rows to list.  The draws of one queue follow each other at
+// some 12 ns, more than a cheap row takes: a draw takes half of the
+// workgroup's share of what is left, up to eight slots, so that the last rows
+// still go one by one (a fixed eighth of the whole share made the last rows of a
+// sparse power-law matrix's 2049- to 4096-output bin wait, 1163 -> 1495 us).
+// The pointers are kept here too, out of the kernel's registers.
+struct SortRows {
+    unsigned* q;
+    int32_t* list;
+    int* count;
+    long long at;
+    int rows, held, nleft;
+    int left[kLeft];
+
+    __device__ __forceinline__ void open(unsigned* q_, int rows_, int32_t* list_, int* count_, long long slot,
+                                         long long* s_slot) {
+        q = q_;
+        rows = rows_;
+        at = 0;
+        list = list_;
+        count = count_;
+        held = nleft = 0;
+        draw(slot, s_slot);
+    }
+    __device__ __forceinline__ void draw(long long slot, long long* s_slot) {
+        if (!q) {
+            *s_slot = slot + gridDim.x;
+            return;
+        }
+        int n = held;
+        long long to = at;
+        if (n == 0) {
+            // (what is left at this workgroup's last draw)
+            n = (int)min(8ll, (rows - to) / (2 * (long long)gridDim.x));
+            n = max(n, 1);
+            to = (long long)atomicAdd(q, (unsigned)n);
+        }
+        *s_slot = to;
+        at = to + 1;
+        held = n - 1;
+    }
+    // (the whole first wave)
+    __device__ __forceinline__ void leave(int row, int lane) {
+        const int n = nleft;
+        if (lane == 0) {
+            left[n] = row;
+            nleft = n + 1;
+        }
+        if (n + 1 == kLeft) flush(lane);
+    }
+    __device__ __forceinline__ void flush(int lane) {
+        lds_fence();
+        const int n = nleft;
+        int to = 0;
+        if (lane == 0 && n > 0) {
+            to = atomicAdd(count, n);
+            nleft = 0;
+        }
+        to = __builtin_amdgcn_readfirstlane(to);
+        if (lane < n) list[to + lane] = left[lane];
+        lds_fence();
+    }
+};
+
 template <int BS, int R>
 struct SortCfg {
     static constexpr int kCap = BS * R;                  // products
@@ -51,7 +116,7 @@ k_num_sort(Work wk,
            const int64_t* __restrict__ arp, const int32_t* __restrict__ acol, const VT* __restrict__ aval,
            const int64_t* __restrict__ brp, const int32_t* __restrict__ bcol, const VT* __restrict__ bval,
            const int64_t* __restrict__ crp, int32_t* __restrict__ ccol, VT* __restrict__ cval,
-           int32_t* __restrict__ cnt_out, DevInfo* info, RowMap mp, unsigned* q, int per,
+           int32_t* __restrict__ cnt_out, DevInfo* info, RowMap mp, unsigned* q,
            int32_t* __restrict__ fb_list, int* fb) {
     using Cfg = SortCfg<BS, R>;
     constexpr int CAP = Cfg::kCap, NB = Cfg::kBuckets, NW = BS / 64, WORDS = Cfg::kWords;
@@ -66,7 +131,7 @@ k_num_sort(Work wk,
     VT* const av = reinterpret_cast<VT*>(area + (Cfg::kEntries + 1) * 8);
     __shared__ unsigned long long mark[WORDS];
     __shared__ long long s_slot;
-    __shared__ int s_left[kLeft];                        // rows to list (thread 0's)
+    __shared__ SortRows rows;
     __shared__ int s_sum[NW], s_some[NW], s_min[NW], s_max[NW], s_tot[NW], s_most[NW], s_heads[NW];
     const uint16_t* const cs = reinterpret_cast<const uint16_t*>(cw);
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -102,19 +167,10 @@ k_num_sort(Work wk,
     // (a batch's bin has its place in the row list on the device)
     const int place = wk.dev ? wk.dev[1] : 0;
     fb_list += place;
-    if (blockIdx.x == 0 && tid == 0) fb[1] = place;
-    int nleft = 0;
-    auto leave = [&](int row) {                            // thread 0
-        if (row >= 0) s_left[nleft++] = row;
-        if (nleft == kLeft || (row < 0 && nleft > 0)) {
-            const int to = atomicAdd(&fb[0], nleft);
-            for (int i = 0; i < nleft; ++i) fb_list[to + i] = s_left[i];
-            nleft = 0;
-        }
-    };
-
-    SlotRun run;
-    run.draw(q, per, (long long)blockIdx.x - gridDim.x, &s_slot);
+    if (tid == 0) {
+        if (blockIdx.x == 0) fb[1] = place;
+        rows.open(q, nrows_bin, fb_list, fb, (long long)blockIdx.x - gridDim.x, &s_slot);
+    }
     __syncthreads();
     long long slot = s_slot;
     __syncthreads();                                       // (a row may come to the next draw without another)
@@ -171,7 +227,7 @@ k_num_sort(Work wk,
                 }
             }
             const bool takes = na <= Cfg::kEntries && total <= CAP;   // uniform
-            run.draw(q, per, slot, &s_slot);
+            if (tid == 0) rows.draw(slot, &s_slot);
             __syncthreads();
             const long long next = s_slot;
             const bool more = next < nrows_bin;            // uniform
@@ -386,7 +442,7 @@ k_num_sort(Work wk,
                     done = true;
                 }
             }
-            if (!done && tid == 0) leave(row);
+            if (!done && wv == 0) rows.leave(row, lane);
             if (!more) break;
             slot = next;
             cur = nxt;
@@ -397,8 +453,8 @@ k_num_sort(Work wk,
             __syncthreads();                               // the next row writes what this one still reads
         }
     }
-    if (tid == 0) leave(-1);
-    block_slots_done(q);
+    if (wv == 0) rows.flush(lane);
+    block_slots_done(rows.q);
     if (err) atomicOr(&info->err, err);
 }
 

@@ -305,27 +305,6 @@ __device__ __forceinline__ void block_draw(unsigned* q, long long slot, long lon
     if (threadIdx.x == 0) *s_slot = q ? (long long)atomicAdd(q, 1u) : slot + gridDim.x;
 }
 
-// The same with several slots a draw (`per`; 1 without a queue): the draws of
-// one queue follow each other at some 12 ns, more than a cheap row takes.
-// Thread 0 keeps the slots drawn (held of them from `at` on).
-struct SlotRun {
-    long long at = 0;
-    int held = 0;
-    __device__ __forceinline__ void draw(unsigned* q, int per, long long slot, long long* s_slot) {
-        if (threadIdx.x != 0) return;
-        if (!q) {
-            *s_slot = slot + gridDim.x;
-            return;
-        }
-        if (held == 0) {
-            at = (long long)atomicAdd(q, (unsigned)per);
-            held = per;
-        }
-        *s_slot = at++;
-        --held;
-    }
-};
-
 // A workgroup's first slot by the same draws.  Every wave has read the ticket
 // when this returns: a row that takes no turn of the caller's loops (an empty
 // one) comes to the next draw without another barrier.

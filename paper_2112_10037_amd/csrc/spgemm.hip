@@ -523,10 +523,8 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
 #define X(BS)                                                                                              \
     if (s.lanes == BS) {                                                                                   \
         const int grid = group_grid(h, (const void*)k_num_sort<BS, kSortR, VT, BATCH>, rows, 1, BS);      \
-        const int per = std::max(1, std::min(8, rows / (8 * grid)));                                       \
         k_num_sort<BS, kSortR, VT, BATCH><<<grid, BS, 0, st>>>(                                            \
-            wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, ccol, cval, cnt_out, info, mp, rq, per, list, \
-            wk.left);                                                                                      \
+            wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, ccol, cval, cnt_out, info, mp, rq, list, wk.left); \
         const msp_status r = launch_check("k_num_sort");                                                   \
         if (r != MSP_OK) return r;                                                                         \
     }
