@@ -662,7 +662,9 @@ k_num_row(Work wk,
 // registers; within 32 kRowWords columns their bits are counted in a bitmap
 // of the span, else every product joins the list of its column's hash slot
 // (one LDS exchange) and counts unless an earlier member has its column.
-// Other rows: an LDS hash of T keys.
+// Other rows: a bitmap of the span, products taken as they come, when they have at most 64 A entries and the span is narrow; else an LDS hash of T
+// keys.  (With the hash for both, 60,000 rows of 2500 products over 950 columns
+// took 558 us, 405 in the kernel before, which had the bitmap.)
 //
 // Bound by LDS and instruction issue, as k_num_row.  The lists need one
 // returning LDS operation a product and then only reads, where a hash of
@@ -831,9 +833,25 @@ k_sym_row(Work wk,
                 lds_fence();
             }
         } else {
+            // The first and last columns of the B rows bound the span of a row
+            // of at most 64 A entries: a bitmap of it when it is narrow (B's
+            // width bounds these rows, so it is), else a hash.
+            int mn = 0x7fffffff, mx = -1;
+            if (cur.a1 - cur.a0 <= 64) {
+                if (cur.a0 + lane < cur.a1 && b1 > b0) {
+                    mn = bcol[b0];
+                    mx = bcol[b1 - 1];
+                }
+                mn = wave_least(mn);
+                mx = wave_most(mx);
+            }
             load_bounds(nxt, kn, &b0n, &b1n);
-            for (int i = lane; i < T / 4; i += 64)
-                reinterpret_cast<int4*>(keys)[i] = make_int4(kEmpty, kEmpty, kEmpty, kEmpty);
+            const bool narrow = mx >= mn && (long long)mx - mn < 32 * kRowWords;     // wave-uniform
+            uint32_t* const bm = reinterpret_cast<uint32_t*>(keys);
+            const int nwd = narrow ? ((mx - mn) >> 5) + 1 : 0;
+            const int clear = narrow ? (nwd + 3) >> 2 : T / 4, empty = narrow ? 0 : kEmpty;
+            for (int i = lane; i < clear; i += 64)
+                reinterpret_cast<int4*>(keys)[i] = make_int4(empty, empty, empty, empty);
             lds_fence();
             int full = 0;
             for (long long c0 = cur.a0; c0 < cur.a1; c0 += 64) {
@@ -850,14 +868,36 @@ k_sym_row(Work wk,
                 s_bst[lane] = bst - (incl - len);
                 lds_fence();
                 const int nact = (int)((cur.a1 - c0) < 64 ? (cur.a1 - c0) : 64);
+                // (GS products a lane in flight)
                 int t = -1;                          // owner of q: one search, then it only moves forward
-                for (long long q = lane; q < all; q += 64) {
-                    if (t < 0) t = owner_search(s_off, nact, q);
-                    else while (s_off[t] <= q) ++t;
-                    cnt += hash_insert_key<T>(keys, bcol[s_bst[t] + q], &full);
+                for (long long q0 = lane; q0 < all; q0 += 64 * GS) {
+                    int32_t j[GS];
+#pragma unroll
+                    for (int u = 0; u < GS; ++u) {
+                        const long long q = q0 + 64 * u;
+                        j[u] = -1;
+                        if (q < all) {
+                            if (t < 0) t = owner_search(s_off, nact, q);
+                            else while (s_off[t] <= q) ++t;
+                            j[u] = bcol[s_bst[t] + q];
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < GS; ++u) {
+                        if (j[u] < 0) continue;
+                        if (narrow) {
+                            // (in the span for canonical B; unsorted rows, which
+                            // the input contract excludes, stay in bounds)
+                            const int d = j[u] - mn;
+                            if ((unsigned)d < (unsigned)(nwd << 5)) atomicOr(&bm[d >> 5], 1u << (d & 31));
+                        } else {
+                            cnt += hash_insert_key<T>(keys, j[u], &full);
+                        }
+                    }
                 }
                 lds_fence();
             }
+            for (int i = lane; i < nwd; i += 64) cnt += __builtin_popcount(bm[i]);
             if (full) err |= kErrProbe;
         }
         cnt = __builtin_amdgcn_readlane(wave_scan(cnt), 63);

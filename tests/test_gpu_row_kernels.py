@@ -405,3 +405,27 @@ def test_edges_in_a_batch(h, monkeypatch, kind, name, dtype):
             got = plan.result(p).to_host()
             oracle.compare(got.row_ptr, got.col, got.val, oracle.spgemm(x, y), TOL[np.dtype(dtype)])
     plan.close()
+
+
+@pytest.mark.parametrize("ncols", [33, 64, 250, 512, 1024])
+def test_symbolic_rows_bounded_by_the_width(h, ncols):
+    """Rows of at most 64 A entries with more products than columns, in spans
+    that start and end anywhere, beside rows of more entries."""
+    rng = np.random.default_rng(ncols)
+    rows = []
+    for _ in range(500):                             # B rows of a stretch of the columns, all of it or single ones
+        lo = int(rng.integers(0, ncols))
+        hi = int(rng.integers(lo, ncols)) + 1
+        n = int(rng.choice([1, hi - lo, (hi - lo + 1) // 2]))
+        rows.append(lo + np.sort(rng.permutation(hi - lo)[:n]))
+    rows[7] = rows[8] = rows[499] = np.zeros(0, np.int64)
+    B = _csr(rows, ncols, rng, np.float64)
+    A = gen.erdos_renyi(900, 500, rng.choice([1, 2, 30, 63, 64, 65, 128], size=900), seed=43)
+    check_full(h, A, B)
+    check_full(h, A, B, tuning=(1, 0, 4096, 1024, -1))
+    import oracle
+    plan = binding.Batch(h, *[binding.PackedBatch.from_host([x, x]) for x in (A, B)])
+    plan.execute()
+    got = plan.result(1).to_host()
+    oracle.compare(got.row_ptr, got.col, got.val, oracle.spgemm(A, B), 1e-12)
+    plan.close()
