@@ -3330,7 +3330,6 @@ __device__ __forceinline__ int bits_below(unsigned long long word, int b) {
 // and the odd word stride of the ranks, 39.3 ms.  A sparse power-law matrix of
 // 2^20 rows: 10.9 -> 8.2 ms.  Listing columns with the ranks, a run of words
 // a thread, took 46.7 ms: a skewed row's bits lie in few threads' words.
-constexpr int kWinBS = 512;                    // threads of the windowed kernel (two workgroups per CU)
 constexpr int kWinRU = 4;                      // 64-product steps per window of a wave's walk
 constexpr bool kWinSwizzle = true;             // accumulator index swizzled within 32-entry groups
 

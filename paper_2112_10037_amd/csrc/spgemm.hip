@@ -132,15 +132,27 @@ BinPlan numeric_plan(const msp_tuning& t, bool force_spill, bool rule) {
 constexpr int kLdsReserve = 18 * 1024;     // static LDS of k_sym_bitmap<1024>
 constexpr int kLdsReserveHalf = 10 * 1024; // and of k_sym_bitmap<512>
 constexpr int kSliceReserve = 27 * 1024;   // static LDS of k_num_slice<kSliceBS>
-constexpr int kWinReserve = 16 * 1024;     // static LDS of k_num_win<kWinBS>
-constexpr int kWinPerCU = 2;               // workgroups of k_num_win per compute unit
+constexpr int kWinReserve = 27 * 1024;     // static LDS of k_num_win<1024>
+constexpr int kWinReserveHalf = 16 * 1024; // and of k_num_win<512>, two of which share a compute unit
 
-// Dynamic LDS of the windowed global-bin kernel (a share of the compute
-// unit's LDS for each of its workgroups), or 0 when a window of full
-// density would not fit.
-static int win_lds(const msp_handle* h) {
+// The kernels that take one long row a workgroup share a compute unit between
+// two workgroups of 512 threads, so that one row's passes overlap the other's
+// gathers, from so many rows a compute unit on; fewer rows get 1024 threads and
+// the whole LDS each, as the longest ones set the time.  k_num_win, us with 512
+// and with 1024 threads, by rows: 30 (the power-law matrix of 171,000 rows) 196
+// and 99; 301 140 and 91; 1505 204 and 171; 5127 528 and 507; R-MAT graphs of
+// 2^16 and 2^17 vertices, 16 edges each, 1395 and 1442, 3864 and 4169.
+// k_sym_bitmap on the same: 28 and 21; 48 and 29; 123 and 114; 217 and 209; 337
+// and 384; 817 and 958.
+constexpr int kFewRows = 16;
+static bool two_per_cu(int rows, int num_cu) { return rows > kFewRows * num_cu; }
+
+// Dynamic LDS of the windowed global-bin kernel (half: a half of the compute
+// unit's), or 0 when a window of full density would not fit.
+static int win_lds(const msp_handle* h, bool half) {
     // (a slice then holds fewer than 2^16 outputs: its word ranks are 16-bit)
-    const int dyn = std::min(h->lds_per_block / kWinPerCU - kWinReserve, 65535 * kWinOut);
+    const int share = half ? h->lds_per_block / 2 - kWinReserveHalf : h->lds_per_block - kWinReserve;
+    const int dyn = std::min(share, 65535 * kWinOut);
     return dyn >= kWinFixed + kWinOut * kWin + kWinSlack ? dyn : 0;
 }
 
@@ -262,9 +274,11 @@ msp_status configure_kernels(msp_handle* h) {
             return hip_fail(e, "hipFuncSetAttribute(MaxDynamicSharedMemorySize)");
         }
     }
-    const int dyn_win = win_lds(h);
-    if (dyn_win > 0) {
-        void* win_fns[] = {(void*)k_num_win<kWinBS, float>, (void*)k_num_win<kWinBS, double>};
+    for (const bool half : {false, true}) {
+        const int dyn_win = win_lds(h, half);
+        if (dyn_win <= 0) continue;
+        void* win_fns[] = {half ? (void*)k_num_win<512, float> : (void*)k_num_win<1024, float>,
+                           half ? (void*)k_num_win<512, double> : (void*)k_num_win<1024, double>};
         for (void* f : win_fns) {
             hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_win);
             if (e != hipSuccess) {
@@ -323,13 +337,13 @@ enum class SymRoute { List, HalfBitmap, Bitmap, Slab };
 // bitmap fits the LDS (on an R-MAT graph of 2^19 vertices its rows of 8193 to
 // 16,384 products take 2968 us in the lists of 1024 threads, which fill the LDS
 // of a compute unit, 1.3 ms in the bitmap).  The bitmap is whole windows of
-// LDS; two workgroups a compute unit while two bitmaps fit, so that one row's
-// passes over its bitmap overlap the other's gathers.
-static SymRoute symbolic_route(const BinSpec& s, const Operands& op, int lds) {
+// LDS; two workgroups a compute unit (`two`: there are rows for them) while two
+// bitmaps fit.
+static SymRoute symbolic_route(const BinSpec& s, const Operands& op, int lds, bool two) {
     const long long bytes = bitmap_bytes(op.ncols);
     const bool fits = bytes <= lds - kLdsReserve;
     if (s.kind == Kind::Block && (s.lanes * s.slots <= 8192 || !fits)) return SymRoute::List;
-    if (bytes <= lds / 2 - kLdsReserveHalf) return SymRoute::HalfBitmap;
+    if (two && bytes <= lds / 2 - kLdsReserveHalf) return SymRoute::HalfBitmap;
     return fits ? SymRoute::Bitmap : SymRoute::Slab;
 }
 
@@ -375,7 +389,7 @@ static msp_status launch_symbolic_t(msp_handle* h, const BinSpec& s, Work wk, in
         MSP_SYM_ROW_SHAPES(X)
 #undef X
     } else if (s.kind == Kind::Block || s.kind == Kind::Bitmap) {
-        const SymRoute route = symbolic_route(s, op, h->lds_per_block);
+        const SymRoute route = symbolic_route(s, op, h->lds_per_block, two_per_cu(rows, h->num_cu));
         if (route == SymRoute::List) {
             // rows past the lists go to the bounds array, which the symbolic pass
             // has read by then; launch_list_rest takes them
@@ -442,10 +456,12 @@ static msp_status launch_window_bin(msp_handle* h, Work wk, int rows, const Oper
                                                   h->win_bslot.as<int32_t>(), h->win_wpos.as<int32_t>(), info);
         if ((r = launch_check("k_bwin_index")) != MSP_OK) return r;
     }
-    const int lds = win_lds(h);
-    const int grid = std::max(1, std::min(rows, kWinPerCU * h->num_cu));
+    const bool half = two_per_cu(rows, h->num_cu);
+    const int lds = win_lds(h, half);
+    const int grid = std::max(1, std::min(rows, (half ? 2 : 1) * h->num_cu));
     hipEvent_t ev = h->prof.sub_begin(MSP_PHASE_GLOBAL_BIN, st);
-    k_num_win<kWinBS, VT><<<grid, kWinBS, (size_t)lds, st>>>(
+    const auto fn = half ? k_num_win<512, VT> : k_num_win<1024, VT>;
+    fn<<<grid, half ? 512 : 1024, (size_t)lds, st>>>(
         wk, nw, op.arp, op.acol, (const VT*)op.aval, op.brp, op.bcol, (const VT*)op.bval,
         h->win_bslot.as<int32_t>(), h->win_wpos.as<int32_t>(), rec, crp, ccol, cval, (long long)lds,
         h->win_fb.as<int32_t>(), info, wk.rowq);
@@ -982,7 +998,7 @@ msp_status device_error(int err) {
 static msp_status setup_records(msp_handle* h, const msp_csr* A, const msp_csr* B, const BinPlan& sp,
                                 const int* counts, const BinPlan* np) {
     h->cur_rec = WinRec{};
-    if (!np || win_lds(h) == 0) return MSP_OK;
+    if (!np || win_lds(h, true) == 0 || win_lds(h, false) == 0) return MSP_OK;
     const long long nw = (B->ncols + kWin - 1) / kWin;
     if (nw <= 0 || nw > kWinMaxNw) return MSP_OK;
     const int thresh = np->table.nb > 1 ? np->table.umax[np->table.nb - 1] : 0;
@@ -1296,16 +1312,22 @@ extern "C" msp_status msp_share_stats_get(msp_handle* h, msp_share_stats* out) {
 extern "C" long long msp_internal_summary_fallbacks(const msp_handle* h) { return h ? h->summary_fallbacks : -1; }
 
 // For tests of the dispatch (no device needed): what takes symbolic rows of
-// `bound` outputs at most, by the default tuning on a compute unit of 160 KB
-// LDS (0: a smaller kernel, else 1 + SymRoute).
-extern "C" int msp_internal_symbolic_route(long long ncols, long long bnnz, int bound) {
+// `bound` outputs at most, more (`many`) or fewer than the compute units, by the
+// default tuning on a compute unit of 160 KB LDS (0: a smaller kernel, else 1 +
+// SymRoute).
+extern "C" int msp_internal_symbolic_route(long long ncols, long long bnnz, int bound, int many) {
     const msp::BinPlan p = msp::symbolic_plan(msp::default_tuning(), false);
     const msp::BinSpec& s = p.spec[msp::bin_of(p.table, bound)];
     if (s.kind != msp::Kind::Block && s.kind != msp::Kind::Bitmap) return 0;
     msp::Operands op{};
     op.ncols = ncols;
     op.bnnz = bnnz;
-    return 1 + (int)msp::symbolic_route(s, op, 160 * 1024);
+    return 1 + (int)msp::symbolic_route(s, op, 160 * 1024, many != 0);
+}
+
+// For tests of the dispatch: threads a row of the global bin gets among `rows`.
+extern "C" int msp_internal_threads_of_long_rows(int rows, int num_cu) {
+    return msp::two_per_cu(rows, num_cu) ? 512 : 1024;
 }
 
 // For tests of the dispatch: slots of the hash behind the workgroup sort for

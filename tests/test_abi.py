@@ -39,15 +39,25 @@ def test_only_the_bitmap_bin_takes_the_slab():
     width and the size of B."""
     lib = ctypes.CDLL(binding.LIB_PATH)
     route = lib.msp_internal_symbolic_route
-    route.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
+    route.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
     LIST, HALF, BITMAP, SLAB = 1, 2, 3, 4
     for nnz in (10 ** 6, (1 << 32) - 1, 1 << 32, 1 << 36):
         for ncols in (20_000, 500_000, 1_000_000, 1_200_000, 2 ** 31 - 1):
-            for bound in (1025, 2048, 2049, 8192):
-                assert route(ncols, nnz, bound) == LIST
-            assert route(ncols, nnz, 16_384) == (LIST if ncols > 1_100_000 else BITMAP if ncols > 570_000 else HALF)
-            assert route(ncols, nnz, 16_385) == (SLAB if ncols > 1_100_000 else BITMAP if ncols > 570_000 else HALF)
-    assert route(10 ** 9, 1 << 32, 1024) == 0
+            for many in (0, 1):
+                for bound in (1025, 2048, 2049, 8192):
+                    assert route(ncols, nnz, bound, many) == LIST
+                wide = ncols > 1_100_000
+                lds = HALF if many and ncols < 570_000 else BITMAP      # few rows get a whole compute unit each
+                assert route(ncols, nnz, 16_384, many) == (LIST if wide else lds)
+                assert route(ncols, nnz, 16_385, many) == (SLAB if wide else lds)
+    assert route(10 ** 9, 1 << 32, 1024, 1) == 0
+
+
+def test_few_long_rows_get_a_compute_unit_each():
+    lib = ctypes.CDLL(binding.LIB_PATH)
+    for rows in (1, 30, 256, 1505, 4096):
+        assert lib.msp_internal_threads_of_long_rows(rows, 256) == 1024
+    assert lib.msp_internal_threads_of_long_rows(4097, 256) == 512
 
 
 def test_rows_past_the_sort_hash_in_tables_of_their_size():

@@ -429,3 +429,16 @@ def test_symbolic_rows_bounded_by_the_width(h, ncols):
     got = plan.result(1).to_host()
     oracle.compare(got.row_ptr, got.col, got.val, oracle.spgemm(A, B), 1e-12)
     plan.close()
+
+
+@pytest.mark.parametrize("rows", [1, 40, 4200])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_global_bin_with_few_and_many_rows(h, rows, dtype):
+    """Both shapes of the window kernel and of the symbolic bitmap: rows of some
+    19,000 products and 15,000 outputs over 50,000 columns, in several slices."""
+    B = gen.erdos_renyi(500, 50_000, 300, seed=71, dtype=dtype)
+    A = gen.erdos_renyi(rows, 500, 64, seed=72, dtype=dtype)
+    C = run(h, A, B)
+    import oracle
+    assert np.array_equal(np.diff(C.row_ptr.cpu().numpy()), oracle.row_nnz(A, B))
+    check_rows(C, A, B, np.unique(np.linspace(0, rows - 1, 25).astype(int)))
