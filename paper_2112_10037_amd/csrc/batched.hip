@@ -396,7 +396,7 @@ static msp_status run_stage(msp_batch* b, int si, bool eager) {
         for (int bn = 1; bn <= S.np.table.nb; ++bn) {
             if (!((S.num_planned >> bn) & 1u)) continue;
             Work wk{h->perm.as<int32_t>(), 0, wnum + 2 * bn, queue(bn), b->queue_rows};
-            wk.left = &info->sort_fb[bn][0];
+            wk.left = &info->left[bn];
             if ((s = launch_numeric_bin<true>(h, S.np.spec[bn], wk, S.num_rows[bn], S.op, S.crp.as<int64_t>(), ccol,
                                               cval, nullptr, S.mp)) != MSP_OK)
                 return s;

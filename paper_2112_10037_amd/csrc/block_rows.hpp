@@ -15,11 +15,9 @@ namespace msp {
 // a skewed matrix's full buckets hold up few waves.  Sums over equal columns,
 // now neighbours, go out in order.  A row of one nonempty B row is its copy,
 // scaled.  Rows past those limits, or with more than kSortBucket products in
-// a bucket, go into the bin's own part of fb_list (count and place in fb) for a
-// hash kernel with a table of the bin's size: rows whose products merge several
-// to an output can be most of a bin.  Such rows cost little here, so they are
-// listed kLeft at a time and drawn several at a time (60,000 of them 711 us one
-// by one).
+// a bucket, are left to a hash kernel with a table of the bin's size: rows whose
+// products merge several to an output can be most of a bin.  left_of[row] says
+// which (1 or 0), *left how many.
 //
 // The walk finds a product's A entry as the row kernels of one wave do: a mark
 // per entry at its last product, counted below the lane.
@@ -34,30 +32,29 @@ namespace msp {
 // workgroups too 1139, 765 and 524 us.
 constexpr int kSortBucket = 256;
 constexpr int kSortR = 8;
-constexpr int kLeft = 16;
 
-// The rows of a workgroup of the sort, its first wave's, in LDS: the slots drawn from
-// the queue and the rows to list.  The draws of one queue follow each other at
-// some 12 ns, more than a cheap row takes: a draw takes half of the
-// workgroup's share of what is left, up to eight slots, so that the last rows
-// still go one by one (a fixed eighth of the whole share made the last rows of a
-// sparse power-law matrix's 2049- to 4096-output bin wait, 1163 -> 1495 us).
-// The pointers are kept here too, out of the kernel's registers.
+// The slots a workgroup of the sort draws from the row queue, thread 0's, in
+// LDS.  The draws of one queue follow each other at some 12 ns, more than a
+// row that the sort leaves takes (60,000 of them 711 us, drawn one by one): a
+// draw takes half of the workgroup's share of what is left, up to eight slots,
+// so that the last rows still go one by one (a fixed eighth of the whole share
+// made the last rows of a sparse power-law matrix's 2049- to 4096-output bin
+// wait, 1163 -> 1495 us).  The pointers are kept here too, out of the kernel's
+// registers.
 struct SortRows {
     unsigned* q;
-    int32_t* list;
-    int* count;
+    int32_t* left_of;
+    int* left;
     long long at;
     int rows, held, nleft;
-    int left[kLeft];
 
-    __device__ __forceinline__ void open(unsigned* q_, int rows_, int32_t* list_, int* count_, long long slot,
+    __device__ __forceinline__ void open(unsigned* q_, int rows_, int32_t* left_of_, int* left_, long long slot,
                                          long long* s_slot) {
         q = q_;
         rows = rows_;
         at = 0;
-        list = list_;
-        count = count_;
+        left_of = left_of_;
+        left = left_;
         held = nleft = 0;
         draw(slot, s_slot);
     }
@@ -78,26 +75,12 @@ struct SortRows {
         at = to + 1;
         held = n - 1;
     }
-    // (the whole first wave)
-    __device__ __forceinline__ void leave(int row, int lane) {
-        const int n = nleft;
-        if (lane == 0) {
-            left[n] = row;
-            nleft = n + 1;
-        }
-        if (n + 1 == kLeft) flush(lane);
+    __device__ __forceinline__ void close(int row, bool done) {
+        left_of[row] = !done;
+        nleft += !done;
     }
-    __device__ __forceinline__ void flush(int lane) {
-        lds_fence();
-        const int n = nleft;
-        int to = 0;
-        if (lane == 0 && n > 0) {
-            to = atomicAdd(count, n);
-            nleft = 0;
-        }
-        to = __builtin_amdgcn_readfirstlane(to);
-        if (lane < n) list[to + lane] = left[lane];
-        lds_fence();
+    __device__ __forceinline__ void finish() {
+        if (nleft > 0) atomicAdd(left, nleft);
     }
 };
 
@@ -117,7 +100,7 @@ k_num_sort(Work wk,
            const int64_t* __restrict__ brp, const int32_t* __restrict__ bcol, const VT* __restrict__ bval,
            const int64_t* __restrict__ crp, int32_t* __restrict__ ccol, VT* __restrict__ cval,
            int32_t* __restrict__ cnt_out, DevInfo* info, RowMap mp, unsigned* q,
-           int32_t* __restrict__ fb_list, int* fb) {
+           int32_t* left_of, int* left) {
     using Cfg = SortCfg<BS, R>;
     constexpr int CAP = Cfg::kCap, NB = Cfg::kBuckets, NW = BS / 64, WORDS = Cfg::kWords;
     int nrows_bin;
@@ -164,13 +147,7 @@ k_num_sort(Work wk,
         *b1 = brp[k + h.bo + 1];
     };
 
-    // (a batch's bin has its place in the row list on the device)
-    const int place = wk.dev ? wk.dev[1] : 0;
-    fb_list += place;
-    if (tid == 0) {
-        if (blockIdx.x == 0) fb[1] = place;
-        rows.open(q, nrows_bin, fb_list, fb, (long long)blockIdx.x - gridDim.x, &s_slot);
-    }
+    if (tid == 0) rows.open(q, nrows_bin, left_of, left, (long long)blockIdx.x - gridDim.x, &s_slot);
     __syncthreads();
     long long slot = s_slot;
     __syncthreads();                                       // (a row may come to the next draw without another)
@@ -442,7 +419,7 @@ k_num_sort(Work wk,
                     done = true;
                 }
             }
-            if (!done && wv == 0) rows.leave(row, lane);
+            if (tid == 0) rows.close(row, done);
             if (!more) break;
             slot = next;
             cur = nxt;
@@ -453,7 +430,7 @@ k_num_sort(Work wk,
             __syncthreads();                               // the next row writes what this one still reads
         }
     }
-    if (wv == 0) rows.flush(lane);
+    if (tid == 0) rows.finish();
     block_slots_done(rows.q);
     if (err) atomicOr(&info->err, err);
 }

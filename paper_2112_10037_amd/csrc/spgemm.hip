@@ -531,27 +531,27 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
         MSP_NUM_ROW_SHAPES(X)
 #undef X
     } else if (s.kind == Kind::Block) {
-        // rows the sort does not take are listed in the bounds array, which the
-        // numeric pass has no other use for, where the bin's rows are in the row
-        // list; the hash takes them behind it on the same stream (and from the
-        // same row queue, which the sort leaves at zero)
-        int32_t* const list = h->u.as<int32_t>() + (wk.perm ? wk.perm - h->perm.as<int32_t>() : 0);
+        // the rows that the sort leaves are marked in the bounds array, which the
+        // numeric pass has no other use for; the hash takes them behind it on the
+        // same stream, in the bin's order (and from the same row queue, which the
+        // sort leaves at zero)
 #define X(BS)                                                                                              \
     if (s.lanes == BS) {                                                                                   \
         const int grid = group_grid(h, (const void*)k_num_sort<BS, kSortR, VT, BATCH>, rows, 1, BS);      \
         k_num_sort<BS, kSortR, VT, BATCH><<<grid, BS, 0, st>>>(                                            \
-            wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, ccol, cval, cnt_out, info, mp, rq, list, wk.left); \
+            wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, ccol, cval, cnt_out, info, mp, rq,            \
+            h->u.as<int32_t>(), wk.left);                                                                  \
         const msp_status r = launch_check("k_num_sort");                                                   \
         if (r != MSP_OK) return r;                                                                         \
     }
         MSP_NUM_SORT_SHAPES(X)
 #undef X
-        const Work rest{list, 0, wk.left};
 #define X(BS, T)                                                                                           \
     if (s.slots == T) {                                                                                    \
         const int grid = group_grid(h, (const void*)k_num_block<BS, T, VT, BATCH>, rows, 1, BS);          \
-        k_num_block<BS, T, VT, BATCH><<<grid, BS, 0, st>>>(rest, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, \
-                                                           ccol, cval, cnt_out, info, mp, rq);             \
+        k_num_block<BS, T, VT, BATCH><<<grid, BS, 0, st>>>(wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, \
+                                                           ccol, cval, cnt_out, info, mp, rq,              \
+                                                           h->u.as<int32_t>(), wk.left);                   \
         return launch_check("k_num_block");                                                                \
     }
         MSP_NUM_BLOCK_SHAPES(X)
@@ -668,7 +668,7 @@ static msp_status launch_numeric(msp_handle* h, const BinSpec& s, int rows, cons
     DevInfo* info = h->info.as<DevInfo>();
     Work wk{perm, rows, nullptr};
     wk.rowq = &info->queue[1][bin][0];
-    wk.left = &info->sort_fb[bin][0];
+    wk.left = &info->left[bin];
     return launch_numeric_bin<false>(h, s, wk, rows, operands_of(A, B), crp, ccol, cval, cnt_out, RowMap{});
 }
 

@@ -69,9 +69,7 @@ struct DevInfo {
     int fused_other;                      // the fused symbolic pass left rows for other bins
     int win_nrec;                         // window records the symbolic pass made
     int win_fb[2];                        // global-bin rows without a record: {count, 0}
-    // numeric rows the workgroup sort of a bin left to its hash: {count,
-    // place of the bin's list in the bounds array}
-    int sort_fb[kNB][2];
+    int left[kNB];                        // numeric rows that a bin's kernel left to the hash behind it
     int list_fb[2];                       // symbolic rows the workgroup lists left to the bitmap: {count, 0}
     int win_nbs;                          // B rows given a window index
     int win_nbms;                         // rows whose bitmap the symbolic pass stored
@@ -163,7 +161,7 @@ struct Work {
     int* ticket;        // shared work queue of the launch (zero at launch), or null
     int tk;             // rows per ticket
     unsigned* rowq = nullptr;   // row queue of a one-row-per-workgroup kernel (see block_first)
-    int* left = nullptr;        // numeric Block bins: the bin's sort_fb entry
+    int* left = nullptr;        // numeric: the bin's entry of DevInfo::left
 };
 
 __device__ __forceinline__ void work_rows(const Work& w, int* n, const int32_t** perm) {
