@@ -385,9 +385,9 @@ static msp_status run_stage(msp_batch* b, int si, bool eager) {
     }
     auto queue = [&](int bn) { return tick ? tick + bn : nullptr; };
     if (S.num_single >= 0) {
-        if ((s = launch_numeric_bin<true>(h, S.np.spec[S.num_single],
-                                          Work{nullptr, M, wnum + 2 * kNB, queue(S.num_single), b->queue_rows}, M,
-                                          S.op, S.crp.as<int64_t>(), ccol, cval, nullptr, S.mp)) != MSP_OK)
+        Work wk{nullptr, M, wnum + 2 * kNB, queue(S.num_single), b->queue_rows};
+        wk.left = &info->left[S.num_single];
+        if ((s = launch_numeric_bin<true>(h, S.np.spec[S.num_single], wk, M, S.op, S.crp.as<int64_t>(), ccol, cval, nullptr, S.mp)) != MSP_OK)
             return s;
     } else if (S.num_planned) {
         k_scatter<<<(M + 255) / 256, 256, 0, st>>>(M, h->rnnz.as<int32_t>(), S.np.table, &info->num_part[0][0],

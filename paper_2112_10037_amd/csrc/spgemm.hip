@@ -479,6 +479,23 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
     const VT* av = (const VT*)op.aval;
     const VT* bv = (const VT*)op.bval;
     unsigned* rq = BATCH ? nullptr : wk.rowq;         // (the batched graph's kernels keep static slots)
+    // The rows that the bin's kernel leaves are marked in the bounds array, which
+    // the numeric pass has no other use for; the hash takes them behind it on the
+    // same stream, in the bin's order (and from the same row queue, which a kernel
+    // leaves at zero).
+    auto hash_left = [&](int slots) -> msp_status {
+#define X(BS, T)                                                                                           \
+    if (slots == T) {                                                                                      \
+        const int grid = group_grid(h, (const void*)k_num_block<BS, T, VT, BATCH>, rows, 1, BS);          \
+        k_num_block<BS, T, VT, BATCH><<<grid, BS, 0, st>>>(wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, \
+                                                           ccol, cval, cnt_out, info, mp, rq,              \
+                                                           h->u.as<int32_t>(), wk.left);                   \
+        return launch_check("k_num_block");                                                                \
+    }
+        MSP_NUM_BLOCK_SHAPES(X)
+#undef X
+        return fail(MSP_ERR_UNSUPPORTED, "no hash of %d slots", slots);
+    };
     if (s.kind == Kind::Merge) {
         const bool small = op.bnnz < INT32_MAX;     // 32-bit positions into B
 #define MSP_MERGE(KK, IT, SH)                                                                            \
@@ -525,16 +542,14 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
     if (s.lanes == 64 && s.slots == T) {                                                                   \
         const int grid = group_grid(h, (const void*)k_num_row<T, VT, BATCH>, rows, 1, 64);                \
         k_num_row<T, VT, BATCH><<<grid, 64, 0, st>>>(wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp,   \
-                                                     ccol, cval, cnt_out, info, mp);                      \
-        return launch_check("k_num_row");                                                                  \
+                                                     ccol, cval, cnt_out, info, mp, h->u.as<int32_t>(),   \
+                                                     wk.left);                                             \
+        const msp_status r = launch_check("k_num_row");                                                    \
+        return r != MSP_OK || T <= 512 ? r : hash_left(T);                                                 \
     }
         MSP_NUM_ROW_SHAPES(X)
 #undef X
     } else if (s.kind == Kind::Block) {
-        // the rows that the sort leaves are marked in the bounds array, which the
-        // numeric pass has no other use for; the hash takes them behind it on the
-        // same stream, in the bin's order (and from the same row queue, which the
-        // sort leaves at zero)
 #define X(BS)                                                                                              \
     if (s.lanes == BS) {                                                                                   \
         const int grid = group_grid(h, (const void*)k_num_sort<BS, kSortR, VT, BATCH>, rows, 1, BS);      \
@@ -546,16 +561,7 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
     }
         MSP_NUM_SORT_SHAPES(X)
 #undef X
-#define X(BS, T)                                                                                           \
-    if (s.slots == T) {                                                                                    \
-        const int grid = group_grid(h, (const void*)k_num_block<BS, T, VT, BATCH>, rows, 1, BS);          \
-        k_num_block<BS, T, VT, BATCH><<<grid, BS, 0, st>>>(wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp, \
-                                                           ccol, cval, cnt_out, info, mp, rq,              \
-                                                           h->u.as<int32_t>(), wk.left);                   \
-        return launch_check("k_num_block");                                                                \
-    }
-        MSP_NUM_BLOCK_SHAPES(X)
-#undef X
+        return hash_left(s.slots);
     } else if (s.kind == Kind::Dense) {
         const long long n = op.ncols;
         if constexpr (!BATCH) {

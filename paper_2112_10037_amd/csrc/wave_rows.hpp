@@ -282,7 +282,12 @@ constexpr int kRowStep = 4;
 // us on the 27-point rows at two, 670 at three, 617 at four); T = 1024, where
 // LDS leaves 11 waves a compute unit, takes 475 us at two and 620 at three
 // with spills.  Two steps between checks instead of four: 1-5% slower.
+//
+// Rows of 257 outputs and more that have past kRowMost products go to a workgroup:
+// a wave hashes 60,000 rows of 6400 products onto 390 outputs in 2147 us, of
+// 25,600 onto 440 in 7480, a workgroup of 256 threads in 2199 and 4616.
 constexpr int kRowBucket = 24;
+constexpr int kRowMost = 8192;
 template <int T>
 struct RowCfg {
     static constexpr int P = T <= 512 ? 512 : 768;            // most products of a wide row
@@ -300,9 +305,11 @@ k_num_row(Work wk,
           const int64_t* __restrict__ arp, const int32_t* __restrict__ acol, const VT* __restrict__ aval,
           const int64_t* __restrict__ brp, const int32_t* __restrict__ bcol, const VT* __restrict__ bval,
           const int64_t* __restrict__ crp, int32_t* __restrict__ ccol, VT* __restrict__ cval,
-          int32_t* __restrict__ cnt_out, DevInfo* info, RowMap mp) {
+          int32_t* __restrict__ cnt_out, DevInfo* info, RowMap mp, int32_t* left_of, int* left) {
     using Cfg = RowCfg<T>;
     constexpr int R = kRowR, OUT = T / 2;
+    constexpr bool LEAVES = T > 512;                // rows past kRowMost products: left (see k_num_block)
+    int nleft = 0;
     constexpr int GS = kRowStep;                    // steps between checks of the row's length
     static_assert(Cfg::P <= 64 * R, "a wide row's products are in registers");
     int nrows_bin;
@@ -643,6 +650,25 @@ k_num_row(Work wk,
         } else {
             load_bounds(nxt, kn, &b0n, &b1n);
         }
+        if constexpr (LEAVES) {
+            bool heavy = false;                     // wave-uniform
+            if (!done) {
+                int n = cur.a0 + lane < cur.a1 ? (int)min(b1 - b0, kRowMost + 1ll) : 0;
+                n = __builtin_amdgcn_readlane(wave_scan(n), 63);
+                for (long long p = cur.a0 + 64; p < cur.a1 && n <= kRowMost; p += 64) {
+                    int x = 0;
+                    if (p + lane < cur.a1) {
+                        const long long kk = acol[p + lane] + cur.bo;
+                        x = (int)min((long long)(brp[kk + 1] - brp[kk]), kRowMost + 1ll);
+                    }
+                    n += __builtin_amdgcn_readlane(wave_scan(x), 63);
+                }
+                heavy = n > kRowMost;
+            }
+            if (lane == 0) left_of[row] = heavy;
+            nleft += heavy;
+            done = done || heavy;
+        }
         if (!done)
             err |= row_hash<T, VT>(cur.a0, cur.a1, cur.bo, expect, rp, row, acol, aval, brp, bcol, bval, ccol, cval,
                                    cnt_out, reinterpret_cast<int32_t*>(area),
@@ -653,6 +679,7 @@ k_num_row(Work wk,
         b0 = b0n;
         b1 = b1n;
     }
+    if (LEAVES && lane == 0 && nleft > 0) atomicAdd(left, nleft);
     if (err) atomicOr(&info->err, err);
 }
 

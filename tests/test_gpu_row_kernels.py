@@ -442,3 +442,38 @@ def test_global_bin_with_few_and_many_rows(h, rows, dtype):
     import oracle
     assert np.array_equal(np.diff(C.row_ptr.cpu().numpy()), oracle.row_nnz(A, B))
     check_rows(C, A, B, np.unique(np.linspace(0, rows - 1, 25).astype(int)))
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("na", [64, 65, 200])
+@pytest.mark.parametrize("total", [8192, 8193, 30_000])
+@pytest.mark.parametrize("alone", [True, False])
+def test_row_kernel_most_products(h, total, na, alone, dtype):
+    """Rows of 257 to 512 outputs on both sides of the products that a wave
+    hashes, in one bin (taken in their natural order) and beside others; plain,
+    by capacity and in a batch."""
+    rng = np.random.default_rng(total + na)
+    arows, brows = [], []
+    for i in range(40):
+        cols = np.sort(rng.permutation(60_000)[:int(rng.integers(300, 500))])
+        first = len(brows)
+        lens = _lengths(min(total, na * 290) if i % 3 else 700, na)
+        brows += [cols[np.sort(rng.permutation(len(cols))[:n])] for n in lens]
+        arows.append(np.arange(first, first + na))
+        arows.append(np.arange(first, first + (0 if alone else 1 + i % 9)))
+    A = _csr(arows, len(brows), rng, dtype)
+    B = _csr(brows, 60_000, rng, dtype)
+    check_full(h, A, B)
+    import oracle
+    ref = oracle.spgemm(A, B)
+    tol = TOL[np.dtype(dtype)]
+    pred = binding.Predictor(h, learned.fixed_capacity_params(np.log2(450) / 16.0))
+    got = h.spgemm_learned(pred, to_dev(A), to_dev(B))[0].to_host()
+    oracle.compare(got.row_ptr, got.col, got.val, ref, tol)
+    pred.close()
+    plan = binding.Batch(h, *[binding.PackedBatch.from_host([x]) for x in (A, B)])
+    for _ in range(2):
+        plan.execute()
+        got = plan.result(0).to_host()
+        oracle.compare(got.row_ptr, got.col, got.val, ref, tol)
+    plan.close()
