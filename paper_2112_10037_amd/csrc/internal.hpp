@@ -39,6 +39,8 @@ struct BinSpec {
                         // BS for Block/Bitmap/Dense
     int slots = 0;      // T (hash slots) for Group and numeric Block; R (products a thread) for symbolic Block
     int share = 0;      // Merge, numeric: rows per batch that share staged B rows (0: off)
+    int many = 0;       // Group: lanes per row of many short rows (0: as few)
+    int umax = 0;       // the bin's bound
 };
 
 struct BinPlan {

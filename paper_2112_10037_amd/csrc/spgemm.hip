@@ -40,6 +40,7 @@ static int next_pow2(int x) {
 static void add_bin(BinPlan& p, int umax, BinSpec s) {
     const int b = p.table.nb;          // bins are appended after bin 0
     p.table.umax[b] = umax;
+    s.umax = umax;
     p.spec[b] = s;
     p.table.nb = b + 1;
 }
@@ -69,7 +70,7 @@ static void add_small_bins(BinPlan& p, const msp_tuning& t, int limit, bool nume
         const int T = next_pow2(umax[i]) << t.hash_scale;
         if (!numeric) {
             if (umax[i] < 64) add_bin(p, umax[i], BinSpec{Kind::Batch, sym_batch_rows(T), T});
-            else if (T <= 2048) add_bin(p, umax[i], BinSpec{Kind::Group, 64, T});
+            else if (T <= 2048) add_bin(p, umax[i], BinSpec{Kind::Group, 64, T, 0, umax[i] == 64 ? 1024 / T : 0});
             else break;
         } else if (T <= 64) {
             const int R = (T == 32 ? (t.group_scale == 0 ? 12 : 8 >> (t.group_scale - 1)) : 8 >> t.group_scale);
@@ -77,7 +78,7 @@ static void add_small_bins(BinPlan& p, const msp_tuning& t, int limit, bool nume
         } else if (T <= 1024) {
             int G = std::min(64, g0[i] << t.group_scale);
             G = std::min(G, T / 2);
-            add_bin(p, umax[i], BinSpec{Kind::Group, G, T});
+            add_bin(p, umax[i], BinSpec{Kind::Group, G, T, 0, umax[i] == 64 ? std::min(64, 32 << t.group_scale) : 0});
         } else {
             break;
         }
@@ -156,21 +157,53 @@ static int win_lds(const msp_handle* h, bool half) {
     return dyn >= kWinFixed + kWinOut * kWin + kWinSlack ? dyn : 0;
 }
 
-#define MSP_NUM_GROUP_SHAPES(X) X(16, 128) X(32, 128)
+#define MSP_NUM_GROUP_SHAPES(X) X(16, 128) X(32, 128) X(32, 256)
 #define MSP_NUM_ROW_SHAPES(X) X(128) X(256) X(512) X(1024)
 #define MSP_SYM_ROW_SHAPES(X) MSP_NUM_ROW_SHAPES(X) X(2048)
 #define MSP_SYM_BATCH_SHAPES(X) X(32, 16) X(64, 16) X(128, 8) X(256, 4)
-// From so many rows the shortest whole-wave bin (128 slots) goes to several
-// rows a wave instead: 200,000 rows of 36 to 56 products take a call of 458 us
-// with a wave a row and 246 with lane groups and batches, 4096 rows of 64
-// products 55 and 84 (few rows are bound by the latency of one, many by the
-// lanes that a short row leaves idle).
-constexpr int kManyRows = 16384;
+// From so many rows the shortest whole-wave bin (33 to 64 outputs) goes to
+// several rows a wave instead (numeric: 32 lanes a row, unless group_scale asks
+// for more; symbolic: 1024 key slots a wave): few rows are bound by the latency
+// of one, many by the lanes that a short row leaves idle.  Rows of 49 products,
+// us of the kernels with a wave a row and several: numeric 8192 rows 18.4 and
+// 13.6 (4096 rows of 64 products 10.3 and 13.7), 16,384 31.8 and 18.3, 65,536
+// 109 and 53; symbolic 8192 11.2 and 14.2, 16,384 14.1 and 16.1, 32,768 24.1
+// and 19.0, 65,536 40 and 29.
+constexpr int kManyRows = 8192;
+constexpr int kManySymRows = 20480;
 static bool symbolic_in_batches(const BinSpec& s, int rows, long long ncols) {
-    // Rows of 256 slots, too, when B's columns are so few that most rows have
+    // Rows of up to 128 products, too, when B's columns are so few that most rows have
     // more products than the wave's registers take: 800,000 rows of 200
     // products over 90 columns 935 us with a wave a row, 373 in batches.
-    return s.kind == Kind::Group && ((s.slots == 128 && rows >= kManyRows) || (s.slots <= 256 && ncols <= s.slots / 2));
+    return s.kind == Kind::Group && ((s.many > 0 && rows >= kManySymRows) || (s.slots <= 256 && ncols <= s.umax));
+}
+// Lanes of a numeric Group bin's row among `rows`.
+static int numeric_lanes(const BinSpec& s, int rows) {
+    return s.many > 0 && rows >= kManyRows ? s.many : s.lanes;
+}
+// The one bin whose kernel takes every row of a phase in its natural order, with
+// no row list, or 0: the only bin that has rows (but done_bin), or the last of
+// small bins alone, whose larger tables take the smaller bins' rows too.  Not so
+// when the short rows, which share waves in a kernel of their own, are so many
+// that it pays for the row lists (of 49 products, with 1% of 140: 200,000 rows
+// 487 us a call together, 388 apart; 20,000 rows 110 and 124), nor for the
+// numeric 1024-slot kernel, which leaves few waves a compute unit (with 1% of 315
+// products: 200,000 rows 628 us together, 398 apart).
+constexpr int kManyApart = 65536;
+static int single_bin(const BinPlan& plan, const int* counts, bool numeric, int done_bin) {
+    int nonempty = 0, last = 0;
+    bool small = true;
+    for (int b = 1; b <= plan.table.nb; ++b) {
+        if (counts[b] == 0 || b == done_bin) continue;
+        const BinSpec& s = plan.spec[b];
+        ++nonempty;
+        last = b;
+        small = small && (s.kind == Kind::Batch || (s.kind == Kind::Group && !(numeric && s.slots > 512)));
+    }
+    if (nonempty <= 1) return last;
+    for (int b = 1; b <= plan.table.nb; ++b)
+        if (plan.spec[b].many > 0 && counts[b] >= kManyApart) small = false;
+    return small ? last : 0;
 }
 #define MSP_NUM_BATCH_SHAPES(X) X(32, 12) X(32, 8) X(32, 4) X(64, 8) X(64, 4) X(64, 2)
 #define MSP_SYM_LIST_SHAPES(X) X(256, 8) X(512, 16) X(1024, 16)
@@ -527,7 +560,7 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
         MSP_NUM_BATCH_SHAPES(X)
 #undef X
     } else if (s.kind == Kind::Group) {
-        const int lanes = s.lanes == 64 && s.slots == 128 && rows >= kManyRows ? 32 : s.lanes;
+        const int lanes = numeric_lanes(s, rows);
 #define X(G, T)                                                                                            \
     if (lanes == G && s.slots == T) {                                                                      \
         const int grid = group_grid(h, (const void*)k_num_group<G, T, VT, BATCH>, rows, 256 / G);         \
@@ -539,7 +572,7 @@ static msp_status launch_numeric_t(msp_handle* h, const BinSpec& s, Work wk, int
 #undef X
         // one wave per row
 #define X(T)                                                                                               \
-    if (s.lanes == 64 && s.slots == T) {                                                                   \
+    if (lanes == 64 && s.slots == T) {                                                                   \
         const int grid = group_grid(h, (const void*)k_num_row<T, VT, BATCH>, rows, 1, 64);                \
         k_num_row<T, VT, BATCH><<<grid, 64, 0, st>>>(wk, op.arp, op.acol, av, op.brp, op.bcol, bv, crp,   \
                                                      ccol, cval, cnt_out, info, mp, h->u.as<int32_t>(),   \
@@ -815,26 +848,19 @@ void sum_parts(const int (*part)[kPartStride], int out[kNB]) {
     }
 }
 
-// Launch the kernels of every nonempty bin.  With one nonempty bin, or when
-// every nonempty bin is a hash bin of the small kernels (whose larger tables
-// subsume the smaller ones), one kernel takes all rows in their natural
-// order (no scatter; these kernels handle smaller and empty rows too).
-// Otherwise row ids are scattered into per-bin lists first.
+// Launch the kernels of every nonempty bin.  One kernel takes all rows in their
+// natural order where it can (single_bin: no scatter; these kernels handle
+// smaller and empty rows too).  Otherwise row ids are scattered into per-bin
+// lists first.
 static msp_status run_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, const BinPlan& plan,
                            const int* counts, const int32_t* key, bool numeric,
                            const int64_t* crp, int32_t* ccol, void* cval, int32_t* rnnz, int done_bin,
                            int32_t* cnt_out = nullptr) {
     const int m = (int)A->nrows;
     const int nb = plan.table.nb;
-    int nonempty = 0, last = -1;
-    bool all_group = true;
-    for (int b = 1; b <= nb; ++b)
-        if (counts[b] > 0 && b != done_bin) {
-            ++nonempty;
-            last = b;
-            all_group = all_group && (plan.spec[b].kind == Kind::Group || plan.spec[b].kind == Kind::Batch);
-        }
-    if (nonempty == 0) return MSP_OK;
+    bool any = false;
+    for (int b = 1; b <= nb; ++b) any = any || (counts[b] > 0 && b != done_bin);
+    if (!any) return MSP_OK;
     DevInfo* info = h->info.as<DevInfo>();
     // what the symbolic Block bins left, after all bins
     auto rest = [&]() -> msp_status {
@@ -850,7 +876,8 @@ static msp_status run_bins(msp_handle* h, const msp_csr* A, const msp_csr* B, co
     auto symq = [&](int b) { return &info->queue[0][b][0]; };
     // bin done_bin was already processed: its rows must not be taken again
     const bool done_rows = done_bin > 0 && counts[done_bin] > 0;
-    if (!done_rows && (nonempty == 1 || all_group)) {
+    const int last = done_rows ? 0 : single_bin(plan, counts, numeric, done_bin);
+    if (last > 0) {
         const msp_status r =
             numeric ? launch_numeric(h, plan.spec[last], m, nullptr, A, B, crp, ccol, cval, cnt_out, last)
                     : launch_symbolic(h, plan.spec[last], m, nullptr, A, B, rnnz, symq(last));
@@ -1334,6 +1361,26 @@ extern "C" int msp_internal_symbolic_route(long long ncols, long long bnnz, int 
 // For tests of the dispatch: threads a row of the global bin gets among `rows`.
 extern "C" int msp_internal_threads_of_long_rows(int rows, int num_cu) {
     return msp::two_per_cu(rows, num_cu) ? 512 : 1024;
+}
+
+// For tests of the dispatch: lanes of a numeric row of 33 to 512 outputs among
+// `rows` (0: another kernel's), and the bin that takes all rows of given bin
+// sizes, as its bound (0: none).
+extern "C" int msp_internal_numeric_lanes(int nnz, int rows, int hash_scale, int group_scale) {
+    msp_tuning t = msp::default_tuning();
+    t.hash_scale = hash_scale;
+    t.group_scale = group_scale;
+    const msp::BinPlan p = msp::numeric_plan(t, false);
+    const msp::BinSpec& s = p.spec[msp::bin_of(p.table, nnz)];
+    return s.kind == msp::Kind::Group ? msp::numeric_lanes(s, rows) : 0;
+}
+extern "C" int msp_internal_single_bin(const int* nnz, const int* rows, int n, int numeric) {
+    const msp::BinPlan p = numeric ? msp::numeric_plan(msp::default_tuning(), false)
+                                   : msp::symbolic_plan(msp::default_tuning(), false);
+    int counts[msp::kNB] = {};
+    for (int i = 0; i < n; ++i) counts[msp::bin_of(p.table, nnz[i])] += rows[i];
+    const int b = msp::single_bin(p, counts, numeric != 0, 0);
+    return b > 0 && b < p.table.nb ? p.table.umax[b] : b;
 }
 
 // For tests of the dispatch: slots of the hash behind the workgroup sort for

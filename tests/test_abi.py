@@ -53,6 +53,37 @@ def test_only_the_bitmap_bin_takes_the_slab():
     assert route(10 ** 9, 1 << 32, 1024, 1) == 0
 
 
+def test_many_short_rows_share_a_wave_under_every_hash_scale():
+    """By the rows' bound, not the table's slots; group_scale still widens them."""
+    lib = ctypes.CDLL(binding.LIB_PATH)
+    for scale in (1, 2):
+        for nnz in (33, 64):
+            assert lib.msp_internal_numeric_lanes(nnz, 8191, scale, 0) == 64
+            assert lib.msp_internal_numeric_lanes(nnz, 8192, scale, 0) == 32
+            assert lib.msp_internal_numeric_lanes(nnz, 8192, scale, 1) == 64
+        assert lib.msp_internal_numeric_lanes(65, 10 ** 6, scale, 0) == 64
+
+
+def test_one_launch_only_where_it_serves_every_row():
+    lib = ctypes.CDLL(binding.LIB_PATH)
+
+    def single(sizes, numeric):
+        nnz, rows = ((ctypes.c_int * len(sizes))(*x) for x in zip(*sizes))
+        return lib.msp_internal_single_bin(nnz, rows, len(sizes), numeric)
+    assert single([(50, 1000), (200, 1000)], 1) == 256
+    assert single([(100, 10 ** 6), (200, 1000)], 1) == 256
+    assert single([(50, 10 ** 6)], 1) == 64
+    assert single([(400, 10 ** 6)], 1) == 512
+    assert single([(50, 65_535), (200, 1000)], 1) == 256
+    assert single([(50, 65_536), (200, 1000)], 1) == 0       # many short rows share waves
+    assert single([(50, 1000), (400, 1000)], 1) == 0         # the 1024-slot kernel is for its own rows
+    assert single([(50, 1000), (1000, 1000)], 1) == 0
+    assert single([(50, 1000), (400, 1000), (1000, 5)], 0) == 1024
+    assert single([(50, 65_535), (400, 1000)], 0) == 512
+    assert single([(50, 65_536), (400, 1000)], 0) == 0
+    assert single([(50, 1000), (1025, 1)], 0) == 0
+
+
 def test_few_long_rows_get_a_compute_unit_each():
     lib = ctypes.CDLL(binding.LIB_PATH)
     for rows in (1, 30, 256, 1505, 4096):

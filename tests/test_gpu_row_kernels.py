@@ -477,3 +477,18 @@ def test_row_kernel_most_products(h, total, na, alone, dtype):
         got = plan.result(0).to_host()
         oracle.compare(got.row_ptr, got.col, got.val, ref, tol)
     plan.close()
+
+
+@pytest.mark.parametrize("rows", [8191, 8192, 20_479, 20_480])
+@pytest.mark.parametrize("tuning", [(1, 0, 4096, 1024, 8), (2, 0, 4096, 1024, 8), (1, 1, 4096, 1024, 8),
+                                    (2, 2, 4096, 1024, -1)])
+def test_many_short_rows_under_every_scale(h, rows, tuning):
+    """Both sides of the row counts from which short rows share a wave, alone and
+    with longer rows among them, under the tunings that shape their bin."""
+    rng = np.random.default_rng(rows)
+    B = gen.erdos_renyi(900, 60_000, 7, seed=54)
+    A = gen.erdos_renyi(rows, 900, 7, seed=55)
+    check_full(h, A, B, tuning=tuning)
+    for n in (rows + 900, 66_000 + rows):
+        k = np.where(rng.random(n) < 0.03, rng.choice([20, 35, 60] if n < 66_000 else [20, 35], size=n), 7)
+        check_full(h, gen.erdos_renyi(n, 900, k, seed=56), B, tuning=tuning)
