@@ -2733,18 +2733,22 @@ k_num_block(Work wk,
                 const int h = hash_slot_of<T>(keys, j, &e2);
                 if (h >= 0) atomicAdd(&vals[h], prod);
                 else s_fail = 1;
+                // a full table: every further column would be looked for in all of it
+                return __ballot(h < 0) == 0;
             };
             if ((long long)nact * BS <= 8 * total) {       // uniform
                 int t = -1;
                 for (long long q = tid; q < total; q += BS) {
                     if (t < 0) t = owner_search(s_off, nact, q);
                     else while (s_off[t] <= q) ++t;
-                    add(t, q);
+                    if (!add(t, q)) break;
                 }
             } else {
-                for (long long q = tid; q < total; q += BS) add(owner_search(s_off, nact, q), q);
+                for (long long q = tid; q < total; q += BS)
+                    if (!add(owner_search(s_off, nact, q), q)) break;
             }
             __syncthreads();
+            if (s_fail) break;                             // uniform (set again after the next barrier only)
         }
         // compaction: thread tid owns slots [tid*PER, tid*PER + PER)
         int32_t rk[PER];

@@ -100,8 +100,11 @@ __device__ __forceinline__ int row_hash(
             const double prod = s_a[t] * to_f64(bval[bi]);
             const int h = hash_slot_of<T>(kt, j, &re);
             if (h >= 0) atomicAdd(&vt[h], prod);
+            // a full table: every further column would be looked for in all of it
+            if (__ballot(h < 0)) break;
         }
         lds_fence();
+        if (__ballot(re != 0)) break;
     }
     // compact the occupied slots to the front, in place: a slot moves to a
     // position no later than its own, and the wave reads its 64 slots before

@@ -492,3 +492,23 @@ def test_many_short_rows_under_every_scale(h, rows, tuning):
     for n in (rows + 900, 66_000 + rows):
         k = np.where(rng.random(n) < 0.03, rng.choice([20, 35, 60] if n < 66_000 else [20, 35], size=n), 7)
         check_full(h, gen.erdos_renyi(n, 900, k, seed=56), B, tuning=tuning)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("room", [40, 100, 200, 400, 900, 1500, 3000])
+@pytest.mark.parametrize("na,length", [(700, 12), (60, 150), (300, 60), (2000, 12)])
+def test_rooms_far_too_small(h, room, na, length, dtype):
+    """Rows of 8000 to 24,000 products in rooms that their outputs fill many times
+    over, in every kernel that takes a capacity, beside rows that fit."""
+    rng = np.random.default_rng(na + room)
+    B = gen.erdos_renyi(4000, 100_000, np.where(np.arange(4000) < 2000, length, 2), seed=73, dtype=dtype)
+    rows = [np.sort(rng.permutation(2000)[:na]) if i % 5 == 0 else 2000 + np.sort(rng.permutation(2000)[:18])
+            for i in range(200)]
+    A = _csr(rows, 4000, rng, dtype)
+    import oracle
+    pred = binding.Predictor(h, learned.fixed_capacity_params(np.log2(room) / 16.0))
+    C, st = h.spgemm_learned(pred, to_dev(A), to_dev(B))
+    assert st["overflow_rows"] == 40
+    got = C.to_host()
+    oracle.compare(got.row_ptr, got.col, got.val, oracle.spgemm(A, B), TOL[np.dtype(dtype)])
+    pred.close()
