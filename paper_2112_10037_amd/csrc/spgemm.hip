@@ -54,7 +54,7 @@ static void add_bin(BinPlan& p, int umax, BinSpec s) {
 // rows with T key slots, lane groups (k_num_group) for larger tables.
 static int sym_batch_rows(int T) { return T <= 64 ? 16 : 1024 / T; }
 
-static void add_small_bins(BinPlan& p, const msp_tuning& t, int limit, bool numeric) {
+static void add_small_bins(BinPlan& p, const msp_tuning& t, int limit, bool numeric, int most_slots = 1024) {
     static const int umax[7] = {16, 32, 64, 128, 256, 512, 1024};
     static const int g0[7] = {8, 16, 64, 64, 64, 64, 64};
     int covered = 0;
@@ -75,7 +75,7 @@ static void add_small_bins(BinPlan& p, const msp_tuning& t, int limit, bool nume
         } else if (T <= 64) {
             const int R = (T == 32 ? (t.group_scale == 0 ? 12 : 8 >> (t.group_scale - 1)) : 8 >> t.group_scale);
             add_bin(p, umax[i], BinSpec{Kind::Batch, R, T});
-        } else if (T <= 1024) {
+        } else if (T <= most_slots) {
             int G = std::min(64, g0[i] << t.group_scale);
             G = std::min(G, T / 2);
             add_bin(p, umax[i], BinSpec{Kind::Group, G, T, 0, umax[i] == 64 ? std::min(64, 32 << t.group_scale) : 0});
@@ -109,10 +109,11 @@ BinPlan numeric_plan(const msp_tuning& t, bool force_spill, bool rule) {
     memset(&p.table, 0, sizeof(p.table));
     p.table.nb = 1;
     if (!force_spill) {
-        add_small_bins(p, t, std::min(t.block_rows, t.spill_nnz), true);
+        // (the capacity rule of the learned product works with small bins of up to
+        // 512 slots and 513..2048 as one bin; 1024 slots and the split at 1024 are
+        // the kernels' alone)
+        add_small_bins(p, t, std::min(t.block_rows, t.spill_nnz), true, rule ? 512 : 1024);
         int last = p.table.umax[p.table.nb - 1];
-        // (split at 1024 for the kernels alone: the capacity rule of the
-        // learned product works with 513..2048 as one bin)
         int list[5] = {512, 1024, 2048, 4096, t.spill_nnz};
         std::sort(list, list + 5);
         for (int u : list) {

@@ -313,3 +313,21 @@ def test_capacity_rule(h, k, l, pt, delta, expect):
     got = C.to_host()
     oracle.compare(got.row_ptr, got.col, got.val, oracle.spgemm(A, B), TOL[np.dtype(np.float64)])
     pred.close()
+
+
+@pytest.mark.parametrize("hash_scale,k,l,pt,expect", [
+    (1, 9, 50, 199.5, 200),       # bound 450 > 2 * 200, bins (128, 256] and (256, 512]
+    (2, 9, 50, 199.5, 450),       # (128, 512] is one bin of the rule: the bound
+    (2, 5, 50, 119.5, 120),       # bound 250 > 2 * 120, bins (64, 128] and (128, 512]
+])
+def test_capacity_rule_goes_by_its_own_bins(h, hash_scale, k, l, pt, expect):
+    """The rule's bins under hash_scale 2, where 257 to 512 outputs and 129 to 256
+    share one (the kernels' bins are apart)."""
+    m = 300
+    A, B = _blocks(m, k, l)
+    pred = binding.Predictor(h, learned.fixed_capacity_params(np.log2(pt) / 16.0))
+    C, st = h.spgemm_learned(pred, to_dev(A), to_dev(B), tuning=(hash_scale, 0, 4096, 1024, 8))
+    assert st["sum_cap"] == m * expect
+    got = C.to_host()
+    oracle.compare(got.row_ptr, got.col, got.val, oracle.spgemm(A, B), TOL[np.dtype(np.float64)])
+    pred.close()
