@@ -10,16 +10,20 @@
 //   * a symbolic pass counts row_nnz_i = |union of the column sets| with an
 //     LDS hash, lists or a bitmap (whole waves or workgroups per row) or
 //     an n-bit bitmap for the largest rows;
-//   * a numeric pass adds a_ik * b_kj into an LDS hash of (key, FP64 value)
-//     sized by the exact row_nnz_i, then writes the row in column order (a
-//     rank count for short rows, an LDS bitonic sort for long rows); rows
-//     too large for LDS are cut into column slices whose bitmap, word ranks
-//     and FP64 accumulator (indexed by the column's rank) fit the LDS, and
-//     each slice goes out in column order from its bitmap, with no sort.
-// Products of a row are enumerated "flattened": a lane group loads a chunk
-// of A's row, prefix-sums the B-row lengths, and every lane takes the next
-// product index and finds its A entry by binary search, so that the lanes
-// stay busy whatever the B-row lengths are.
+//   * a numeric pass, by the exact row_nnz_i: the shortest rows merge B's rows
+//     a lane each; longer ones hold their products in registers (a wave or a
+//     workgroup a row) and sum them at the ranks of a bitmap of the columns'
+//     span or put them in order by a counting sort; rows past the registers
+//     add into an LDS hash of (key, FP64 value) that is then put in order;
+//     rows too large for LDS are cut into column slices whose bitmap, word
+//     ranks and FP64 accumulator (indexed by the column's rank) fit the LDS,
+//     and each slice goes out in column order from its bitmap, with no sort.
+// Products of a row are enumerated "flattened", so that the lanes stay busy
+// whatever the B-row lengths are: a chunk of A's row is loaded, the B-row
+// lengths prefix-summed, and every lane takes the next product index.  Its A
+// entry is the number of entries that end before it: a mark at each entry's
+// last product, counted below the lane (RowWalk, WaveWindow), or in the hashes
+// and lane groups a binary search and a walk.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -758,13 +762,14 @@ __device__ __forceinline__ int hash_insert_key(int32_t* keys, int32_t j, int* er
 
 // Slot of key j in an LDS (key, value) table, inserting it if absent.
 template <int T>
-__device__ __forceinline__ int hash_slot_of(int32_t* keys, int32_t j, int* err) {
+__device__ __forceinline__ int hash_slot_of(int32_t* keys, int32_t j, int* err, bool* fresh = nullptr) {
     uint32_t h = hash_slot<T>(j);
     for (int probe = 0; probe < T; ++probe) {
         int32_t k = keys[h];
         if (k == j) return (int)h;
         if (k == kEmpty) {
             int32_t old = atomicCAS(&keys[h], kEmpty, j);
+            if (old == kEmpty && fresh) *fresh = true;
             if (old == kEmpty || old == j) return (int)h;
         }
         h = (h + 1) & (T - 1);
@@ -2670,7 +2675,7 @@ k_num_block(Work wk,
     long long* const s_bst = s_ob + BS;
     __shared__ double s_a[BS];
     __shared__ BlockScanSmem<BS> sm;
-    __shared__ int s_fail;
+    __shared__ int s_fail, s_new;                          // s_new: columns so far (with cnt_out)
     __shared__ int s_mm[2][BS / 64];
     const int tid = threadIdx.x;
     int err = 0;
@@ -2700,9 +2705,10 @@ k_num_block(Work wk,
     for (int row = next_row(); row >= 0; row = next_row()) {
         const long long bo = row_boff<BATCH>(mp, row);
         for (int s = tid; s < T; s += BS) { keys[s] = kEmpty; vals[s] = 0.0; }
-        if (tid == 0) s_fail = 0;
+        if (tid == 0) s_fail = s_new = 0;
         __syncthreads();
         const long long a0 = arp[row], a1 = arp[row + 1];
+        const long long room = crp[row + 1] - crp[row];
         for (long long c0 = a0; c0 < a1; c0 += BS) {
             const long long p = c0 + tid;
             long long len = 0, bst = 0;
@@ -2730,10 +2736,18 @@ k_num_block(Work wk,
                 const int32_t j = bcol[bi];
                 const double prod = s_a[t] * to_f64(bval[bi]);
                 int e2 = 0;
-                const int h = hash_slot_of<T>(keys, j, &e2);
+                bool fresh = false;
+                const int h = hash_slot_of<T>(keys, j, &e2, &fresh);
                 if (h >= 0) atomicAdd(&vals[h], prod);
                 else s_fail = 1;
-                // a full table: every further column would be looked for in all of it
+                if (cnt_out) {
+                    // more columns than the room: the row is over (in a table that
+                    // fills up, every further column would be looked for in all of it)
+                    const uint64_t m = __ballot(fresh);
+                    const int more = __builtin_popcountll(m);
+                    if (m && (tid & 63) == __builtin_ctzll(m) && atomicAdd(&s_new, more) + more > room) s_fail = 1;
+                    return __hip_atomic_load(&s_fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0;
+                }
                 return __ballot(h < 0) == 0;
             };
             if ((long long)nact * BS <= 8 * total) {       // uniform

@@ -70,7 +70,8 @@ __device__ __forceinline__ int row_hash(
     const VT* __restrict__ bval, int32_t* __restrict__ ccol, VT* __restrict__ cval, int32_t* __restrict__ cnt_out,
     int32_t* kt, double* vt, long long* s_off, long long* s_bst, double* s_a) {
     const int lane = threadIdx.x & 63;
-    int re = 0;                                  // the table overflowed
+    int re = 0;                                  // the table or the room overflowed
+    int ncol = 0;                                // columns that this lane saw added
 #pragma unroll
     for (int i = 0; i < T / 64; ++i) { kt[lane + i * 64] = kEmpty; vt[lane + i * 64] = 0.0; }
     lds_fence();
@@ -98,10 +99,20 @@ __device__ __forceinline__ int row_hash(
             const long long bi = s_bst[t] + q;
             const int32_t j = bcol[bi];
             const double prod = s_a[t] * to_f64(bval[bi]);
-            const int h = hash_slot_of<T>(kt, j, &re);
-            if (h >= 0) atomicAdd(&vt[h], prod);
-            // a full table: every further column would be looked for in all of it
-            if (__ballot(h < 0)) break;
+            // A full table ends the row (every further column would be looked for
+            // in all of it), and so do more columns than the room, which is only
+            // looked at where registers allow it.
+            if constexpr (T > 512) {
+                bool fresh = false;
+                const int h = hash_slot_of<T>(kt, j, &re, &fresh);
+                if (h >= 0) atomicAdd(&vt[h], prod);
+                ncol += __builtin_popcountll(__ballot(fresh));
+                if ((cnt_out && ncol > expect) || __ballot(h < 0)) { re = 1; break; }
+            } else {
+                const int h = hash_slot_of<T>(kt, j, &re);
+                if (h >= 0) atomicAdd(&vt[h], prod);
+                if (__ballot(h < 0)) break;
+            }
         }
         lds_fence();
         if (__ballot(re != 0)) break;
