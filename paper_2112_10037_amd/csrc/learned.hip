@@ -713,8 +713,11 @@ extern "C" msp_status msp_predictor_load(msp_handle* h, msp_predictor* p, const 
 
 // One forward and backward pass on batch rows idx[0..batch) and the gradient;
 // with `adam`, also the parameters' update (p->step counts this step).
+// (k_mlp_tiles steps over the batch in 32 bits, kTileWG tiles at a time)
+constexpr int kMaxBatch = INT32_MAX - 2 * kTile * kTileWG;
 static msp_status grad_step(msp_handle* h, msp_predictor* p, const float* feats, const float* targets, int64_t n,
                             const int32_t* idx, int batch, float* loss_dev, const msp_train_opts* adam) {
+    if (batch > kMaxBatch) return fail(MSP_ERR_INDEX_OVERFLOW, "at most %d samples a batch", kMaxBatch);
     const int parts = std::min((batch + kTile - 1) / kTile, kTileWG);
     msp_status s;
     if ((s = p->part.ensure((size_t)parts * kPartRow * 8)) != MSP_OK ||

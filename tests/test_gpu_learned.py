@@ -331,3 +331,18 @@ def test_capacity_rule_goes_by_its_own_bins(h, hash_scale, k, l, pt, expect):
     got = C.to_host()
     oracle.compare(got.row_ptr, got.col, got.val, oracle.spgemm(A, B), TOL[np.dtype(np.float64)])
     pred.close()
+
+
+@pytest.mark.parametrize("batch", [2 ** 31 - 1, 2 ** 31 - 2048])
+def test_batches_past_32_bits_are_refused(h, batch):
+    """(refused on the host: the index array stays unread)"""
+    x, t = _rows(8, n=500)
+    dx, dt = _dev(x), _dev(t)
+    idx = _dev(np.zeros(16, np.int32))
+    p = binding.Predictor(h, gen.mlp_init(3).astype(np.float32))
+    before = p.get()[0]
+    args = (h._h, p._p, dx.data_ptr(), dt.data_ptr(), 500, idx.data_ptr())
+    assert h._lib.msp_predictor_grad(*args, batch, None, None) == 7
+    assert h._lib.msp_predictor_train(*args, 1, batch, None, None) == 7
+    assert np.array_equal(p.get()[0], before)
+    p.close()
