@@ -101,8 +101,13 @@ typedef void (*msp_free_fn)(void* ctx, void* ptr, void* stream);
 /* Tuning of the per-bin accumulators.  Zero-initialised fields mean "use the
  * library default".  See msp_autotune. */
 typedef struct {
-    int32_t hash_scale;     /* table slots = nextpow2(bound) << hash_scale (1..2) */
-    int32_t group_scale;    /* lanes per row = default << group_scale (0..2)      */
+    int32_t hash_scale;     /* slots of a bin's hash table = nextpow2(bound) <<
+                               hash_scale (1..2), at most 8192.  Rows whose
+                               products fit registers, the workgroup sort or
+                               the symbolic lists use none                      */
+    int32_t group_scale;    /* lanes per row << group_scale (0..2): rows of at
+                               most 32 outputs without the merge, and many rows
+                               of 33 to 64; longer rows have a whole wave       */
     int32_t spill_nnz;      /* numeric rows with more nnz use the global path
                                (a power of two, 256..4096)                       */
     int32_t block_rows;     /* rows with bound above this (a power of two,

@@ -25,11 +25,13 @@ namespace msp {
 // Bound by LDS and barriers (about ten a row, spread over the compute unit's
 // two to nine workgroups).  Measured on a sparse power-law matrix of 2^20 rows
 // (FP32): rows of 2049 to 4096 outputs 3272 us in the LDS hash with its radix
-// sort before, 1138 us here; rows of 1025 to 2048 2741 us (with those of 513
-// to 1024), 767 us here; rows of 513 to 1024 outputs of a uniform FP64 matrix
-// 1329 -> 488 us.  Nine products a thread spill (1708 and 1022 us, 543 us);
-// half the buckets 1160, 888 and 489 us; 128 registers for the smaller
-// workgroups too 1139, 765 and 524 us.
+// sort before, 1257 us here and 373 in the hash behind; rows of 1025 to 2048
+// 2741 us (with those of 513 to 1024), 800 and 146 here; rows of 513 to 1024
+// outputs of a uniform FP64 matrix 1329 -> 284 us.  Without the check of each
+// column's neighbour and the rows' marks, and with one draw a row, these took
+// 1138, 767 and 488 us; then nine products a thread, which spill, 1708, 1022 and
+// 543; half the buckets 1160, 888 and 489; 128 registers for the smaller
+// workgroups too 1139, 765 and 524.
 constexpr int kSortBucket = 256;
 constexpr int kSortR = 8;
 

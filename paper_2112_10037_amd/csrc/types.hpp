@@ -82,9 +82,12 @@ struct DevInfo {
     int long_n;                           // row statistics: rows taken apart as long rows
     int long_chunks;                      // and their chunks
     // row queues of the persistent one-row-per-workgroup kernels, per phase
-    // (symbolic, numeric) and bin, plus [1][kNB] for the global bin's rows
-    // without a window record: {slots handed out, workgroups done}, zero
-    // between launches
+    // (symbolic, numeric) and bin: {slots handed out, workgroups done}, zero
+    // between launches.  A bin's queue serves one kernel after the other on the
+    // bin's stream (numeric: the hash behind the sort).  [1][kNB] is that of the
+    // global bin's rows without a window record, which run behind it on its
+    // stream; [0][kNB] that of the rows the symbolic lists left, which run once,
+    // after every bin has joined.
     unsigned queue[2][kNB + 1][2];
     int sym_part[kParts][kPartStride];    // rows per symbolic bin, per partition
     int num_part[kParts][kPartStride];    // rows per numeric bin, per partition

@@ -289,9 +289,10 @@ constexpr int kRowStep = 4;
 // the product), so both went; HBM is at 15-20%.  One wave a workgroup, so that
 // LDS is handed out a row at a time: 16 waves a compute unit up to T = 512.
 // Measured against the hash kernels it replaced: 300,763 27-point rows (FP64,
-// 729 products, 125 outputs) 1311 -> 617 us; 260,000 banded rows (FP32, 256
-// products) 735 -> 307 us; the 257- to 512-output rows of a uniform FP64
-// matrix of 262,144 rows 2820 -> 475 us (a workgroup a row before).  At three
+// 729 products, 125 outputs) 1311 -> 588 us; 260,000 banded rows (FP32, 256
+// products) 735 -> 303 us; the 257- to 512-output rows of a uniform FP64
+// matrix of 262,144 rows 2820 -> 523 us (a workgroup a row before; 475 without
+// the count of distinct columns where there are as many outputs as products).  At three
 // waves a SIMD without spills the FP64 kernel up to T = 512 is no faster (657
 // us on the 27-point rows at two, 670 at three, 617 at four); T = 1024, where
 // LDS leaves 11 waves a compute unit, takes 475 us at two and 620 at three
